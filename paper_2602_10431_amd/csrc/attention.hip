@@ -35,11 +35,13 @@ struct AttnDev {
     const int4* items;           // prefill work list: (sequence or -1, query tile, first compact row, rows) per item
     const int32_t* n_items;
     int items_max;               // host bound on the number of work items (row stride of the logical grid)
-    const half_t* k_cache;
-    const half_t* v_cache;
+    half_t* k_cache;
+    half_t* v_cache;
     const int32_t* kv_old;
     int cap;
     float scale_log2;            // log2(e) / sqrt(d)
+    const float2* cs;            // decode: [row][D / 2] (cos, sin) at the row's position
+    int32_t* arrive;             // decode, split keys: [row][kv head] ranges done so far
     float* part;                 // decode, split keys: [row][head][split][D + 2] fp32 (numerators, maximum, denominator)
     int n_split;                 // key ranges per (row, kv head); 1 = no split
 };
@@ -448,13 +450,21 @@ __device__ __forceinline__ float key_group_sum(float x) {
     return x;
 }
 
-// Decode-style attention: workgroup = (executed row, kv head); REP query heads share the kv head.
+// Accesses that are coherent across the XCDs (and with the counter they are used with).
+__device__ __forceinline__ void agent_store(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float agent_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Decode-style attention: workgroup = (executed row, kv head); REP query heads share the kv head.  The kernel also
+// does what a launch of its own would do before it (rotary embedding and cache append: 5 us per layer for a few KB):
+// the queries are rotated as they are read, the call's own keys (rows row_begin .. i of the same sequence) are rotated
+// from the compact buffer, and the workgroup appends its own row's key and value.  The cached keys are streamed.
 // SPLIT: with few rows there are fewer workgroups than the chip needs to saturate HBM (8 rows x 32 kv heads is
-// one workgroup per CU: 4.1 TB/s against 6.0 with eight per CU), so the keys of a (row, kv head) are cut into
-// n_split contiguous ranges (multiples of the 64- or 128-key step) that separate workgroups stream; each writes
-// its unnormalised sums with their maximum and denominator, and attn_merge_kernel combines the ranges in order.
+// one workgroup per CU: 4.1 TB/s against 6.0 with eight per CU), so the cached keys of a (row, kv head) are cut into
+// n_split contiguous ranges (multiples of the 64- or 128-key step) that separate workgroups stream (range 0 also takes the
+// new keys); each writes its unnormalised sums with their maximum and denominator, and the one that arrives last
+// combines the ranges in range order, so the result does not depend on who that is.
 template <int D, int REP, bool SPLIT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, SPLIT ? 1 : REP == 1 ? 8 : 1)
 attn_decode_kernel(AttnDev p) {
     constexpr int LPK = D / 8;            // lanes per key (each lane owns 8 of the D columns)
     constexpr int KPW = 64 / LPK;         // keys per wave per step
@@ -463,49 +473,62 @@ attn_decode_kernel(AttnDev p) {
     const int i = blockIdx.y;
     if (i >= *p.count) return;
     const int hk = blockIdx.x;
-    const int b = p.row_seq[i];
-    const int row_begin = p.cu_exec[b];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = lane % LPK, slot = lane / LPK;
 
-    const half_t* kbase;
-    const half_t* vbase;
-    int kv_stride, n_keys;
-    if (p.k_cache) {
-        kv_stride = D;                        // cache [B][n_kv_heads][cap][D]: one contiguous stream per workgroup
-        kbase = p.k_cache + (static_cast<size_t>(b) * p.nkv + hk) * p.cap * D;
-        vbase = p.v_cache + (static_cast<size_t>(b) * p.nkv + hk) * p.cap * D;
-        n_keys = min(p.kv_old[b] + (i - row_begin) + 1, p.cap);
-    } else {
-        kv_stride = p.width;
-        kbase = p.qkv + static_cast<size_t>(row_begin) * p.width + (p.nh + hk) * D;
-        vbase = kbase + p.nkv * D;
-        n_keys = i - row_begin + 1;
+    // This row's query, key and value and their rotation depend on nothing but i: they are requested first and arrive
+    // while the chain row -> sequence -> cache length is followed.  This lane's 8 columns pair with those D / 2 away; the
+    // first half subtracts.
+    const int psub = sub < LPK / 2 ? sub + LPK / 2 : sub - LPK / 2;
+    const float sign = sub < LPK / 2 ? -1.0f : 1.0f;
+    const float2* cs0 = p.cs + (sub % (LPK / 2)) * 8;
+    auto rotate = [&](const half8_t& mine, const half8_t& other, const float2* cs, half8_t& out) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            out[e] = static_cast<half_t>(fmaf(static_cast<float>(mine[e]), cs[e].x, sign * (static_cast<float>(other[e]) * cs[e].y)));
+    };
+    const half_t* row_i = p.qkv + static_cast<size_t>(i) * p.width;
+    half8_t qa[REP], qb[REP];
+    float2 cs_i[8];
+#pragma unroll
+    for (int r = 0; r < REP; ++r) {
+        qa[r] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + r) * D + sub * 8);
+        qb[r] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + r) * D + psub * 8);
     }
+    const half8_t ka = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + sub * 8);
+    const half8_t kb_ = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + psub * 8);
+    const half8_t v_own = *reinterpret_cast<const half8_t*>(row_i + (p.nh + p.nkv + hk) * D + sub * 8);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) cs_i[e] = cs0[static_cast<size_t>(i) * (D / 2) + e];
+
+    const int b = p.row_seq[i];
+    const int row_begin = p.cu_exec[b];
+    const size_t head_off = (static_cast<size_t>(b) * p.nkv + hk) * p.cap * D;   // cache [B][n_kv_heads][cap][D]
+    const half_t* kbase = p.k_cache + head_off;
+    const half_t* vbase = p.v_cache + head_off;
+    const int old = p.kv_old[b];
+    const int own = i - row_begin;                               // place of this row among the sequence's new rows
+    const int n_cached = min(old, p.cap);
+    const int n_new = max(min(own + 1, p.cap - old), 0);         // new keys that fit the cache; later ones are not seen
 
     float q[REP][8];
+    half8_t k_own;
 #pragma unroll
     for (int r = 0; r < REP; ++r) {
-        const half8_t qv = *reinterpret_cast<const half8_t*>(p.qkv + static_cast<size_t>(i) * p.width + (hk * REP + r) * D + sub * 8);
+        half8_t qr;
+        rotate(qa[r], qb[r], cs_i, qr);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) q[r][e] = static_cast<float>(qv[e]) * p.scale_log2;
+        for (int e = 0; e < 8; ++e) q[r][e] = static_cast<float>(qr[e]) * p.scale_log2;
     }
-    float m_run[REP], l_run[REP], o[REP][8];
-#pragma unroll
-    for (int r = 0; r < REP; ++r) {
-        m_run[r] = kNegBig;
-        l_run[r] = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[r][e] = 0.0f;
-    }
+    rotate(ka, kb_, cs_i, k_own);
 
     const int step = 4 * KPW;             // keys per workgroup step
-    int key_lo = 0, key_hi = n_keys;      // this workgroup's key range
+    int key_lo = 0, key_hi = n_cached;    // this workgroup's range of the cached keys
     if (SPLIT) {
         const int gran = UNR * step;
-        const int per = ((n_keys + p.n_split - 1) / p.n_split + gran - 1) / gran * gran;
-        key_lo = min(static_cast<int>(blockIdx.z) * per, n_keys);
-        key_hi = min(key_lo + per, n_keys);
+        const int per = ((n_cached + p.n_split - 1) / p.n_split + gran - 1) / gran * gran;
+        key_lo = min(static_cast<int>(blockIdx.z) * per, n_cached);
+        key_hi = min(key_lo + per, n_cached);
     }
     // The keys and values of the next step are requested before the current step is consumed, so the memory
     // pipe never drains while the lanes do their dot products and exponentials (keys past the end are clamped
@@ -515,11 +538,66 @@ attn_decode_kernel(AttnDev p) {
         const int k0 = kb + wave * KPW + slot;
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const int kc = min(k0 + u * step, n_keys - 1);      // n_keys >= 1: always a valid row
-            kn[u] = *reinterpret_cast<const half8_t*>(kbase + static_cast<size_t>(kc) * kv_stride + sub * 8);
-            vn[u] = *reinterpret_cast<const half8_t*>(vbase + static_cast<size_t>(kc) * kv_stride + sub * 8);
+            const int kc = max(min(k0 + u * step, n_cached - 1), 0);       // an empty cache: slot 0, loaded and not used
+            kn[u] = *reinterpret_cast<const half8_t*>(kbase + static_cast<size_t>(kc) * D + sub * 8);
+            vn[u] = *reinterpret_cast<const half8_t*>(vbase + static_cast<size_t>(kc) * D + sub * 8);
         }
     };
+
+    float m_run[REP], l_run[REP], o[REP][8];
+    // The row's own key starts the sums of one lane group of range 0 (and goes into the cache); the other groups start
+    // empty.
+    const bool mine = (!SPLIT || blockIdx.z == 0) && wave == 0 && slot == 0 && own < n_new;
+    if (mine) {
+        const size_t at = head_off + static_cast<size_t>(old + own) * D + sub * 8;
+        *reinterpret_cast<half8_t*>(p.k_cache + at) = k_own;
+        *reinterpret_cast<half8_t*>(p.v_cache + at) = v_own;
+    }
+#pragma unroll
+    for (int r = 0; r < REP; ++r) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc = fmaf(q[r][e], static_cast<float>(k_own[e]), acc);
+        acc = key_group_sum<LPK>(acc);
+        m_run[r] = mine ? acc : kNegBig;
+        l_run[r] = mine ? 1.0f : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[r][e] = mine ? static_cast<float>(v_own[e]) : 0.0f;
+    }
+    // the sequence's other new keys (none in a decode step of one token per sequence)
+    if (own > 0 && (!SPLIT || blockIdx.z == 0)) {
+        const int n_other = min(own, n_new);
+        for (int jb = 0; jb < n_other; jb += step) {             // uniform trip count
+            const int j = jb + wave * KPW + slot;
+            const bool ok = j < n_other;
+            const int rj = row_begin + min(j, own);
+            const half_t* row_k = p.qkv + static_cast<size_t>(rj) * p.width + (p.nh + hk) * D;
+            const half8_t ja = *reinterpret_cast<const half8_t*>(row_k + sub * 8);
+            const half8_t jo = *reinterpret_cast<const half8_t*>(row_k + psub * 8);
+            const half8_t vv = *reinterpret_cast<const half8_t*>(row_k + p.nkv * D + sub * 8);
+            float2 cs[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) cs[e] = cs0[static_cast<size_t>(rj) * (D / 2) + e];
+            half8_t kr;
+            rotate(ja, jo, cs, kr);
+#pragma unroll
+            for (int r = 0; r < REP; ++r) {
+                float acc = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc = fmaf(q[r][e], static_cast<float>(kr[e]), acc);
+                acc = key_group_sum<LPK>(acc);
+                const float s = ok ? acc : kNegBig;
+                const float mx = fmaxf(m_run[r], s);
+                const float alpha = exp2f(m_run[r] - mx);
+                const float pv = ok ? exp2f(s - mx) : 0.0f;
+                m_run[r] = mx;
+                l_run[r] = l_run[r] * alpha + pv;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[r][e] = fmaf(pv, static_cast<float>(vv[e]), o[r][e] * alpha);
+            }
+        }
+    }
+
     fetch(key_lo);
     for (int kb = key_lo; kb < key_hi; kb += UNR * step) {     // trip count is uniform over the workgroup
         const int k0 = kb + wave * KPW + slot;
@@ -531,7 +609,7 @@ attn_decode_kernel(AttnDev p) {
             kv[u] = kn[u];
             vv[u] = vn[u];
         }
-        fetch(min(kb + UNR * step, n_keys - 1));               // past the end: one redundant, unused fetch
+        fetch(kb + UNR * step);                                // past the end: one redundant, unused fetch
 #pragma unroll
         for (int r = 0; r < REP; ++r) {
             float s[UNR];
@@ -601,34 +679,48 @@ attn_decode_kernel(AttnDev p) {
         if (SPLIT) {
             // an empty range leaves num = 0, den = 0 and the maximum at its initial value: it drops out of the merge
             float* dst = p.part + ((static_cast<size_t>(i) * p.nh + hk * REP + r) * p.n_split + blockIdx.z) * (D + 2);
-            dst[e] = num;
-            if (e == 0) { dst[D] = mn; dst[D + 1] = den; }
+            agent_store(dst + e, num);
+            if (e == 0) { agent_store(dst + D, mn); agent_store(dst + D + 1, den); }
         } else {
             p.out[static_cast<size_t>(i) * (p.nh * D) + (hk * REP + r) * D + e] = static_cast<half_t>(num / den);
         }
     }
-}
-
-// Combines the key ranges of the split decode kernel: out = sum_s num_s 2^(m_s - m) / sum_s den_s 2^(m_s - m),
-// ranges taken in order.  One workgroup per (row, 256 / D heads).
-template <int D>
-__global__ void __launch_bounds__(256)
-attn_merge_kernel(AttnDev p) {
-    const int i = blockIdx.y;
-    if (i >= *p.count) return;
-    const int head = blockIdx.x * (256 / D) + threadIdx.x / D;
-    const int e = threadIdx.x % D;
-    if (head >= p.nh) return;
-    const float* src = p.part + (static_cast<size_t>(i) * p.nh + head) * p.n_split * (D + 2);
-    float mn = kNegBig;
-    for (int s = 0; s < p.n_split; ++s) mn = fmaxf(mn, src[s * (D + 2) + D]);
-    float num = 0.0f, den = 0.0f;
-    for (int s = 0; s < p.n_split; ++s) {
-        const float a = exp2f(src[s * (D + 2) + D] - mn);
-        num += src[s * (D + 2) + e] * a;
-        den += src[s * (D + 2) + D + 1] * a;
+    if (SPLIT) {
+        // The range that arrives last combines all of them: out = sum_s num_s 2^(m_s - m) / sum_s den_s 2^(m_s - m).  Nobody
+        // waits: a workgroup counts itself in and leaves unless it is the last.  The ranges may have run on different
+        // XCDs, whose L2s are not coherent with each other for plain accesses: the partial sums are written and read with
+        // agent-scope accesses (they go past the L2), and every thread's stores have completed (vmcnt 0, then the barrier)
+        // before thread 0 counts.  A release fence instead would write back a whole L2 per workgroup.
+        __shared__ int s_arrived;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) s_arrived = __hip_atomic_fetch_add(p.arrive + static_cast<size_t>(i) * p.nkv + hk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (s_arrived != p.n_split - 1) return;
+        for (int c = tid; c < REP * D; c += 256) {
+            const int r = c / D, e = c % D;
+            const float* src = p.part + (static_cast<size_t>(i) * p.nh + hk * REP + r) * p.n_split * (D + 2);
+            float num_s[kAttnSplitMax], m_s[kAttnSplitMax], den_s[kAttnSplitMax];
+            float mn = kNegBig;
+#pragma unroll
+            for (int s = 0; s < kAttnSplitMax; ++s) {            // all ranges are requested before any is used
+                const float* ps = src + min(s, p.n_split - 1) * (D + 2);
+                num_s[s] = agent_load(ps + e);
+                m_s[s] = agent_load(ps + D);
+                den_s[s] = agent_load(ps + D + 1);
+            }
+#pragma unroll
+            for (int s = 0; s < kAttnSplitMax; ++s) mn = fmaxf(mn, m_s[s]);
+            float num = 0.0f, den = 0.0f;
+#pragma unroll
+            for (int s = 0; s < kAttnSplitMax; ++s) {
+                const float a = s < p.n_split ? exp2f(m_s[s] - mn) : 0.0f;
+                num += num_s[s] * a;
+                den += den_s[s] * a;
+            }
+            p.out[static_cast<size_t>(i) * (p.nh * D) + (hk * REP + r) * D + e] = static_cast<half_t>(num / den);
+        }
     }
-    p.out[static_cast<size_t>(i) * (p.nh * D) + head * D + e] = static_cast<half_t>(num / den);
 }
 
 // CUs of the current device (queried once per device).
@@ -660,11 +752,20 @@ static hipError_t launch_decode_rep(const AttnDev& d, int rep, int rows, int nkv
 template <int D>
 static hipError_t launch_decode_d(const AttnDev& d, int rep, int rows, int nkv, hipStream_t stream) {
     if (d.n_split <= 1) return launch_decode_rep<D, false>(d, rep, rows, nkv, stream);
-    hipError_t e = launch_decode_rep<D, true>(d, rep, rows, nkv, stream);
-    if (e != hipSuccess) return e;
-    const dim3 grid((d.nh * D + 255) / 256, rows), block(256);
-    hipLaunchKernelGGL(attn_merge_kernel<D>, grid, block, 0, stream, d);
-    return hipGetLastError();
+    return launch_decode_rep<D, true>(d, rep, rows, nkv, stream);
+}
+
+bool attention_is_decode(bool cache, int T, int B, int nh, int nkv) {
+    const int rep = nh / nkv;
+    return cache && T <= 4 * B && (rep == 1 || rep == 2 || rep == 4 || rep == 8);
+}
+
+// Few rows: cut the cached keys so that about four workgroups per CU stream them.  A range is worth its partial sums from
+// about 128 keys on.
+int attention_splits(int max_rows, int nkv, int cap) {
+    const int wgs = max_rows * nkv;
+    if (max_rows <= 0 || max_rows > kAttnSplitRows || wgs >= 2 * attn_cus()) return 1;
+    return std::max(1, std::min({kAttnSplitMax, (4 * attn_cus() + wgs - 1) / wgs, cap / 128}));
 }
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
@@ -680,21 +781,17 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
     d.row_seq = a.row_seq;
     d.items = reinterpret_cast<const int4*>(a.items);
     d.n_items = a.n_items;
-    d.k_cache = reinterpret_cast<const half_t*>(a.k_cache);
-    d.v_cache = reinterpret_cast<const half_t*>(a.v_cache);
+    d.k_cache = reinterpret_cast<half_t*>(a.k_cache);
+    d.v_cache = reinterpret_cast<half_t*>(a.v_cache);
     d.kv_old = a.kv_old;
     d.cap = a.cap;
     d.scale_log2 = kLog2e / sqrtf(static_cast<float>(a.d));
-    const int rep = a.nh / a.nkv;
-    const bool decode_style = a.k_cache != nullptr && a.T <= 4 * a.B && (rep == 1 || rep == 2 || rep == 4 || rep == 8);
-    if (decode_style) {
-        // Few rows: cut the keys so that about four workgroups per CU stream the cache (needs the partial buffer
-        // and pays one more launch, so only where the cache is long enough for the stream to matter).
-        d.n_split = 1;
+    if (a.cs) {                                                  // decode style (attention_is_decode)
+        d.cs = a.cs;
+        d.arrive = a.arrive;
         d.part = a.partials;
-        const int wgs = a.max_rows * a.nkv;
-        if (a.partials && a.max_rows <= kAttnSplitRows && a.cap >= 1024 && wgs < 2 * attn_cus())
-            d.n_split = std::min(kAttnSplitMax, (4 * attn_cus() + wgs - 1) / wgs);
+        d.n_split = a.partials && a.arrive ? attention_splits(a.max_rows, a.nkv, a.cap) : 1;
+        const int rep = a.nh / a.nkv;
         return a.d == 128 ? launch_decode_d<128>(d, rep, a.max_rows, a.nkv, stream)
                           : launch_decode_d<64>(d, rep, a.max_rows, a.nkv, stream);
     }

@@ -374,6 +374,7 @@ hipError_t launch_gemm_skinny(GemmDev& d, int epilogue, hipStream_t stream);
 // split_max > 1, the number of K parts (the epilogue must then be EPI_PARTIAL_F32: out = fp32 [parts][M_max][ldo]).
 int gemm_decode_plan(const GemmDev& d, int epilogue, int split_max, int* nwn_out);
 hipError_t launch_gemm_decode(GemmDev& d, int epilogue, int nwn, int split, hipStream_t stream);
+hipError_t launch_gemm_few(const GemmDev& d, int epilogue, const FewPrologue* pro, int cus, hipStream_t stream);   // at most kFewRows rows
 hipError_t launch_gemm_mid(GemmDev& d, int epilogue, hipStream_t stream);
 
 }  // namespace qtale

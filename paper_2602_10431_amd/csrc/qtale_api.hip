@@ -213,7 +213,28 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     s.idx = ws.idx; s.count = count; s.cu_exec = ws.cu_exec; s.row_seq = ws.row_seq;
     s.kv_len = kv ? kv->kv_len : nullptr; s.kv_old = ws.kv_old; s.kv_cap = kv ? kv->cap : 0;
     s.idx_copy = sel_idx; s.count_copy = sel_count;
-    if (!(link && link->scores_ready)) {
+    // Decode-style attention rotates and appends by itself: the first kernels leave it the rows' rotary table (in the
+    // buffer of the residual h, which is written after attention) and cleared arrival counters (in the buffer of act).
+    const bool decode_attn = attention_is_decode(kv != nullptr, T, B, nh, nkv) && H >= d;
+    RowAux aux{};
+    if (decode_attn) {
+        aux.cs = reinterpret_cast<float2*>(ws.h); aux.positions = positions; aux.half = d / 2; aux.base = c->rope_base;
+        if (2 * nkv <= I && attention_splits(M_max, nkv, kv->cap) > 1) {
+            aux.arrive = reinterpret_cast<int32_t*>(ws.act);
+            aux.n_arrive = M_max * nkv;
+        }
+    }
+    const int qkv_w = (nh + 2 * nkv) * d;
+    GemmArgs qg{};
+    qg.A = ws.nbuf; qg.count = count; qg.M_max = M_max; qg.rows_exact = ratio_mode; qg.K = H; qg.group = c->group; qg.bits = lbits; qg.n_w = 3;
+    qg.w[0] = {w->q.prepacked, w->q.N, w->q.K};
+    qg.w[1] = {w->k.prepacked, w->k.N, w->k.K};
+    qg.w[2] = {w->v.prepacked, w->v.N, w->v.K};
+    qg.epilogue = EPI_STORE_F16; qg.out = ws.qkv; qg.ldo = qkv_w;
+
+    const bool scored = link && link->scores_ready;
+    const bool few_fused = few_prologue_fits(T, M_max, H);
+    if (!scored && (!few_fused || w->router_hidden > 0)) {
         Prof pr(ctx, stream, 0);
         if (w->router_hidden > 0)
             HIP_TRY(launch_router_mlp(x, bf16, T, H, w->router_w1, w->router_b1, w->router_w2, w->router_b2,
@@ -222,11 +243,18 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
             HIP_TRY(launch_router_score(x, bf16, T, H, w->router_w, w->router_b, z, stream));
     }
     const bool small_call = fused_select_norm_fits(T, M_max);
-    if (small_call) {
+    FewPrologue pro{};
+    pro.eps = c->rms_eps; pro.bf16 = bf16;
+    if (small_call) s.inv = ws.inv;
+    if (few_fused) {
+        // a handful of tokens: router score, decision, compaction and RMSNorm 1 are part of the q|k|v launch
+        pro.x = x; pro.gain = w->norm1; pro.s = s; pro.aux = aux;
+        if (!scored && w->router_hidden == 0) { pro.router_w = w->router_w; pro.router_b = w->router_b; pro.z_out = z; }
+        qg.pro = &pro;
+    } else if (small_call) {
         // decode-sized call: decision, compaction and gather + RMSNorm 1 in one launch
-        s.inv = ws.inv;
         Prof pr(ctx, stream, 1);
-        HIP_TRY(launch_select_norm(x, bf16, H, z, w->norm1, c->rms_eps, ws.nbuf, s, M_max, stream));
+        HIP_TRY(launch_select_norm(x, bf16, H, z, w->norm1, c->rms_eps, ws.nbuf, s, aux, M_max, stream));
     } else {
         {
             Prof pr(ctx, stream, 1);
@@ -235,22 +263,15 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         if (M_max == 0) return QTALE_OK;
         {
             Prof pr(ctx, stream, 2);
-            HIP_TRY(launch_gather_rmsnorm(x, bf16, H, ws.idx, count, M_max, w->norm1, c->rms_eps, ws.nbuf, stream));
+            HIP_TRY(launch_gather_rmsnorm(x, bf16, H, ws.idx, count, M_max, w->norm1, c->rms_eps, ws.nbuf, aux, stream));
         }
     }
-    const int qkv_w = (nh + 2 * nkv) * d;
     int o_parts = 0;
     {
         Prof pr(ctx, stream, 3);
-        GemmArgs g{};
-        g.A = ws.nbuf; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.K = H; g.group = c->group; g.bits = lbits; g.n_w = 3;
-        g.w[0] = {w->q.prepacked, w->q.N, w->q.K};
-        g.w[1] = {w->k.prepacked, w->k.N, w->k.K};
-        g.w[2] = {w->v.prepacked, w->v.N, w->v.K};
-        g.epilogue = EPI_STORE_F16; g.out = ws.qkv; g.ldo = qkv_w;
-        HIP_TRY(launch_gemm_w4a16(g, stream));
+        HIP_TRY(launch_gemm_w4a16(qg, stream));
     }
-    {
+    if (!decode_attn) {
         Prof pr(ctx, stream, 4);
         RopeArgs r{};
         r.qkv = ws.qkv; r.nh = nh; r.nkv = nkv; r.d = d; r.base = c->rope_base;
@@ -266,6 +287,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         a.B = B; a.cu_exec = ws.cu_exec; a.row_seq = ws.row_seq;
         if (kv) { a.k_cache = kv->k_cache; a.v_cache = kv->v_cache; a.cap = kv->cap; }
         a.kv_old = ws.kv_old; a.T = T; a.items = ws.items; a.n_items = ws.scalars + 1; a.partials = ws.attn_part;
+        a.cs = aux.cs; a.arrive = aux.arrive;
         HIP_TRY(launch_attention(a, stream));
     }
     {
@@ -277,7 +299,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         g.part = M_max <= kGemmPartRows ? ws.gemm_part : nullptr; g.n_parts = &o_parts;
         HIP_TRY(launch_gemm_w4a16(g, stream));
     }
-    {
+    if (!few_fused) {
         Prof pr(ctx, stream, 7);
         if (o_parts > 0)       // the o-proj left K-part partial tiles: add them and the residual here
             HIP_TRY(launch_reduce_rmsnorm(ws.gemm_part, o_parts, x, bf16, ws.idx, H, count, M_max, w->norm2, c->rms_eps,
@@ -292,6 +314,10 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         g.w[0] = {w->gate.prepacked, w->gate.N, w->gate.K};
         g.w[1] = {w->up.prepacked, w->up.N, w->up.K};
         g.epilogue = EPI_SWIGLU_F16; g.out = ws.act; g.ldo = I;
+        if (few_fused) {                                         // RMSNorm 2 is part of the launch
+            pro.h = ws.h; pro.gain = w->norm2;
+            g.pro = &pro;
+        }
         HIP_TRY(launch_gemm_w4a16(g, stream));
     }
     {

@@ -17,6 +17,16 @@ hipError_t launch_quantize(const float* W, int N, int K, int bits, int group, ui
 hipError_t launch_prepack(const uint32_t* codes, const uint16_t* scales, const uint16_t* zeros, int N,
                           int K, int bits, int group, void* prepacked, hipStream_t stream);
 
+// What the kernel that normalises the executed rows also prepares for the decode attention kernel.
+struct RowAux {
+    float2* cs;                // nullable: [rows][half] (cos, sin) of every executed row's position
+    const int32_t* positions;  // [T]
+    int half;                  // head_dim / 2
+    float base;
+    int32_t* arrive;           // [n_arrive] counters to clear
+    int n_arrive;
+};
+
 // ---- router + selection --------------------------------------------------------------------
 hipError_t launch_router_score(const void* x, int bf16, int T, int H, const float* w, float b,
                                float* z, hipStream_t stream);
@@ -51,7 +61,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream);
 // fused_select_norm_fits(T, max_rows); max_rows > 0 is the host bound on executed rows.
 bool fused_select_norm_fits(int T, int max_rows);
 hipError_t launch_select_norm(const void* x, int bf16, int H, const float* z, const void* gain, float eps, void* out_f16,
-                              const SelectArgs& s, int max_rows, hipStream_t stream);
+                              const SelectArgs& s, const RowAux& aux, int max_rows, hipStream_t stream);
 
 // Decode-sized stacks: the last kernel of layer l (sum of the down-proj's K parts + residual + scatter, Eq. 1 and 3) also
 // scores every token for layer l + 1 (Eq. 2, linear router; the same fp64 summation order as launch_router_score, on the
@@ -69,7 +79,8 @@ hipError_t launch_threshold_bins(const float* scores, long n, const float* zthr_
 // ---- row operations ---------------------------------------------------------------------------
 // n1[i] = fp16(rmsnorm(x[idx[i]]) * gain) for i < *count
 hipError_t launch_gather_rmsnorm(const void* x, int bf16, int H, const int32_t* idx, const int32_t* count,
-                                 int max_rows, const void* gain, float eps, void* out_f16, hipStream_t stream);
+                                 int max_rows, const void* gain, float eps, void* out_f16, const RowAux& aux,
+                                 hipStream_t stream);
 // n2[i] = fp16(rmsnorm(h[i]) * gain), h fp32
 hipError_t launch_rmsnorm_f32(const float* h, int H, const int32_t* count, int max_rows, const void* gain,
                               int gain_bf16, float eps, void* out_f16, hipStream_t stream);
@@ -127,9 +138,30 @@ struct GemmArgs {
     // caller then runs the consumer that adds the parts (launch_reduce_rmsnorm / launch_reduce_scatter).
     float* part;               // nullable: room for kGemmPartMax x M_max x ldo floats
     int* n_parts;              // host out, required with `part`: 0 = epilogue applied as usual, else parts written
+    const struct FewPrologue* pro;   // nullable: A is made by the kernel itself (only where few_prologue_fits)
 };
 constexpr int kGemmPartRows = 64;
 constexpr int kGemmPartMax = 4;
+
+// A handful of rows: the GEMM can make its own activations (launch_gemm_w4a16 with `pro`).
+constexpr int kFewRows = 16;           // rows up to which gemm_few_kernel is used
+constexpr int kFewFuseT = 4;           // tokens of a call up to which it selects and normalises them itself
+constexpr int kFewPasses = 2;          // 8-column pieces of a row per thread of a 512-thread workgroup
+struct FewPrologue {
+    // h != null: A = RMSNorm(h rows) * gain (launch_rmsnorm_f32).  Else: router score, decision, gather and RMSNorm of x
+    // (launch_router_score + launch_select_norm), with everything those write.
+    const float* h;
+    const void* x;
+    const float* router_w;     // null: the scores are in s.z already
+    float router_b;
+    float* z_out;              // scores go here when router_w is given
+    const void* gain;
+    float eps;
+    int bf16;                  // dtype of x and gain
+    SelectArgs s;
+    RowAux aux;
+};
+bool few_prologue_fits(int T, int max_rows, int hidden);
 hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream);
 
 // ---- attention over executed tokens ---------------------------------------------------------------
@@ -142,18 +174,25 @@ struct AttnArgs {
     int B;
     const int32_t* cu_exec;    // [B+1]
     const int32_t* row_seq;    // [rows]
-    // cache (nullable): when given, keys/values are read from the cache only (new rows were appended)
-    const void* k_cache; const void* v_cache; int cap;
+    // cache (nullable): when given, keys/values are read from the cache only (launch_rope_append has appended the new
+    // rows; decode-style calls append them here)
+    void* k_cache; void* v_cache; int cap;
     const int32_t* kv_old;     // [B]
     int T;                     // tokens in the call
     void* items;               // scratch: (max_rows / kAttnBQ + B + 1) x int4 work list of the prefill kernel, 16-byte aligned
     int32_t* n_items;          // scratch [1]
+    // decode-style calls (attention_is_decode): q and k of the new rows arrive unrotated, the kernel rotates them with this
+    // table (RowAux) and appends the new keys and values to the cache
+    const float2* cs;
+    int32_t* arrive;           // nullable: max_rows x nkv zeroed counters (RowAux); without them keys are not split
     float* partials;           // scratch (nullable): min(max_rows, kAttnSplitRows) x nh x kAttnSplitMax x (d + 2) fp32,
                                // lets the decode kernel cut long caches into key ranges when there are few rows
 };
 constexpr int kAttnBQ = 128;   // executed rows per prefill-attention workgroup
 constexpr int kAttnSplitRows = 128;   // decode attention splits the keys only up to this many rows
 constexpr int kAttnSplitMax = 8;      // and into at most this many ranges
+bool attention_is_decode(bool cache, int T, int B, int nh, int nkv);
+int attention_splits(int max_rows, int nkv, int cap);   // key ranges of a decode-style call
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream);
 
 }  // namespace qtale

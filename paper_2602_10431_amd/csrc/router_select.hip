@@ -9,6 +9,7 @@
 //   ratio mode:     execute the k largest z, equal scores to the lower token index.
 #include "qtale_dev.h"
 #include "qtale_kernels.h"
+#include "row_aux.h"
 
 namespace qtale {
 
@@ -19,25 +20,8 @@ router_score_kernel(const uint16_t* __restrict__ x, int T, int H, const float* _
     const int lane = threadIdx.x & 63;
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= T) return;
-    const U4* xr = reinterpret_cast<const U4*>(x + static_cast<size_t>(t) * H);
-    const float4* wr = reinterpret_cast<const float4*>(w);
-    double acc0 = 0.0, acc1 = 0.0;
-    const int chunks = H >> 3;
-    for (int c = lane; c < chunks; c += 64) {
-        const U4 xv = xr[c];
-        const float4 w0 = wr[2 * c], w1 = wr[2 * c + 1];
-        const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w};
-        const float ws[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const double a0 = static_cast<double>(act_to_float<BF16>(static_cast<uint16_t>(xs[i] & 0xffffu)));
-            const double a1 = static_cast<double>(act_to_float<BF16>(static_cast<uint16_t>(xs[i] >> 16)));
-            acc0 = fma(a0, static_cast<double>(ws[2 * i]), acc0);
-            acc1 = fma(a1, static_cast<double>(ws[2 * i + 1]), acc1);
-        }
-    }
-    double acc = wave_sum(acc0 + acc1);
-    if (lane == 0) z[t] = static_cast<float>(acc + static_cast<double>(b));
+    const float score = router_row_score<BF16>(x + static_cast<size_t>(t) * H, H, w, b, lane);
+    if (lane == 0) z[t] = score;
 }
 
 hipError_t launch_router_score(const void* x, int bf16, int T, int H, const float* w, float b, float* z,
@@ -349,16 +333,6 @@ hipError_t launch_router_mlp(const void* x, int bf16, int T, int H, const float*
     return hipGetLastError();
 }
 
-// fp32 -> uint32 key whose unsigned order is the float order (-0 is first folded onto +0).  A NaN score gets the
-// smallest key: it ranks below every number, also below -inf, so it never meets a threshold (as in
-// threshold_bins_kernel) and is taken by the ratio rule only after every other token.
-__device__ __forceinline__ uint32_t order_key(float f) {
-    f += 0.0f;
-    const uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return 0u;
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 template <int kSelThreads>
 __device__ __forceinline__ uint32_t block_scan_inclusive(uint32_t v, uint32_t* wsum, uint32_t& total) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -580,7 +554,7 @@ constexpr int kFusedMaxT = 256;
 
 struct FusedArgs {
     const uint16_t* x; int H; const float* z; const uint16_t* gain; float eps; uint16_t* out;
-    SelectArgs s;
+    SelectArgs s; RowAux aux; int rows;
 };
 
 template <bool BF16>
@@ -594,6 +568,7 @@ select_norm_kernel(FusedArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int T = a.s.T, H = a.H;
     const int chunks = H >> 3;
+    const int row_id = blockIdx.x % a.rows, role = blockIdx.x / a.rows;   // 0: normalise compact row row_id, 1: its rotary table
     // 1. order keys of the scores the router kernel left in z (0 = below every real key for the padding)
     skey[tid] = tid < T ? order_key(a.z[tid]) : 0u;
     __syncthreads();
@@ -625,7 +600,7 @@ select_norm_kernel(FusedArgs a) {
     const int count = __popcll(smask[0]) + __popcll(smask[1]) + __popcll(smask[2]) + __popcll(smask[3]);
     if (tid < T) spre[tid] = static_cast<uint32_t>(before);
     if (tid == 0) spre[T] = static_cast<uint32_t>(count);
-    if (exec && before == static_cast<int>(blockIdx.x)) srow = tid; // the row this workgroup normalises
+    if (exec && before == row_id) srow = tid;                      // the row this workgroup works on
     __syncthreads();
     if (blockIdx.x == 0) {
         if (tid == 0) {
@@ -660,8 +635,14 @@ select_norm_kernel(FusedArgs a) {
             }
         }
     }
-    // 3. this workgroup's compact row
-    const int i = blockIdx.x;
+    if (blockIdx.x == 0) aux_clear(a.aux, tid, 256);
+    // 3. this workgroup's compact row.  The rotary table of the rows is written by workgroups of its own (two fp64
+    // functions: 2 us that the normalising workgroups would spend after their loads).
+    if (role == 1) {
+        if (row_id < count) aux_rope_row(a.aux, row_id, srow, tid);
+        return;
+    }
+    const int i = row_id;
     if (i >= count) return;
     const int t = srow;
     const u32x4_t* xr = reinterpret_cast<const u32x4_t*>(a.x + static_cast<size_t>(t) * H);
@@ -715,13 +696,14 @@ select_norm_kernel(FusedArgs a) {
 bool fused_select_norm_fits(int T, int max_rows) { return max_rows > 0 && T <= kFusedMaxT; }
 
 hipError_t launch_select_norm(const void* x, int bf16, int H, const float* z, const void* gain, float eps, void* out_f16,
-                              const SelectArgs& s, int max_rows, hipStream_t stream) {
+                              const SelectArgs& s, const RowAux& aux, int max_rows, hipStream_t stream) {
     FusedArgs a{};
     a.x = reinterpret_cast<const uint16_t*>(x); a.H = H; a.z = z;
     a.gain = reinterpret_cast<const uint16_t*>(gain); a.eps = eps;
-    a.out = reinterpret_cast<uint16_t*>(out_f16); a.s = s;
-    if (bf16) hipLaunchKernelGGL(select_norm_kernel<true>, dim3(max_rows), dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL(select_norm_kernel<false>, dim3(max_rows), dim3(256), 0, stream, a);
+    a.out = reinterpret_cast<uint16_t*>(out_f16); a.s = s; a.aux = aux; a.rows = max_rows;
+    const dim3 grid(aux.cs ? 2 * max_rows : max_rows);
+    if (bf16) hipLaunchKernelGGL(select_norm_kernel<true>, grid, dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL(select_norm_kernel<false>, grid, dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 // All are bandwidth-bound: 16-byte loads, one workgroup per row, fp32 reductions.
 #include "qtale_dev.h"
 #include "qtale_kernels.h"
+#include "row_aux.h"
 
 namespace qtale {
 
@@ -21,11 +22,13 @@ template <bool BF16>
 __global__ void __launch_bounds__(256)
 gather_rmsnorm_kernel(const uint16_t* __restrict__ x, int H, const int32_t* __restrict__ idx,
                       const int32_t* __restrict__ count, const uint16_t* __restrict__ gain, float eps,
-                      uint16_t* __restrict__ out) {
+                      uint16_t* __restrict__ out, RowAux aux) {
     __shared__ float red[4];
     const int i = blockIdx.x;
+    if (i == 0) aux_clear(aux, threadIdx.x, 256);
     if (i >= *count) return;
     const int t = idx[i];
+    aux_rope_row(aux, i, t, threadIdx.x);
     const u32x4_t* xr = reinterpret_cast<const u32x4_t*>(x + static_cast<size_t>(t) * H);
     const u32x4_t* gr = reinterpret_cast<const u32x4_t*>(gain);
     u32x4_t* orow = reinterpret_cast<u32x4_t*>(out + static_cast<size_t>(i) * H);
@@ -74,15 +77,16 @@ gather_rmsnorm_kernel(const uint16_t* __restrict__ x, int H, const int32_t* __re
 }
 
 hipError_t launch_gather_rmsnorm(const void* x, int bf16, int H, const int32_t* idx, const int32_t* count,
-                                 int max_rows, const void* gain, float eps, void* out_f16, hipStream_t stream) {
+                                 int max_rows, const void* gain, float eps, void* out_f16, const RowAux& aux,
+                                 hipStream_t stream) {
     if (max_rows == 0) return hipSuccess;
     const dim3 grid(max_rows), block(256);
     if (bf16)
         hipLaunchKernelGGL(gather_rmsnorm_kernel<true>, grid, block, 0, stream, reinterpret_cast<const uint16_t*>(x),
-                           H, idx, count, reinterpret_cast<const uint16_t*>(gain), eps, reinterpret_cast<uint16_t*>(out_f16));
+                           H, idx, count, reinterpret_cast<const uint16_t*>(gain), eps, reinterpret_cast<uint16_t*>(out_f16), aux);
     else
         hipLaunchKernelGGL(gather_rmsnorm_kernel<false>, grid, block, 0, stream, reinterpret_cast<const uint16_t*>(x),
-                           H, idx, count, reinterpret_cast<const uint16_t*>(gain), eps, reinterpret_cast<uint16_t*>(out_f16));
+                           H, idx, count, reinterpret_cast<const uint16_t*>(gain), eps, reinterpret_cast<uint16_t*>(out_f16), aux);
     return hipGetLastError();
 }
 

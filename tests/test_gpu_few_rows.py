@@ -1,0 +1,136 @@
+"""GPU parity of the few-row paths (run with -m gpu): the 16-column-fragment GEMM (at most 16 rows), the calls of at most
+four tokens whose q|k|v and gate/up launches also select and normalise, and the decode attention kernel that rotates,
+appends and combines its key ranges by itself.  References and tolerances are those of the other GPU tests."""
+import numpy as np
+import pytest
+import torch
+
+import synth_inputs as si
+from oracle import qtale_oracle as orc
+from tests.helpers import cfg_dict, check_parity, oracle_layer, to_f64
+from tests.test_gpu_layer import _cache_case, _run_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def qt():
+    import paper_2602_10431_amd as pkg
+    pkg.load_library()
+    return pkg
+
+
+# Output widths in each of the workgroup shapes (16-column fragments: up to 256, 512, 768, more) with a last fragment of 8
+# columns; K of one k-tile, an odd number of k-tiles, and not a multiple of 64; rows at the edges of the staged 4 / 8 / 16
+# and just past the kernel's range.
+@pytest.mark.parametrize("M", [1, 4, 5, 8, 9, 16, 17])
+@pytest.mark.parametrize("N,K,G,bits", [(8, 64, 64, 4), (40, 1096, 128, 4), (4104, 72, 32, 3), (8200, 192, 64, 2), (12296, 136, 128, 4),
+                                        (4088, 320, 32, 4)])
+def test_few_row_linear(qt, M, N, K, G, bits):
+    g = torch.Generator().manual_seed(M + N + K)
+    W = torch.randn(N, K, generator=g) * 0.05
+    A = torch.randn(M, K, generator=g).to(torch.float16)
+    out = qt.qtale_linear_w4a16(qt.qtale_quantize(W.cuda(), bits, G), A.cuda())
+    torch.cuda.synchronize()
+    want = to_f64(A) @ orc.dequantize(*orc.quantize_rtn(W.numpy(), bits, G), G).T
+    check_parity(orc.parity_error(to_f64(out), want), "fp16", ("few-row linear", M, N, K))
+
+
+@pytest.mark.parametrize("M", [1, 8, 16])
+@pytest.mark.parametrize("I,K,G,bits", [(24, 136, 64, 4), (4104, 64, 32, 2), (8200, 72, 64, 3), (12296, 64, 64, 4)])
+def test_few_row_swiglu(qt, M, I, K, G, bits):
+    g = torch.Generator().manual_seed(M + I + K)
+    Wg, Wu = torch.randn(I, K, generator=g) * 0.05, torch.randn(I, K, generator=g) * 0.05
+    A = torch.randn(M, K, generator=g).to(torch.float16)
+    out = qt.qtale_swiglu_w4a16(qt.qtale_quantize(Wg.cuda(), bits, G), qt.qtale_quantize(Wu.cuda(), bits, G), A.cuda())
+    torch.cuda.synchronize()
+    d = [orc.dequantize(*orc.quantize_rtn(W.numpy(), bits, G), G).T for W in (Wg, Wu)]
+    want = orc.silu(to_f64(A) @ d[0]) * (to_f64(A) @ d[1])
+    check_parity(orc.parity_error(to_f64(out), want), "fp16", ("few-row swiglu", M, I, K))
+
+
+@pytest.mark.parametrize("T,lens,old,cap", [(1, [1], [0], 64), (1, [0, 1, 0], [9, 700, 3], 704), (3, [1, 1, 1], [300, 1, 77], 304),
+                                            (4, [4], [130], 256), (4, [2, 0, 2], [63, 5, 64], 128), (5, [1] * 5, [9, 8, 7, 6, 5], 64)])
+@pytest.mark.parametrize("H,ratio", [(256, 1.0), (256, 0.5), (4104, 1.0)])
+def test_decode_call_of_a_few_tokens(qt, T, lens, old, cap, H, ratio):
+    # up to four tokens select and normalise inside the GEMM launches, five do not; hidden 4104 takes two pieces per thread
+    # and is not a multiple of the 64-wide k-tile; empty and fresh caches, several new rows per sequence, empty sequences
+    if int(ratio * T + 0.5) == 0:
+        pytest.skip("no token executes")
+    shape = si.LayerShape(H, 4, 2, 64, 344, 4, 32, "bf16") if H == 256 else si.LayerShape(H, 2, 1, 128, 136, 3, 64, "fp16")
+    _cache_case(qt, shape, lens, old, old, cap, 400 + T + H, ratio)
+
+
+@pytest.mark.parametrize("router", ["linear", "mlp"])
+@pytest.mark.parametrize("mode,val", [("ratio", 0.5), ("threshold", 0.5), ("threshold", 0.0), ("threshold", 1.0)])
+def test_selection_inside_the_first_gemm(qt, router, mode, val):
+    # four tokens without a cache, two of them tied: decision, scores and bypassed rows against the oracle
+    shape = si.LayerShape(512, 4, 4, 64, 344, 4, 64, "bf16")
+    tensors = si.layer_tensors(shape, 0, 5, unit_gains=False, std=0.057)
+    if router == "mlp":
+        tensors["router_mlp"] = si.router_mlp(shape, 0, 5, std1=0.057)
+    x = si.hidden_states(shape, 4, 5)[[0, 1, 0, 3]].contiguous()
+    offs, pos = si.ragged_sequences([3, 1], [0, 9])
+    got, idx, _ = _run_layer(qt, shape, tensors, x, offs, pos, mode, val)
+    p, _ = oracle_layer(shape, 0, 5, tensors=tensors)
+    if router == "mlp":
+        p.router_mlp = tuple(t.numpy() for t in tensors["router_mlp"])
+    want, widx, _ = orc.layer_forward(to_f64(x), p, cfg_dict(shape), offs.numpy(), pos.numpy(), mode, val)
+    assert np.array_equal(idx, widx)
+    skipped = np.setdiff1d(np.arange(4), widx)
+    assert torch.equal(got[skipped], x[skipped])
+    if len(widx):
+        check_parity(orc.parity_error(to_f64(got)[widx], want[widx]), shape.act_dtype, ("few tokens", router, mode, val), hidden=shape.hidden)
+
+
+@pytest.mark.parametrize("rep", [1, 2, 4, 8])
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_attention_rotates_and_appends(qt, rep, d):
+    # many rows (keys not split) and few rows (split, combined by the last range); more new rows per sequence than one step
+    # of the kernel covers
+    shape = si.LayerShape(256, 2 * rep, 2, d, 128, 4, 32, "fp16")
+    old = [int(v) for v in np.random.default_rng(rep + d).integers(0, 300, size=140)]
+    _cache_case(qt, shape, [1] * 140, old, old, 301, 500 + rep, 1.0)
+    _cache_case(qt, shape, [40, 0, 1, 3] + [0] * 8, [70, 5, 640, 0] + [1] * 8, [70, 5, 640, 0] + [1] * 8, 641, 510 + rep, 1.0)
+
+
+def test_decode_rows_that_do_not_fit_the_cache(qt):
+    # five new rows, room for two: the others are dropped, see what the cache holds, and the counter stops at the capacity
+    shape = si.LayerShape(256, 4, 2, 64, 344, 4, 32, "fp16")
+    tensors = si.layer_tensors(shape, 0, 8, unit_gains=False, std=0.08)
+    x = si.hidden_states(shape, 5, 8)
+    offs, pos = torch.tensor([0, 5, 5], dtype=torch.int32), torch.arange(30, 35, dtype=torch.int32)
+    kc, vc = si.kv_cache(shape, 2, 32, 0, 8)
+
+    def run(n):
+        kv = qt.KVCache.from_token_major(kc.cuda(), vc.cuda(), torch.tensor([30, 4], dtype=torch.int32).cuda(), 2)
+        o = torch.tensor([0, n, n], dtype=torch.int32)
+        got, _, _ = _run_layer(qt, shape, tensors, x[:n], o, pos[:n], "ratio", 1.0, kv=kv)
+        return got, kv
+
+    full, kv = run(5)
+    fits, kv2 = run(2)
+    assert kv.kv_len.tolist() == [32, 4] and kv2.kv_len.tolist() == [32, 4]
+    assert torch.equal(kv.k, kv2.k) and torch.equal(kv.v, kv2.v)
+    check_parity(orc.parity_error(to_f64(full[:2]), to_f64(fits)), "fp16", "rows that fit", hidden=256)
+    assert torch.isfinite(full).all()
+
+
+def test_few_row_stack_is_the_same_on_every_run(qt):
+    # the last range to arrive combines the key ranges: whichever that is, the bits are the same
+    shape = si.LayerShape(256, 8, 2, 64, 344, 4, 32, "bf16")
+    layers = [qt.quantize_layer(si.layer_tensors(shape, l, 9, unit_gains=False, std=0.08), 4, 32) for l in range(3)]
+    old = [900, 333, 1200]
+    caches = [si.kv_cache(shape, 3, 1216, l, 9) for l in range(3)]
+    offs, pos = torch.arange(4, dtype=torch.int32).cuda(), torch.tensor(old, dtype=torch.int32).cuda()
+    ctx = qt.Context()
+    qt.qtale_set_exec_ratio(ctx, 1.0)
+    outs = []
+    for _ in range(4):
+        kvs = [qt.KVCache.from_token_major(k.cuda(), v.cuda(), torch.tensor(old, dtype=torch.int32).cuda(), 2) for k, v in caches]
+        x = si.hidden_states(shape, 3, 9).cuda()
+        qt.qtale_stack_forward(ctx, qt.Stack(qt.cfg_from_shape(shape), layers, kvs), x, offs, pos)
+        torch.cuda.synchronize()
+        outs.append((x.cpu(), [kv.k.cpu() for kv in kvs]))
+    for x, ks in outs[1:]:
+        assert torch.equal(x, outs[0][0]) and all(torch.equal(a, b) for a, b in zip(ks, outs[0][1]))
