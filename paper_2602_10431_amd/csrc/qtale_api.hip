@@ -469,8 +469,7 @@ int qtale_quantize(const float* W, int N, int K, int bits, int group, uint32_t* 
     if (!W || !codes || !scales || !zeros) return QTALE_ERR_INVALID_ARG;
     if (prepacked && reinterpret_cast<uintptr_t>(prepacked) % 16 != 0) return QTALE_ERR_INVALID_ARG;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    HIP_TRY(launch_quantize(W, N, K, bits, group, codes, scales, zeros, s));
-    if (prepacked) HIP_TRY(launch_prepack(codes, scales, zeros, N, K, bits, group, prepacked, s));
+    HIP_TRY(launch_quantize(W, N, K, bits, group, codes, scales, zeros, prepacked, s));
     return QTALE_OK;
 }
 

@@ -13,7 +13,7 @@ struct PrepackDims {
 PrepackDims prepack_dims(int N, int K, int group, int bits);
 
 hipError_t launch_quantize(const float* W, int N, int K, int bits, int group, uint32_t* codes,
-                           uint16_t* scales, uint16_t* zeros, hipStream_t stream);
+                           uint16_t* scales, uint16_t* zeros, void* prepacked /*nullable*/, hipStream_t stream);
 hipError_t launch_prepack(const uint32_t* codes, const uint16_t* scales, const uint16_t* zeros, int N,
                           int K, int bits, int group, void* prepacked, hipStream_t stream);
 
