@@ -21,6 +21,7 @@ struct GemmDev {
     const int32_t* idx;
     int bf16;
     int bits;                      // 4, 3 or 2: width of the weight codes
+    int chunk_rows;                // wide kernel: rows per chunk
     int ksplit;                    // decode kernel: parts K is cut into across workgroups (1 = none)
     int epi_rt;                    // decode kernel: epilogue chosen at run time (GemmEpilogue)
     int tail;                      // 0: all rows; 1: all but gemm_tail_rows(); 2: only those last rows (small-row kernels)
@@ -375,6 +376,9 @@ hipError_t launch_gemm_skinny(GemmDev& d, int epilogue, hipStream_t stream);
 int gemm_decode_plan(const GemmDev& d, int epilogue, int split_max, int* nwn_out);
 hipError_t launch_gemm_decode(GemmDev& d, int epilogue, int nwn, int split, hipStream_t stream);
 hipError_t launch_gemm_few(const GemmDev& d, int epilogue, const FewPrologue* pro, int cus, hipStream_t stream);   // at most kFewRows rows
+// 65 to 256 rows; EPI_STORE_F16, EPI_SWIGLU_F16 and (any ksplit, out = fp32 [ksplit][M_max][ldo]) EPI_PARTIAL_F32.
+int gemm_wide_blocks(const GemmDev& d);     // workgroups without a K split
+hipError_t launch_gemm_wide(GemmDev& d, int epilogue, int ksplit, hipStream_t stream);
 hipError_t launch_gemm_mid(GemmDev& d, int epilogue, hipStream_t stream);
 
 }  // namespace qtale

@@ -320,6 +320,41 @@ static hipError_t launch_small_rows(GemmDev& d, const GemmArgs& a, bool parts_ok
     return launch_gemm_skinny(d, a.epilogue, stream);
 }
 
+// 65 to kGemmWideRows rows.  Measured with 4-bit group-128 weights on 7B-, 8B-GQA- and 13B-shaped linears (us at 66 / 128 /
+// 150 / 256 rows; "wide" counts its workgroups per 128-row chunk, one workgroup per CU):
+//   gate/up, 172 to 224 wide workgroups per chunk: wide 28-38 / 36-48 / 55-70 / 72-90, mid 37-48 / 38-49 / 58-75 / 63-85, skinny
+//     36-55 / 40-60 / 55-81 / 73-105; 88 workgroups (hidden 2048): skinny 15 / 16, wide 17 / 22 / 18 / 22, mid 21 at any
+//   q|k|v 6144 to 15360 wide: decode 18-31 / 18-32 / 21-52 / 24-60, skinny 22-37 / 24-41 / 30-53 / 35-74, wide 27-32 / 34-43 /
+//     27-37 / 34-50 (best at two chunks once they fill the chip); 3072 and 4096 wide: skinny 8-12 / 8-14 / 13-22 / 15-24, decode
+//     10-17 / 10-18 / 11-18 / 11-19
+//   residual outputs with K cut over workgroups (fp32 parts, added by the next kernel): 13B down-proj at 77 rows 59.5 -> 31.5 + 5.3,
+//     o-proj 31.7 -> 18.1 (+ 3.6 in RMSNorm 2); with fewer than 40 column blocks x chunks the four parts do not fill the chip and skinny is level or better.
+static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t stream) {
+    const int cus = resident_workgroups(1);
+    const int chunks = d.M_max > kGemmWideRows / 2 ? 2 : 1;
+    const int blocks = ((d.vf_total + 3) / 4) * chunks;              // wide workgroups
+    if (a.epilogue == EPI_SWIGLU_F16) {
+        if (chunks == 1 && (blocks < cus / 2 || blocks > cus)) return blocks > cus ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_skinny(d, a.epilogue, stream);
+        if (d.M_max > 192) return launch_gemm_mid(d, a.epilogue, stream);
+        return launch_gemm_wide(d, a.epilogue, 1, stream);
+    }
+    if (a.epilogue == EPI_STORE_F16) {
+        if (blocks > cus) return launch_gemm_mid(d, a.epilogue, stream);
+        if (8 * blocks >= 5 * cus) return launch_gemm_wide(d, a.epilogue, 1, stream);
+        if (chunks == 1 && d.vf_total < 192) return launch_gemm_skinny(d, a.epilogue, stream);
+        int nwn;
+        gemm_decode_plan(d, a.epilogue, 1, &nwn);
+        return launch_gemm_decode(d, a.epilogue, nwn, 1, stream);
+    }
+    const int parts = std::min(kGemmPartMax, cus / std::max(blocks, 1));
+    if (a.part && a.n_parts && blocks >= 40 && parts >= 2 && d.KT >= 4 * parts) {
+        d.out = a.part;
+        *a.n_parts = parts;
+        return launch_gemm_wide(d, EPI_PARTIAL_F32, parts, stream);
+    }
+    return launch_gemm_skinny(d, a.epilogue, stream);
+}
+
 hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     if (a.M_max <= 0) return hipSuccess;
     GemmDev d{};
@@ -350,14 +385,12 @@ hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     d.idx = a.idx;
     d.bf16 = a.bf16;
     d.bits = a.bits;
-    // Few rows: the weight stream dominates and 128-row tiles cannot fill the chip (a 5120-column output is 20
-    // workgroups).  Up to 64 rows the skinny kernel streams the weights once; up to 256 rows it runs one 64-row
-    // chunk per workgroup (measured on 13B-shaped linears at 128 rows: 26-59 us against 64-178 us here; at 256
-    // rows the two are level).
+    // Few rows: the weight stream dominates and 128-row tiles cannot fill the chip.  Each range has a kernel of its own:
+    // gemm_few.h, launch_small_rows, launch_mid_rows.
     if (a.n_parts) *a.n_parts = 0;
     if (d.M_max <= kFewRows) return launch_gemm_few(d, a.epilogue, a.pro, resident_workgroups(1), stream);
     if (d.M_max <= kGemmPartRows) return launch_small_rows(d, a, true, stream);
-    if (d.M_max <= 256) return launch_gemm_skinny(d, a.epilogue, stream);
+    if (d.M_max <= kGemmWideRows) return launch_mid_rows(d, a, stream);
     // A few hundred rows: so few 128 x 256 tiles that a CU holds at most one workgroup, whose k-loop then runs
     // at one memory latency per k-tile.  The 64-row kernel with its deep prefetch rings takes over while its own
     // grid fits the chip in one round (measured crossovers on 7B- and 13B-shaped linears: 2.5 workgroups per CU

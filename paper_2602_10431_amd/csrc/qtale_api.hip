@@ -266,6 +266,11 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
             HIP_TRY(launch_gather_rmsnorm(x, bf16, H, ws.idx, count, M_max, w->norm1, c->rms_eps, ws.nbuf, aux, stream));
         }
     }
+    // fp32 K parts of the o- and down-proj: their own buffer, or (more rows) the one of the attention's key ranges, which is
+    // free again by then
+    const size_t attn_part_floats = static_cast<size_t>(std::min(T, kAttnSplitRows)) * nh * kAttnSplitMax * (d + 2);
+    float* part = M_max <= kGemmPartRows ? ws.gemm_part
+                  : M_max <= kGemmWideRows && static_cast<size_t>(kGemmPartMax) * M_max * H <= attn_part_floats ? ws.attn_part : nullptr;
     int o_parts = 0;
     {
         Prof pr(ctx, stream, 3);
@@ -296,13 +301,13 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         g.A = ws.attn; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.K = nh * d; g.group = c->group; g.bits = lbits; g.n_w = 1;
         g.w[0] = {w->o.prepacked, w->o.N, w->o.K};
         g.epilogue = EPI_RESID_F32; g.out = ws.h; g.ldo = H; g.resid = x; g.idx = ws.idx; g.bf16 = bf16;
-        g.part = M_max <= kGemmPartRows ? ws.gemm_part : nullptr; g.n_parts = &o_parts;
+        g.part = part; g.n_parts = &o_parts;
         HIP_TRY(launch_gemm_w4a16(g, stream));
     }
     if (!few_fused) {
         Prof pr(ctx, stream, 7);
         if (o_parts > 0)       // the o-proj left K-part partial tiles: add them and the residual here
-            HIP_TRY(launch_reduce_rmsnorm(ws.gemm_part, o_parts, x, bf16, ws.idx, H, count, M_max, w->norm2, c->rms_eps,
+            HIP_TRY(launch_reduce_rmsnorm(part, o_parts, x, bf16, ws.idx, H, count, M_max, w->norm2, c->rms_eps,
                                           ws.h, ws.nbuf, stream));
         else
             HIP_TRY(launch_rmsnorm_f32(ws.h, H, count, M_max, w->norm2, bf16, c->rms_eps, ws.nbuf, stream));
@@ -327,15 +332,15 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         g.w[0] = {w->down.prepacked, w->down.N, w->down.K};
         g.epilogue = EPI_RESID_SCATTER; g.out = x; g.ldo = H; g.resid = ws.h; g.idx = ws.idx; g.bf16 = bf16;
         int d_parts = 0;
-        g.part = M_max <= kGemmPartRows ? ws.gemm_part : nullptr; g.n_parts = &d_parts;
+        g.part = part; g.n_parts = &d_parts;
         HIP_TRY(launch_gemm_w4a16(g, stream));
         if (d_parts > 0) {
             if (link && link->next && link->next->router_hidden == 0 && small_call) {
-                HIP_TRY(launch_reduce_scatter_score(ws.gemm_part, d_parts, M_max, ws.h, H, ws.inv, T, x, bf16,
+                HIP_TRY(launch_reduce_scatter_score(part, d_parts, M_max, ws.h, H, ws.inv, T, x, bf16,
                                                     link->next->router_w, link->next->router_b, link->next_z, stream));
                 link->next_scored = true;
             } else {
-                HIP_TRY(launch_reduce_scatter(ws.gemm_part, d_parts, ws.h, H, ws.idx, count, M_max, x, bf16, stream));
+                HIP_TRY(launch_reduce_scatter(part, d_parts, ws.h, H, ws.idx, count, M_max, x, bf16, stream));
             }
         }
     }

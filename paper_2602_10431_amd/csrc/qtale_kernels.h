@@ -133,14 +133,15 @@ struct GemmArgs {
     const void* resid;         // RESID_F32: x (act dtype, rows via idx); RESID_SCATTER: h fp32 [M][ldo]
     const int32_t* idx;        // compact row -> token row (RESID_F32 reads, RESID_SCATTER writes)
     int bf16;                  // act dtype of x
-    // Decode steps (M_max <= kGemmPartRows) with a RESID_* epilogue: when `part` is given the GEMM may cut K across
+    // Up to kGemmWideRows rows with a RESID_* epilogue: when `part` is given the GEMM may cut K across
     // workgroups and write fp32 partial tiles [*n_parts][M_max][ldo] there INSTEAD of applying its epilogue; the
     // caller then runs the consumer that adds the parts (launch_reduce_rmsnorm / launch_reduce_scatter).
     float* part;               // nullable: room for kGemmPartMax x M_max x ldo floats
     int* n_parts;              // host out, required with `part`: 0 = epilogue applied as usual, else parts written
     const struct FewPrologue* pro;   // nullable: A is made by the kernel itself (only where few_prologue_fits)
 };
-constexpr int kGemmPartRows = 64;
+constexpr int kGemmPartRows = 64;      // rows of the small-row kernels, and of the workspace's own part buffer
+constexpr int kGemmWideRows = 256;
 constexpr int kGemmPartMax = 4;
 
 // A handful of rows: the GEMM can make its own activations (launch_gemm_w4a16 with `pro`).

@@ -1,0 +1,72 @@
+"""GPU parity of the linears at 65 to 256 rows (run with -m gpu): the 128-row x 128-column K-sliced kernel in its three
+epilogues, and the shapes next to it that stay on the other kernels.  References and tolerances as in the other GPU tests."""
+import pytest
+import torch
+
+import synth_inputs as si
+from oracle import qtale_oracle as orc
+from tests.helpers import check_parity, to_f64
+from tests.test_gpu_layer import _check_layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def qt():
+    import paper_2602_10431_amd as pkg
+    pkg.load_library()
+    return pkg
+
+
+# One and two row chunks with 2, 3 and 4 live 32-row fragments, rows at their edges; a width that fills the chip with one
+# chunk, one that does with two, one too wide, one too narrow, last column blocks of one fragment of 8 columns; K of less than
+# a round of four k-tiles, of every remainder of the three-slot ring, and not a multiple of 64.
+@pytest.mark.parametrize("M", [65, 96, 97, 128, 129, 150, 192, 193, 256])
+@pytest.mark.parametrize("N,K,G,bits", [(20488, 136, 128, 4), (10248, 64, 32, 3), (10248, 1096, 64, 2), (33000, 72, 64, 4), (6152, 1480, 128, 4),
+                                        (3080, 776, 32, 4)])
+def test_linear_of_a_hundred_rows(qt, M, N, K, G, bits):
+    g = torch.Generator().manual_seed(M + N + K)
+    W = torch.randn(N, K, generator=g) * 0.05
+    A = torch.randn(M, K, generator=g).to(torch.float16)
+    out = qt.qtale_linear_w4a16(qt.qtale_quantize(W.cuda(), bits, G), A.cuda())
+    torch.cuda.synchronize()
+    want = to_f64(A) @ orc.dequantize(*orc.quantize_rtn(W.numpy(), bits, G), G).T
+    check_parity(orc.parity_error(to_f64(out), want), "fp16", ("linear", M, N, K))
+
+
+@pytest.mark.parametrize("M", [66, 97, 128, 150, 192, 200])
+@pytest.mark.parametrize("I,K,G,bits", [(8200, 520, 128, 4), (16392, 72, 64, 2), (4104, 328, 32, 3)])
+def test_swiglu_of_a_hundred_rows(qt, M, I, K, G, bits):
+    g = torch.Generator().manual_seed(M + I + K)
+    Wg, Wu = torch.randn(I, K, generator=g) * 0.05, torch.randn(I, K, generator=g) * 0.05
+    A = torch.randn(M, K, generator=g).to(torch.float16)
+    out = qt.qtale_swiglu_w4a16(qt.qtale_quantize(Wg.cuda(), bits, G), qt.qtale_quantize(Wu.cuda(), bits, G), A.cuda())
+    torch.cuda.synchronize()
+    d = [orc.dequantize(*orc.quantize_rtn(W.numpy(), bits, G), G).T for W in (Wg, Wu)]
+    want = orc.silu(to_f64(A) @ d[0]) * (to_f64(A) @ d[1])
+    check_parity(orc.parity_error(to_f64(out), want), "fp16", ("swiglu", M, I, K))
+
+
+# hidden 2568: 21 column blocks, two row chunks, the o- and down-proj leave K parts (27 k-tiles with a ragged last one)
+SHAPE = si.LayerShape(2568, 24, 24, 64, 1672, 4, 64, "bf16")
+
+
+@pytest.mark.parametrize("T,mode,val", [(150, "ratio", 1.0), (230, "threshold", 0.5), (300, "ratio", 0.5)])
+def test_layer_with_k_parts_in_two_row_chunks(qt, T, mode, val):
+    _check_layer(qt, SHAPE, T, [T // 2, 0, T - T // 2], mode, val, seed=T)
+
+
+def test_stack_with_k_parts_equals_layer_by_layer_calls(qt):
+    T, L = 140, 2
+    layers = [qt.quantize_layer(si.layer_tensors(SHAPE, l, 3, unit_gains=False), 4, 64) for l in range(L)]
+    cfg, ctx = qt.cfg_from_shape(SHAPE), qt.Context()
+    qt.qtale_set_exec_ratio(ctx, 0.96)
+    x0 = si.hidden_states(SHAPE, T, 3).cuda()
+    offs, pos = (t.cuda() for t in si.ragged_sequences([100, 40]))
+    xs, xl = x0.clone(), x0.clone()
+    zs, zl = torch.zeros(L, T, device="cuda"), torch.zeros(L, T, device="cuda")
+    qt.qtale_stack_forward(ctx, qt.Stack(cfg, layers), xs, offs, pos, scores=zs)
+    for l in range(L):
+        qt.qtale_layer_forward(ctx, cfg, layers[l], xl, offs, pos, scores=zl[l])
+    torch.cuda.synchronize()
+    assert torch.equal(xs, xl) and torch.equal(zs, zl)
