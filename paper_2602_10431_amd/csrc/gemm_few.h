@@ -223,7 +223,7 @@ gemm_few_kernel(FewDev a) {
             __syncthreads();
             mask = wave_decide(s, s_score, lane);
             if (static_cast<int>(blockIdx.x) == p.tiles_n) {      // the extra workgroup: everything else the call leaves behind
-                if (wave == 0) wave_write_selection(s, mask, s_score, score_here ? a.pro.z_out : nullptr, lane);
+                if (wave == 0) wave_write_selection(s, a.pro.aux, mask, s_score, score_here ? a.pro.z_out : nullptr, lane);
                 aux_clear(a.pro.aux, tid, NT);
                 for (int t = wave; t < s.T; t += NW)
                     if ((mask >> t) & 1ull) aux_rope_row(a.pro.aux, __popcll(mask & ((1ull << t) - 1ull)), t, lane);

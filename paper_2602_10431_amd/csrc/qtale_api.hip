@@ -36,7 +36,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct Workspace {
     float* z;
     int32_t* idx;
-    int32_t* scalars;      // [0] count, [1] n_items
+    int32_t* scalars;      // [0] count, [1] n_items, [2] keys per range of decode attention
     int32_t* cu_exec;
     int32_t* row_seq;
     int32_t* kv_old;
@@ -219,9 +219,15 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     RowAux aux{};
     if (decode_attn) {
         aux.cs = reinterpret_cast<float2*>(ws.h); aux.positions = positions; aux.half = d / 2; aux.base = c->rope_base;
-        if (2 * nkv <= I && attention_splits(M_max, nkv, kv->cap) > 1) {
+        const bool device_chunk = fused_select_norm_fits(T, M_max);   // the calls whose first kernel sees all cache lengths
+        const int ranges = attention_splits(M_max, nh, nkv, kv->cap, device_chunk, &aux.target);
+        if (2 * nkv <= I && ranges > 1) {
             aux.arrive = reinterpret_cast<int32_t*>(ws.act);
             aux.n_arrive = M_max * nkv;
+            if (device_chunk) {
+                aux.chunk = ws.scalars + 2;
+                aux.nkv = nkv; aux.gran = d == 128 ? 64 : 128; aux.max_ranges = ranges;
+            }
         }
     }
     const int qkv_w = (nh + 2 * nkv) * d;
@@ -292,7 +298,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         a.B = B; a.cu_exec = ws.cu_exec; a.row_seq = ws.row_seq;
         if (kv) { a.k_cache = kv->k_cache; a.v_cache = kv->v_cache; a.cap = kv->cap; }
         a.kv_old = ws.kv_old; a.T = T; a.items = ws.items; a.n_items = ws.scalars + 1; a.partials = ws.attn_part;
-        a.cs = aux.cs; a.arrive = aux.arrive;
+        a.cs = aux.cs; a.arrive = aux.arrive; a.chunk = aux.chunk;
         HIP_TRY(launch_attention(a, stream));
     }
     {

@@ -25,6 +25,10 @@ struct RowAux {
     float base;
     int32_t* arrive;           // [n_arrive] counters to clear
     int n_arrive;
+    // split keys: *chunk = cached keys per range such that the executed rows' ranges are equally long and about `target` of
+    // them cover the call (a multiple of `gran`, at most `max_ranges` ranges per row)
+    int32_t* chunk;            // nullable
+    int nkv, target, gran, max_ranges;
 };
 
 // ---- router + selection --------------------------------------------------------------------
@@ -185,6 +189,7 @@ struct AttnArgs {
     // decode-style calls (attention_is_decode): q and k of the new rows arrive unrotated, the kernel rotates them with this
     // table (RowAux) and appends the new keys and values to the cache
     const float2* cs;
+    const int32_t* chunk;      // nullable: keys per range (RowAux); else every row is cut into equally many ranges
     int32_t* arrive;           // nullable: max_rows x nkv zeroed counters (RowAux); without them keys are not split
     float* partials;           // scratch (nullable): min(max_rows, kAttnSplitRows) x nh x kAttnSplitMax x (d + 2) fp32,
                                // lets the decode kernel cut long caches into key ranges when there are few rows
@@ -193,7 +198,9 @@ constexpr int kAttnBQ = 128;   // executed rows per prefill-attention workgroup
 constexpr int kAttnSplitRows = 128;   // decode attention splits the keys only up to this many rows
 constexpr int kAttnSplitMax = 8;      // and into at most this many ranges
 bool attention_is_decode(bool cache, int T, int B, int nh, int nkv);
-int attention_splits(int max_rows, int nkv, int cap);   // key ranges of a decode-style call
+// Key ranges per (row, kv head) of a decode-style call (1 = not split).  device_chunk: the ranges' length is set on the device
+// (RowAux::chunk) and the result is the bound on their number; target (nullable): workgroups that run at once.
+int attention_splits(int max_rows, int nh, int nkv, int cap, bool device_chunk, int* target);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream);
 
 }  // namespace qtale

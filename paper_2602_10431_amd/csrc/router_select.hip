@@ -547,7 +547,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
 //   1. every workgroup reads the T scores the router kernel wrote (Eq. 2) and turns them into order keys in LDS;
 //   2. every workgroup takes the decision (Eq. 9 / the k largest, ties to the lower index) on those keys: rank by
 //      counting, exclusive prefix of the executed flags by counting;
-//   3. workgroup i normalises the row of the i-th executed token (App. B.2 gather + RMSNorm); workgroup 0 also writes the
+//   3. workgroup i + 1 normalises the row of the i-th executed token (App. B.2 gather + RMSNorm); workgroup 0 writes the
 //      call-wide results (ascending indices, count, per-sequence offsets, row -> sequence map, cache lengths).
 // The redundant decision costs T LDS reads per thread, which bounds T (kFusedMaxT).
 constexpr int kFusedMaxT = 256;
@@ -563,12 +563,14 @@ select_norm_kernel(FusedArgs a) {
     __shared__ __align__(16) uint32_t skey[kFusedMaxT];
     __shared__ uint32_t spre[kFusedMaxT + 1];
     __shared__ unsigned long long smask[4];
-    __shared__ int srow;
+    __shared__ int srow, s_pairs[4], s_longest[4];
     __shared__ float red[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int T = a.s.T, H = a.H;
     const int chunks = H >> 3;
-    const int row_id = blockIdx.x % a.rows, role = blockIdx.x / a.rows;   // 0: normalise compact row row_id, 1: its rotary table
+    // workgroup 0 writes the call-wide results (a chain of its own: offsets, cache lengths, counts), the next `rows` normalise
+    // one compact row each, the last `rows` (with a decode attention to follow) write one row of the rotary table each
+    const int row_id = (static_cast<int>(blockIdx.x) - 1) % a.rows, role = blockIdx.x == 0 ? 2 : (static_cast<int>(blockIdx.x) - 1) / a.rows;
     // 1. order keys of the scores the router kernel left in z (0 = below every real key for the padding)
     skey[tid] = tid < T ? order_key(a.z[tid]) : 0u;
     __syncthreads();
@@ -626,16 +628,33 @@ select_norm_kernel(FusedArgs a) {
             if (a.s.cu_exec) a.s.cu_exec[b] = o >= T ? count : static_cast<int>(spre[o]);
         }
         if (a.s.kv_len) {
+            int pairs = 0, longest = 0;
             for (int b = tid; b < a.s.B; b += 256) {
                 const int o0 = a.s.seq_offsets[b], o1 = a.s.seq_offsets[b + 1];
                 const int n = (o1 >= T ? count : static_cast<int>(spre[o1])) - (o0 >= T ? count : static_cast<int>(spre[o0]));
                 const int old = a.s.kv_len[b];
                 a.s.kv_old[b] = old;
                 a.s.kv_len[b] = a.s.kv_cap > 0 ? min(old + n, max(old, a.s.kv_cap)) : old + n;
+                aux_count_keys(n, old, a.s.kv_cap, pairs, longest);
+            }
+            if (a.aux.chunk) {                                     // uniform over the workgroup
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) {
+                    pairs += __shfl_xor(pairs, o, 64);
+                    longest = max(longest, __shfl_xor(longest, o, 64));
+                }
+                if (lane == 0) { s_pairs[wave] = pairs; s_longest[wave] = longest; }
+                __syncthreads();
+                if (tid == 0)
+                    aux_write_chunk(a.aux, s_pairs[0] + s_pairs[1] + s_pairs[2] + s_pairs[3],
+                                    max(max(s_longest[0], s_longest[1]), max(s_longest[2], s_longest[3])), count);
             }
         }
     }
-    if (blockIdx.x == 0) aux_clear(a.aux, tid, 256);
+    if (role == 2) {
+        aux_clear(a.aux, tid, 256);
+        return;
+    }
     // 3. this workgroup's compact row.  The rotary table of the rows is written by workgroups of its own (two fp64
     // functions: 2 us that the normalising workgroups would spend after their loads).
     if (role == 1) {
@@ -701,7 +720,7 @@ hipError_t launch_select_norm(const void* x, int bf16, int H, const float* z, co
     a.x = reinterpret_cast<const uint16_t*>(x); a.H = H; a.z = z;
     a.gain = reinterpret_cast<const uint16_t*>(gain); a.eps = eps;
     a.out = reinterpret_cast<uint16_t*>(out_f16); a.s = s; a.aux = aux; a.rows = max_rows;
-    const dim3 grid(aux.cs ? 2 * max_rows : max_rows);
+    const dim3 grid(1 + (aux.cs ? 2 * max_rows : max_rows));
     if (bf16) hipLaunchKernelGGL(select_norm_kernel<true>, grid, dim3(256), 0, stream, a);
     else hipLaunchKernelGGL(select_norm_kernel<false>, grid, dim3(256), 0, stream, a);
     return hipGetLastError();

@@ -57,8 +57,25 @@ __device__ __forceinline__ unsigned long long wave_decide(const SelectArgs& s, c
     return __ballot(exec && lane < s.T);
 }
 
+// RowAux::chunk from the number of (executed row, cached key) pairs of the call and the longest cached prefix.
+__device__ __forceinline__ void aux_write_chunk(const RowAux& a, int pairs, int longest, int rows) {
+    const int want = a.target - rows * a.nkv / 2;              // half a range per row is lost to rounding
+    // (fp32: a range more or less does not matter, a 64-bit division would be the longest chain of the kernel)
+    float c = want > 0 ? static_cast<float>(pairs) * static_cast<float>(a.nkv) / static_cast<float>(want) : static_cast<float>(longest);
+    const int least = (longest + a.max_ranges - 1) / a.max_ranges;
+    const int keys = max(max(static_cast<int>(c), least), 1);
+    *a.chunk = (keys + a.gran - 1) & ~(a.gran - 1);            // gran is a power of two
+}
+// (row, key) pairs and longest prefix of one sequence, added to a running pair
+__device__ __forceinline__ void aux_count_keys(int rows, int old, int cap, int& pairs, int& longest) {
+    const int keys = cap > 0 ? min(old, cap) : old;
+    pairs += rows * keys;
+    if (rows > 0) longest = max(longest, keys);
+}
+
 // Call-wide results of such a decision, by one wave of one workgroup.
-__device__ __forceinline__ void wave_write_selection(const SelectArgs& s, unsigned long long mask, const float* score, float* z_out, int lane) {
+__device__ __forceinline__ void wave_write_selection(const SelectArgs& s, const RowAux& aux, unsigned long long mask, const float* score,
+                                                     float* z_out, int lane) {
     const int count = __popcll(mask);
     auto before = [&](int t) { return t >= s.T ? count : __popcll(mask & ((1ull << t) - 1ull)); };   // executed tokens below t
     if (lane == 0) {
@@ -86,11 +103,21 @@ __device__ __forceinline__ void wave_write_selection(const SelectArgs& s, unsign
     for (int b = lane; b <= s.B; b += 64)
         if (s.cu_exec) s.cu_exec[b] = before(s.seq_offsets[b]);
     if (s.kv_len) {
+        int pairs = 0, longest = 0;
         for (int b = lane; b < s.B; b += 64) {
             const int n = before(s.seq_offsets[b + 1]) - before(s.seq_offsets[b]);
             const int old = s.kv_len[b];
             s.kv_old[b] = old;
             s.kv_len[b] = s.kv_cap > 0 ? min(old + n, max(old, s.kv_cap)) : old + n;
+            aux_count_keys(n, old, s.kv_cap, pairs, longest);
+        }
+        if (aux.chunk) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                pairs += __shfl_xor(pairs, o, 64);
+                longest = max(longest, __shfl_xor(longest, o, 64));
+            }
+            if (lane == 0) aux_write_chunk(aux, pairs, longest, count);
         }
     }
 }
