@@ -7,6 +7,8 @@
 // Decision (logit domain; sigmoid is strictly increasing so p_0 >= theta <=> z >= logit(theta)):
 //   threshold mode: execute iff z >= z_thr;
 //   ratio mode:     execute the k largest z, equal scores to the lower token index.
+#include <type_traits>
+
 #include "qtale_dev.h"
 #include "qtale_kernels.h"
 #include "row_aux.h"
@@ -145,10 +147,9 @@ hipError_t launch_reduce_scatter_score(const float* part, int n_parts, int part_
 // from L2).
 constexpr int kMlpRC = 4;         // hidden units per pass
 constexpr int kMlpKC = 512;       // columns per staged chunk
-constexpr int kMlpTW = 4;         // tokens per wave
 constexpr int kMlpWL = (kMlpRC * kMlpKC / 4) / 256;   // float4 loads per thread per chunk
 
-template <bool BF16>
+template <bool BF16, int kMlpTW>
 __global__ void __launch_bounds__(256, 2)
 router_mlp_kernel(const uint16_t* __restrict__ x, int T, int H, const float* __restrict__ W1,
                   const float* __restrict__ b1, const float* __restrict__ W2, const float* __restrict__ b2, int R,
@@ -325,11 +326,21 @@ hipError_t launch_router_mlp(const void* x, int bf16, int T, int H, const float*
             hipLaunchKernelGGL(router_mlp_small_kernel<false>, dim3(T), dim3(256), 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
         return hipGetLastError();
     }
-    const dim3 grid((T + 4 * kMlpTW - 1) / (4 * kMlpTW)), block(256);
-    if (bf16)
-        hipLaunchKernelGGL(router_mlp_kernel<true>, grid, block, 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
-    else
-        hipLaunchKernelGGL(router_mlp_kernel<false>, grid, block, 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
+    // kMlpTW tokens per wave: four reuse every converted weight four times, but 16 tokens per workgroup need 16 tokens per CU; with
+    // fewer tokens the workgroups get smaller until they number about two per CU (1400 tokens x 2048 columns x 16 units: 28 us
+    // at four tokens per wave, 19 at one; 1000 x 4096 40 -> 27).  A token's sums are the same bits either way.
+    auto go = [&](auto bf, auto tw) {
+        constexpr int TW = decltype(tw)::value;
+        hipLaunchKernelGGL((router_mlp_kernel<decltype(bf)::value, TW>), dim3((T + 4 * TW - 1) / (4 * TW)), dim3(256), 0, stream, xp, T, H, W1, b1,
+                           W2, b2, R, z);
+    };
+    auto by_tokens = [&](auto bf) {
+        if (T > 4096) go(bf, std::integral_constant<int, 4>{});
+        else if (T > 2048) go(bf, std::integral_constant<int, 2>{});
+        else go(bf, std::integral_constant<int, 1>{});
+    };
+    if (bf16) by_tokens(std::true_type{});
+    else by_tokens(std::false_type{});
     return hipGetLastError();
 }
 
