@@ -48,8 +48,9 @@ gemm_few_kernel(FewDev a) {
     static_assert(!SWIGLU || NF == 2, "a gate and an up fragment");
     constexpr int NW = NP * NK;
     constexpr int NT = NW * 64;
-    // steps in flight per wave (registers): weights alone where A is in LDS, else weights and activations of a step together
-    constexpr int kSteps = PRO != PRO_NONE ? (NF == 2 ? 4 : 6) : (NF == 2 ? 2 : 3);
+    // steps in flight per wave; deeper rings were slower (one token, 7B shape: 53.8 us per layer at 3 / 2 steps, 55.8 at 6 / 4,
+    // 57.7 at 8 / 6): the loads that the prologue waits for queue behind more weights, and the registers cost waves
+    constexpr int kSteps = NF == 2 ? 2 : 3;
     constexpr int AL = MR / 4;                                    // 16-byte pieces of a step's activations per lane
     constexpr int ASTR = 136;                                     // halves per staged row (128 + 8: conflict-free 16-byte reads)
     const GemmDev& p = a.g;
