@@ -13,7 +13,9 @@
 //     accumulator layout, are fed straight back as the B operand of O^T = V^T P^T; V is transposed on
 //     its way into LDS.
 //   * decode: one workgroup per (executed row, kv head); lanes stream K and V rows with 16-byte loads,
-//     16 (or 8) lanes per key, online softmax per lane group, merged at the end.  Bandwidth-bound.
+//     16 (or 8) lanes per key, online softmax per lane group, merged at the end.  Bandwidth-bound.  It also
+//     rotates the query and the call's own keys (table of the normalising kernel) and appends the new row; with
+//     few rows the cached keys are cut into ranges and the workgroup that arrives last combines them.
 #include <algorithm>
 #include <type_traits>
 

@@ -1,8 +1,8 @@
-// Skinny W4A16 / W3A16 GEMM for decode steps: at most 64 executed rows, so the linears stream their weights once
-// and the question is bandwidth and latency, not matrix-core throughput (Sec. 4.1 weights; the executed
+// Skinny W4A16 / W3A16 GEMM: q|k|v at 33 to 64 executed rows, and 65 to 256 rows in 64-row chunks where the rule for
+// those sizes picks it.  The linears stream their weights once per chunk and the question is bandwidth and latency, not matrix-core throughput (Sec. 4.1 weights; the executed
 // rows come from the gather of App. B.2).
 //
-// Shape of the work: C[M<=64][N] = A[M][K] x W'[N][K]^T.  The weights (N*K/2 bytes) dominate; A is at most
+// Shape of the work, per chunk: C[M<=64][N] = A[M][K] x W'[N][K]^T.  The weights (N*K/2 bytes) dominate; A is at most
 // 64 x K fp16 and stays in L2.  A k-loop with a barrier per 64-wide tile would be latency-bound
 // (K/64 round trips), so here nothing synchronises inside the k-loop:
 //   * a workgroup owns NFB consecutive 32-column fragments and ALL of K; its NW waves split K by

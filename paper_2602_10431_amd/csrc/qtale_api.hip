@@ -3,6 +3,8 @@
 //   router score -> select/compact -> gather+RMSNorm -> q|k|v GEMM -> rotary (+cache append) ->
 //   attention over executed tokens -> o GEMM (+residual) -> RMSNorm -> gate/up GEMM (SiLU*up) ->
 //   down GEMM (+residual, scatter back).
+// Small calls have fewer launches: selection joins the first normalisation up to 256 tokens, rotary and append join a
+// decode-style attention, and with at most four tokens selection and both normalisations join the GEMM that follows.
 // In ratio mode the executed count k is known on the host, so every launch shape is static and the
 // stack runs without any device->host synchronisation; in threshold mode grids are sized for all T
 // tokens and the kernels read the device-side count.
@@ -46,7 +48,7 @@ struct Workspace {
     void* attn;            // [T][nh d] fp16
     float* h;              // [T][H] fp32
     void* act;             // [T][I] fp16
-    float* attn_part;      // [min(T, kAttnSplitRows)][nh][kAttnSplitMax][d + 2] fp32: key-range partials of decode attention
+    float* attn_part;      // [min(T, kAttnSplitRows)][nh][kAttnSplitMax][d + 2] fp32: key-range partials of decode attention; K parts of 65 to 256 rows
     float* gemm_part;      // [kGemmPartMax][min(T, kGemmPartRows)][H] fp32: K-part partial tiles of the decode o-/down-proj
     int32_t* inv;          // [min(T, 256)] token -> compact row of small calls (-1 = bypassed)
     size_t total;

@@ -554,7 +554,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
 
 // ---- decode-sized calls: decision, compaction and the first normalisation in ONE launch -------------------------
 // With a few dozen tokens (a decode step: one token per sequence) selection and gather + RMSNorm as two launches are
-// pure launch and latency cost.  Here workgroup i produces compact row i on its own:
+// pure launch and latency cost.  Here workgroup i + 1 produces compact row i on its own:
 //   1. every workgroup reads the T scores the router kernel wrote (Eq. 2) and turns them into order keys in LDS;
 //   2. every workgroup takes the decision (Eq. 9 / the k largest, ties to the lower index) on those keys: rank by
 //      counting, exclusive prefix of the executed flags by counting;
