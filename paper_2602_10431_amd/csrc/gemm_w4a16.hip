@@ -320,6 +320,26 @@ static hipError_t launch_small_rows(GemmDev& d, const GemmArgs& a, bool parts_ok
     return launch_gemm_skinny(d, a.epilogue, stream);
 }
 
+// Residual outputs of 65 to kGemmPartsMaxRows rows with K cut over workgroups: the number of parts, as many as one round of the
+// chip takes and the caller's buffer holds (1 = don't).  Above 256 rows the 64-row kernel is the other choice, a single
+// round of workgroups that each walk all of K.  Whole layer, us, without / with
+// parts: 7B shape 264 rows 250 / 225, 300 rows 252 / 233, 400 rows 315 / 306, 512 rows 324 / 320; 13B 264 rows 359 / 329;
+// 8B-GQA 300 rows 289 / 262; hidden 2048 at 264 / 512 / 700 / 900 / 1024 rows 124 / 106, 145 / 138, 178 / 175, 194 / 196, 199 / 207.
+constexpr int kGemmPartsMaxRows = 768;
+static int wide_parts(const GemmDev& d, const GemmArgs& a) {
+    if (!a.part || !a.n_parts) return 1;
+    const int blocks = ((d.vf_total + 3) / 4) * ((d.M_max + 127) / 128);
+    const size_t room = a.part_floats / (static_cast<size_t>(d.M_max) * a.ldo);
+    const int parts = std::min(static_cast<int>(std::min<size_t>(kGemmPartMax, room)), resident_workgroups(1) / std::max(blocks, 1));
+    return blocks >= 40 && parts >= 2 && d.KT >= 4 * parts ? parts : 1;
+}
+
+static hipError_t launch_wide_parts(GemmDev& d, const GemmArgs& a, hipStream_t stream) {
+    d.out = a.part;
+    *a.n_parts = wide_parts(d, a);
+    return launch_gemm_wide(d, EPI_PARTIAL_F32, *a.n_parts, stream);
+}
+
 // 65 to kGemmWideRows rows.  Measured with 4-bit group-128 weights on 7B-, 8B-GQA- and 13B-shaped linears (us at 66 / 128 /
 // 150 / 256 rows; "wide" counts its workgroups per 128-row chunk, one workgroup per CU):
 //   gate/up, 172 to 224 wide workgroups per chunk: wide 28-38 / 36-48 / 55-70 / 72-90, mid 37-48 / 38-49 / 58-75 / 63-85, skinny
@@ -346,12 +366,7 @@ static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t str
         gemm_decode_plan(d, a.epilogue, 1, &nwn);
         return launch_gemm_decode(d, a.epilogue, nwn, 1, stream);
     }
-    const int parts = std::min(kGemmPartMax, cus / std::max(blocks, 1));
-    if (a.part && a.n_parts && blocks >= 40 && parts >= 2 && d.KT >= 4 * parts) {
-        d.out = a.part;
-        *a.n_parts = parts;
-        return launch_gemm_wide(d, EPI_PARTIAL_F32, parts, stream);
-    }
+    if (wide_parts(d, a) > 1) return launch_wide_parts(d, a, stream);
     return launch_gemm_skinny(d, a.epilogue, stream);
 }
 
@@ -391,6 +406,7 @@ hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     if (d.M_max <= kFewRows) return launch_gemm_few(d, a.epilogue, a.pro, resident_workgroups(1), stream);
     if (d.M_max <= kGemmPartRows) return launch_small_rows(d, a, true, stream);
     if (d.M_max <= kGemmWideRows) return launch_mid_rows(d, a, stream);
+    if (d.M_max <= kGemmPartsMaxRows && wide_parts(d, a) > 1) return launch_wide_parts(d, a, stream);
     // A few hundred rows: so few 128 x 256 tiles that a CU holds at most one workgroup, whose k-loop then runs
     // at one memory latency per k-tile.  The 64-row kernel with its deep prefetch rings takes over while its own
     // grid fits the chip in one round (measured crossovers on 7B- and 13B-shaped linears: 2.5 workgroups per CU

@@ -48,7 +48,7 @@ struct Workspace {
     void* attn;            // [T][nh d] fp16
     float* h;              // [T][H] fp32
     void* act;             // [T][I] fp16
-    float* attn_part;      // [min(T, kAttnSplitRows)][nh][kAttnSplitMax][d + 2] fp32: key-range partials of decode attention; K parts of 65 to 256 rows
+    float* attn_part;      // [min(T, kAttnSplitRows)][nh][kAttnSplitMax][d + 2] fp32: key-range partials of decode attention; K parts above 64 rows
     float* gemm_part;      // [kGemmPartMax][min(T, kGemmPartRows)][H] fp32: K-part partial tiles of the decode o-/down-proj
     int32_t* inv;          // [min(T, 256)] token -> compact row of small calls (-1 = bypassed)
     size_t total;
@@ -274,11 +274,18 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
             HIP_TRY(launch_gather_rmsnorm(x, bf16, H, ws.idx, count, M_max, w->norm1, c->rms_eps, ws.nbuf, aux, stream));
         }
     }
-    // fp32 K parts of the o- and down-proj: their own buffer, or (more rows) the one of the attention's key ranges, which is
-    // free again by then
-    const size_t attn_part_floats = static_cast<size_t>(std::min(T, kAttnSplitRows)) * nh * kAttnSplitMax * (d + 2);
-    float* part = M_max <= kGemmPartRows ? ws.gemm_part
-                  : M_max <= kGemmWideRows && static_cast<size_t>(kGemmPartMax) * M_max * H <= attn_part_floats ? ws.attn_part : nullptr;
+    // fp32 K parts of the o- and down-proj: their own buffer, or (more rows) the largest that nobody else needs just then:
+    // that of the attention's key ranges, for the o-proj that of act, for the down-proj those of q|k|v and of attn, which adjoin
+    float *o_part = ws.gemm_part, *d_part = ws.gemm_part;
+    size_t o_floats = static_cast<size_t>(kGemmPartMax) * M_max * H, d_floats = o_floats;
+    if (M_max > kGemmPartRows) {
+        const size_t ranges = static_cast<size_t>(std::min(T, kAttnSplitRows)) * nh * kAttnSplitMax * (d + 2);
+        const size_t act = static_cast<size_t>(T) * I / 2, qkv_attn = static_cast<size_t>(T) * (qkv_w + nh * d) / 2;
+        o_part = act > ranges ? reinterpret_cast<float*>(ws.act) : ws.attn_part;
+        o_floats = std::max(act, ranges);
+        d_part = qkv_attn > ranges ? reinterpret_cast<float*>(ws.qkv) : ws.attn_part;
+        d_floats = std::max(qkv_attn, ranges);
+    }
     int o_parts = 0;
     {
         Prof pr(ctx, stream, 3);
@@ -309,13 +316,13 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         g.A = ws.attn; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.K = nh * d; g.group = c->group; g.bits = lbits; g.n_w = 1;
         g.w[0] = {w->o.prepacked, w->o.N, w->o.K};
         g.epilogue = EPI_RESID_F32; g.out = ws.h; g.ldo = H; g.resid = x; g.idx = ws.idx; g.bf16 = bf16;
-        g.part = part; g.n_parts = &o_parts;
+        g.part = o_part; g.part_floats = o_floats; g.n_parts = &o_parts;
         HIP_TRY(launch_gemm_w4a16(g, stream));
     }
     if (!few_fused) {
         Prof pr(ctx, stream, 7);
         if (o_parts > 0)       // the o-proj left K-part partial tiles: add them and the residual here
-            HIP_TRY(launch_reduce_rmsnorm(part, o_parts, x, bf16, ws.idx, H, count, M_max, w->norm2, c->rms_eps,
+            HIP_TRY(launch_reduce_rmsnorm(o_part, o_parts, x, bf16, ws.idx, H, count, M_max, w->norm2, c->rms_eps,
                                           ws.h, ws.nbuf, stream));
         else
             HIP_TRY(launch_rmsnorm_f32(ws.h, H, count, M_max, w->norm2, bf16, c->rms_eps, ws.nbuf, stream));
@@ -340,15 +347,15 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         g.w[0] = {w->down.prepacked, w->down.N, w->down.K};
         g.epilogue = EPI_RESID_SCATTER; g.out = x; g.ldo = H; g.resid = ws.h; g.idx = ws.idx; g.bf16 = bf16;
         int d_parts = 0;
-        g.part = part; g.n_parts = &d_parts;
+        g.part = d_part; g.part_floats = d_floats; g.n_parts = &d_parts;
         HIP_TRY(launch_gemm_w4a16(g, stream));
         if (d_parts > 0) {
             if (link && link->next && link->next->router_hidden == 0 && small_call) {
-                HIP_TRY(launch_reduce_scatter_score(part, d_parts, M_max, ws.h, H, ws.inv, T, x, bf16,
+                HIP_TRY(launch_reduce_scatter_score(d_part, d_parts, M_max, ws.h, H, ws.inv, T, x, bf16,
                                                     link->next->router_w, link->next->router_b, link->next_z, stream));
                 link->next_scored = true;
             } else {
-                HIP_TRY(launch_reduce_scatter(part, d_parts, ws.h, H, ws.idx, count, M_max, x, bf16, stream));
+                HIP_TRY(launch_reduce_scatter(d_part, d_parts, ws.h, H, ws.idx, count, M_max, x, bf16, stream));
             }
         }
     }

@@ -137,10 +137,11 @@ struct GemmArgs {
     const void* resid;         // RESID_F32: x (act dtype, rows via idx); RESID_SCATTER: h fp32 [M][ldo]
     const int32_t* idx;        // compact row -> token row (RESID_F32 reads, RESID_SCATTER writes)
     int bf16;                  // act dtype of x
-    // Up to kGemmWideRows rows with a RESID_* epilogue: when `part` is given the GEMM may cut K across
+    // Up to a few hundred rows with a RESID_* epilogue: when `part` is given the GEMM may cut K across
     // workgroups and write fp32 partial tiles [*n_parts][M_max][ldo] there INSTEAD of applying its epilogue; the
     // caller then runs the consumer that adds the parts (launch_reduce_rmsnorm / launch_reduce_scatter).
-    float* part;               // nullable: room for kGemmPartMax x M_max x ldo floats
+    float* part;               // nullable
+    size_t part_floats;        // its size: at most part_floats / (M_max x ldo) parts are written
     int* n_parts;              // host out, required with `part`: 0 = epilogue applied as usual, else parts written
     const struct FewPrologue* pro;   // nullable: A is made by the kernel itself (only where few_prologue_fits)
 };

@@ -70,3 +70,15 @@ def test_stack_with_k_parts_equals_layer_by_layer_calls(qt):
         qt.qtale_layer_forward(ctx, cfg, layers[l], xl, offs, pos, scores=zl[l])
     torch.cuda.synchronize()
     assert torch.equal(xs, xl) and torch.equal(zs, zl)
+
+
+# three to six row chunks; the parts' buffer of the first shape (1.6 M floats) holds two parts up to 315 rows and none beyond, the
+# narrow one takes four and three parts at 513 rows, two at 768 and the ordinary path at 769
+NARROW = si.LayerShape(1032, 32, 8, 64, 1096, 4, 128, "fp16")
+
+
+@pytest.mark.parametrize("shape,T,mode,val", [(SHAPE, 257, "ratio", 1.0), (SHAPE, 315, "ratio", 1.0), (SHAPE, 316, "ratio", 1.0),
+                                              (SHAPE, 310, "threshold", 0.5), (NARROW, 513, "ratio", 1.0),
+                                              (NARROW, 768, "threshold", 0.5), (NARROW, 769, "ratio", 1.0)])
+def test_layer_with_k_parts_in_more_row_chunks(qt, shape, T, mode, val):
+    _check_layer(qt, shape, T, [T // 3, 0, T - T // 3], mode, val, seed=T)
