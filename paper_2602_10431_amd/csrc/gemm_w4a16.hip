@@ -320,18 +320,30 @@ static hipError_t launch_small_rows(GemmDev& d, const GemmArgs& a, bool parts_ok
     return launch_gemm_skinny(d, a.epilogue, stream);
 }
 
-// Residual outputs of 65 to kGemmPartsMaxRows rows with K cut over workgroups: the number of parts, as many as one round of the
-// chip takes and the caller's buffer holds (1 = don't).  Above 256 rows the 64-row kernel is the other choice, a single
-// round of workgroups that each walk all of K.  Whole layer, us, without / with
-// parts: 7B shape 264 rows 250 / 225, 300 rows 252 / 233, 400 rows 315 / 306, 512 rows 324 / 320; 13B 264 rows 359 / 329;
-// 8B-GQA 300 rows 289 / 262; hidden 2048 at 264 / 512 / 700 / 900 / 1024 rows 124 / 106, 145 / 138, 178 / 175, 194 / 196, 199 / 207.
+// Above 256 rows: sizes at which the 64-row kernel needs more than one round of the chip (one workgroup per CU and round runs at
+// the latency of its k-tiles) and the 128-row kernel does not.  Linears, us, 64-row / 128-row kernel: 6144 x 4096 at 320 rows (one
+// round) 25.6 / 30.6, at 400 rows 36.6 / 33.1, at 640 rows 42.6 / 39.0; 8192 x 4096 at 257 / 512 rows 35.9 / 28.1, 43.6 / 40.0;
+// 4096 x 4096 at 500 rows (one round) 26.1 / 30.9, 640 and 900 rows 36.4 / 32.1, 42.4 / 39.3; 12288 x 4096 at 500 rows (two rounds
+// of either) 59.7 / 67.0.
+static bool wide_round(const GemmDev& d) {
+    const int cus = resident_workgroups(1), cols = (d.vf_total + 3) / 4;
+    return d.M_max > kGemmWideRows && cols * ((d.M_max + 63) / 64) > cus && cols * ((d.M_max + 127) / 128) <= cus;
+}
+
+// Residual outputs above 64 rows on the 128-row kernel: the number of K parts, as many as one round of the chip takes and the
+// caller's buffer holds (0 = another kernel).  Two or more up to kGemmPartsMaxRows, whole layer, us, without / with parts: 7B shape
+// 264 rows 250 / 225, 300 rows 252 / 233, 400 rows 315 / 306, 512 rows 324 / 320; 13B 264 rows 359 / 329; 8B-GQA 300 rows 289 /
+// 262; hidden 2048 at 264 / 512 / 700 / 900 / 1024 rows 124 / 106, 145 / 138, 178 / 175, 194 / 196, 199 / 207.  One part (the
+// consumer adds the residual) where the 128-row kernel saves a round; with the q|k|v rule: 7B 550 / 800 / 1000 rows 374 / 353,
+// 503 / 488, 534 / 524; 13B 450 / 640 rows 447 / 416, 592 / 573; 8B-GQA 700 rows 461 / 436; hidden 2048 at 1200 rows 223 / 217.
 constexpr int kGemmPartsMaxRows = 768;
 static int wide_parts(const GemmDev& d, const GemmArgs& a) {
-    if (!a.part || !a.n_parts) return 1;
+    if (!a.part || !a.n_parts) return 0;
     const int blocks = ((d.vf_total + 3) / 4) * ((d.M_max + 127) / 128);
     const size_t room = a.part_floats / (static_cast<size_t>(d.M_max) * a.ldo);
     const int parts = std::min(static_cast<int>(std::min<size_t>(kGemmPartMax, room)), resident_workgroups(1) / std::max(blocks, 1));
-    return blocks >= 40 && parts >= 2 && d.KT >= 4 * parts ? parts : 1;
+    if (d.M_max <= kGemmPartsMaxRows && blocks >= 40 && parts >= 2 && d.KT >= 4 * parts) return parts;
+    return room >= 1 && wide_round(d) ? 1 : 0;
 }
 
 static hipError_t launch_wide_parts(GemmDev& d, const GemmArgs& a, hipStream_t stream) {
@@ -366,7 +378,7 @@ static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t str
         gemm_decode_plan(d, a.epilogue, 1, &nwn);
         return launch_gemm_decode(d, a.epilogue, nwn, 1, stream);
     }
-    if (wide_parts(d, a) > 1) return launch_wide_parts(d, a, stream);
+    if (wide_parts(d, a) > 0) return launch_wide_parts(d, a, stream);
     return launch_gemm_skinny(d, a.epilogue, stream);
 }
 
@@ -406,7 +418,8 @@ hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     if (d.M_max <= kFewRows) return launch_gemm_few(d, a.epilogue, a.pro, resident_workgroups(1), stream);
     if (d.M_max <= kGemmPartRows) return launch_small_rows(d, a, true, stream);
     if (d.M_max <= kGemmWideRows) return launch_mid_rows(d, a, stream);
-    if (d.M_max <= kGemmPartsMaxRows && wide_parts(d, a) > 1) return launch_wide_parts(d, a, stream);
+    if (wide_parts(d, a) > 0) return launch_wide_parts(d, a, stream);
+    if (a.epilogue == EPI_STORE_F16 && wide_round(d)) return launch_gemm_wide(d, a.epilogue, 1, stream);
     // A few hundred rows: so few 128 x 256 tiles that a CU holds at most one workgroup, whose k-loop then runs
     // at one memory latency per k-tile.  The 64-row kernel with its deep prefetch rings takes over while its own
     // grid fits the chip in one round (measured crossovers on 7B- and 13B-shaped linears: 2.5 workgroups per CU

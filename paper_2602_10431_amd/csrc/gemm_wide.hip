@@ -1,5 +1,5 @@
-// W4A16 / W3A16 / W2A16 GEMM for 65 to 256 executed rows (large decode batches, short prompts), with K cut over workgroups to
-// a few hundred more: C[M][N] = A[M][K] x W'[N][K]^T
+// W4A16 / W3A16 / W2A16 GEMM for 65 to 256 executed rows (large decode batches, short prompts), and
+// for more rows where its workgroups fill the chip once: C[M][N] = A[M][K] x W'[N][K]^T
 // with the weights dequantized once per 128-row chunk (Sec. 4.1 weights; rows gathered per App. B.2).
 //
 // At these sizes a linear is a few dozen 128 x 256 tiles, so the prefill kernel leaves most CUs idle, while 64-row chunks of

@@ -137,7 +137,7 @@ struct GemmArgs {
     const void* resid;         // RESID_F32: x (act dtype, rows via idx); RESID_SCATTER: h fp32 [M][ldo]
     const int32_t* idx;        // compact row -> token row (RESID_F32 reads, RESID_SCATTER writes)
     int bf16;                  // act dtype of x
-    // Up to a few hundred rows with a RESID_* epilogue: when `part` is given the GEMM may cut K across
+    // Calls below the tiled kernel's range with a RESID_* epilogue: when `part` is given the GEMM may cut K across
     // workgroups and write fp32 partial tiles [*n_parts][M_max][ldo] there INSTEAD of applying its epilogue; the
     // caller then runs the consumer that adds the parts (launch_reduce_rmsnorm / launch_reduce_scatter).
     float* part;               // nullable
