@@ -537,17 +537,29 @@ attn_decode_kernel(AttnDev p) {
         key_lo = min(static_cast<int>(blockIdx.z) * per, n_cached);
         key_hi = min(key_lo + per, n_cached);
     }
-    // The keys and values of the next step are requested before the current step is consumed, so the memory
-    // pipe never drains while the lanes do their dot products and exponentials (keys past the end are clamped
-    // to the last one and masked).
+    // Keys past the end are clamped to the last one and masked.  kAhead: the keys and values of the next step are requested
+    // before the current step is consumed, so the memory pipe never drains while the lanes do their dot products and
+    // exponentials.  One query head per kv head without split keys runs eight workgroups per CU on 64 registers, which do not
+    // hold two steps (asked to, the compiler loaded one row after the other, a round trip each: 16 rows x 32 heads x 1000 keys
+    // 58 us, 4 x 4 rows 44): the step's loads are issued together at its start and the other workgroups fill the wait.
+    constexpr bool kAhead = SPLIT || REP > 1;
+    // Addresses are a uniform base that walks with the step plus a 32-bit lane offset inside it.
     half8_t kn[UNR], vn[UNR];
+    const int last = max(n_cached - 1, 0);                       // an empty cache: slot 0, loaded and not used
+    const int lane_key = wave * KPW + slot;
     auto fetch = [&](int kb) {
-        const int k0 = kb + wave * KPW + slot;
+        const int first = min(kb, last);
+        // (scalar registers; as ordinary pointers they are folded into a 64-bit sum per load and lane)
+        uint64_t ks = reinterpret_cast<uint64_t>(kbase + static_cast<size_t>(first) * D);
+        uint64_t vs = reinterpret_cast<uint64_t>(vbase + static_cast<size_t>(first) * D);
+        asm("" : "+s"(ks), "+s"(vs));
+        using Bytes = const __attribute__((address_space(1))) char*;
+        using Piece = const __attribute__((address_space(1))) half8_t*;
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
-            const int kc = max(min(k0 + u * step, n_cached - 1), 0);       // an empty cache: slot 0, loaded and not used
-            kn[u] = *reinterpret_cast<const half8_t*>(kbase + static_cast<size_t>(kc) * D + sub * 8);
-            vn[u] = *reinterpret_cast<const half8_t*>(vbase + static_cast<size_t>(kc) * D + sub * 8);
+            const uint32_t off = static_cast<uint32_t>(min(lane_key + u * step, last - first) * D + sub * 8) * 2u;
+            kn[u] = *reinterpret_cast<Piece>(reinterpret_cast<Bytes>(ks) + off);
+            vn[u] = *reinterpret_cast<Piece>(reinterpret_cast<Bytes>(vs) + off);
         }
     };
     // Few workgroups (SPLIT): latency counts and registers do not, the stream starts before anything else is computed.  Many
@@ -594,6 +606,7 @@ attn_decode_kernel(AttnDev p) {
             float2 cs[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) cs[e] = cs0[static_cast<size_t>(rj) * (D / 2) + e];
+            if (!SPLIT) __builtin_amdgcn_sched_barrier(0);      // one round trip per step
             half8_t kr;
             rotate(ja, jo, cs, kr);
 #pragma unroll
@@ -611,18 +624,22 @@ attn_decode_kernel(AttnDev p) {
         }
     }
 
-    if (!SPLIT) fetch(key_lo);
+    if (kAhead && !SPLIT) fetch(key_lo);
     for (int kb = key_lo; kb < key_hi; kb += UNR * step) {     // trip count is uniform over the workgroup
         const int k0 = kb + wave * KPW + slot;
         half8_t kv[UNR], vv[UNR];
         bool ok[UNR];
+        if (!kAhead) {
+            fetch(kb);
+            __builtin_amdgcn_sched_barrier(0);                  // all eight loads before the first wait
+        }
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             ok[u] = k0 + u * step < key_hi;
             kv[u] = kn[u];
             vv[u] = vn[u];
         }
-        fetch(kb + UNR * step);                                // past the end: one redundant, unused fetch
+        if (kAhead) fetch(kb + UNR * step);                    // past the end: one redundant, unused fetch
 #pragma unroll
         for (int r = 0; r < REP; ++r) {
             float s[UNR];
