@@ -476,7 +476,9 @@ __device__ __forceinline__ float agent_load(const float* p) { return __hip_atomi
 // n_split contiguous ranges (multiples of the 64- or 128-key step) that separate workgroups stream (range 0 also takes the
 // new keys); each writes its unnormalised sums with their maximum and denominator, and the one that arrives last
 // combines the ranges in range order, so the result does not depend on who that is.
-template <int D, int REP, bool SPLIT>
+// FUSED = false: rope_append_kernel has rotated and appended already, the queries are read as they are and all keys from the
+// cache (attention_rotates says when).
+template <int D, int REP, bool SPLIT, bool FUSED>
 __global__ void __launch_bounds__(256, SPLIT ? 1 : REP == 1 ? 8 : 1)
 attn_decode_kernel(AttnDev p) {
     constexpr int LPK = D / 8;            // lanes per key (each lane owns 8 of the D columns)
@@ -494,25 +496,27 @@ attn_decode_kernel(AttnDev p) {
     // first half subtracts.
     const int psub = sub < LPK / 2 ? sub + LPK / 2 : sub - LPK / 2;
     const float sign = sub < LPK / 2 ? -1.0f : 1.0f;
-    const float2* cs0 = p.cs + (sub % (LPK / 2)) * 8;
+    const float2* cs0 = FUSED ? p.cs + (sub % (LPK / 2)) * 8 : nullptr;
     auto rotate = [&](const half8_t& mine, const half8_t& other, const float2* cs, half8_t& out) {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
             out[e] = static_cast<half_t>(fmaf(static_cast<float>(mine[e]), cs[e].x, sign * (static_cast<float>(other[e]) * cs[e].y)));
     };
     const half_t* row_i = p.qkv + static_cast<size_t>(i) * p.width;
-    half8_t qa[REP], qb[REP];
+    half8_t qa[REP], qb[REP], ka{}, kb_{}, v_own{};
     float2 cs_i[8];
 #pragma unroll
     for (int r = 0; r < REP; ++r) {
         qa[r] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + r) * D + sub * 8);
-        qb[r] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + r) * D + psub * 8);
+        if (FUSED) qb[r] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + r) * D + psub * 8);
     }
-    const half8_t ka = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + sub * 8);
-    const half8_t kb_ = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + psub * 8);
-    const half8_t v_own = *reinterpret_cast<const half8_t*>(row_i + (p.nh + p.nkv + hk) * D + sub * 8);
+    if (FUSED) {
+        ka = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + sub * 8);
+        kb_ = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + psub * 8);
+        v_own = *reinterpret_cast<const half8_t*>(row_i + (p.nh + p.nkv + hk) * D + sub * 8);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) cs_i[e] = cs0[static_cast<size_t>(i) * (D / 2) + e];
+        for (int e = 0; e < 8; ++e) cs_i[e] = cs0[static_cast<size_t>(i) * (D / 2) + e];
+    }
 
     if (SPLIT) __builtin_amdgcn_sched_barrier(0);
 
@@ -523,7 +527,7 @@ attn_decode_kernel(AttnDev p) {
     const half_t* vbase = p.v_cache + head_off;
     const int old = p.kv_old[b];
     const int own = i - row_begin;                               // place of this row among the sequence's new rows
-    const int n_cached = min(old, p.cap);
+    const int n_cached = min(FUSED ? old : old + own + 1, p.cap);
     const int n_new = max(min(own + 1, p.cap - old), 0);         // new keys that fit the cache; later ones are not seen
 
     const int step = 4 * KPW;             // keys per workgroup step
@@ -569,16 +573,18 @@ attn_decode_kernel(AttnDev p) {
         __builtin_amdgcn_sched_barrier(0);
     }
 
-    half8_t qh[REP], k_own;
+    half8_t qh[REP], k_own{};
 #pragma unroll
-    for (int r = 0; r < REP; ++r) rotate(qa[r], qb[r], cs_i, qh[r]);
-    rotate(ka, kb_, cs_i, k_own);
-
+    for (int r = 0; r < REP; ++r) {
+        if (FUSED) rotate(qa[r], qb[r], cs_i, qh[r]);
+        else qh[r] = qa[r];
+    }
+    if (FUSED) rotate(ka, kb_, cs_i, k_own);
 
     float m_run[REP], l_run[REP], o[REP][8];
     // The row's own key starts the sums of one lane group of range 0 (and goes into the cache); the other groups start
     // empty.
-    const bool mine = (!SPLIT || blockIdx.z == 0) && wave == 0 && slot == 0 && own < n_new;
+    const bool mine = FUSED && (!SPLIT || blockIdx.z == 0) && wave == 0 && slot == 0 && own < n_new;
     if (mine) {
         const size_t at = head_off + static_cast<size_t>(old + own) * D + sub * 8;
         *reinterpret_cast<half8_t*>(p.k_cache + at) = k_own;
@@ -586,14 +592,14 @@ attn_decode_kernel(AttnDev p) {
     }
 #pragma unroll
     for (int r = 0; r < REP; ++r) {
-        const float acc = key_group_sum<LPK>(dot8(qh[r], k_own)) * p.scale_log2;
+        const float acc = FUSED ? key_group_sum<LPK>(dot8(qh[r], k_own)) * p.scale_log2 : 0.0f;
         m_run[r] = mine ? acc : kNegBig;
         l_run[r] = mine ? 1.0f : 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[r][e] = mine ? static_cast<float>(v_own[e]) : 0.0f;
     }
     // the sequence's other new keys (none in a decode step of one token per sequence)
-    if (own > 0 && (!SPLIT || blockIdx.z == 0)) {
+    if (FUSED && own > 0 && (!SPLIT || blockIdx.z == 0)) {
         const int n_other = min(own, n_new);
         for (int jb = 0; jb < n_other; jb += step) {             // uniform trip count
             const int j = jb + wave * KPW + slot;
@@ -763,14 +769,14 @@ static int attn_cus() {
     return cus[dev];
 }
 
-template <int D, bool SPLIT>
+template <int D, bool SPLIT, bool FUSED>
 static hipError_t launch_decode_rep(const AttnDev& d, int rep, int rows, int nkv, hipStream_t stream) {
     const dim3 grid(nkv, rows, SPLIT ? d.n_split : 1), block(256);
     switch (rep) {
-        case 1: hipLaunchKernelGGL((attn_decode_kernel<D, 1, SPLIT>), grid, block, 0, stream, d); break;
-        case 2: hipLaunchKernelGGL((attn_decode_kernel<D, 2, SPLIT>), grid, block, 0, stream, d); break;
-        case 4: hipLaunchKernelGGL((attn_decode_kernel<D, 4, SPLIT>), grid, block, 0, stream, d); break;
-        case 8: hipLaunchKernelGGL((attn_decode_kernel<D, 8, SPLIT>), grid, block, 0, stream, d); break;
+        case 1: hipLaunchKernelGGL((attn_decode_kernel<D, 1, SPLIT, FUSED>), grid, block, 0, stream, d); break;
+        case 2: hipLaunchKernelGGL((attn_decode_kernel<D, 2, SPLIT, FUSED>), grid, block, 0, stream, d); break;
+        case 4: hipLaunchKernelGGL((attn_decode_kernel<D, 4, SPLIT, FUSED>), grid, block, 0, stream, d); break;
+        case 8: hipLaunchKernelGGL((attn_decode_kernel<D, 8, SPLIT, FUSED>), grid, block, 0, stream, d); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -778,14 +784,18 @@ static hipError_t launch_decode_rep(const AttnDev& d, int rep, int rows, int nkv
 
 template <int D>
 static hipError_t launch_decode_d(const AttnDev& d, int rep, int rows, int nkv, hipStream_t stream) {
-    if (d.n_split <= 1) return launch_decode_rep<D, false>(d, rep, rows, nkv, stream);
-    return launch_decode_rep<D, true>(d, rep, rows, nkv, stream);
+    if (!d.cs) return d.n_split <= 1 ? launch_decode_rep<D, false, false>(d, rep, rows, nkv, stream)
+                                     : launch_decode_rep<D, true, false>(d, rep, rows, nkv, stream);
+    return d.n_split <= 1 ? launch_decode_rep<D, false, true>(d, rep, rows, nkv, stream)
+                          : launch_decode_rep<D, true, true>(d, rep, rows, nkv, stream);
 }
 
 bool attention_is_decode(bool cache, int T, int B, int nh, int nkv) {
     const int rep = nh / nkv;
     return cache && T <= 4 * B && (rep == 1 || rep == 2 || rep == 4 || rep == 8);
 }
+
+bool attention_rotates(int T, int B, int hidden, int head_dim) { return hidden >= head_dim && T - B <= kAttnFuseNew; }
 
 // Few rows: cut the cached keys.  With the ranges' length set on the device they are equally long over all rows and fill the chip
 // once (`target`: what the split kernel's registers let a CU hold); sequences of different lengths cut into equally many
@@ -817,7 +827,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
     d.kv_old = a.kv_old;
     d.cap = a.cap;
     d.scale_log2 = kLog2e / sqrtf(static_cast<float>(a.d));
-    if (a.cs) {                                                  // decode style (attention_is_decode)
+    if (a.decode) {
         d.cs = a.cs;
         d.arrive = a.arrive;
         d.chunk = a.chunk;

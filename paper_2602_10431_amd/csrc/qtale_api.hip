@@ -215,13 +215,17 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     s.idx = ws.idx; s.count = count; s.cu_exec = ws.cu_exec; s.row_seq = ws.row_seq;
     s.kv_len = kv ? kv->kv_len : nullptr; s.kv_old = ws.kv_old; s.kv_cap = kv ? kv->cap : 0;
     s.idx_copy = sel_idx; s.count_copy = sel_count;
-    // Decode-style attention rotates and appends by itself: the first kernels leave it the rows' rotary table (in the
+    // Decode-style attention mostly rotates and appends by itself: the first kernels leave it the rows' rotary table (in the
     // buffer of the residual h, which is written after attention) and cleared arrival counters (in the buffer of act).
-    const bool decode_attn = attention_is_decode(kv != nullptr, T, B, nh, nkv) && H >= d;
+    const bool decode_attn = attention_is_decode(kv != nullptr, T, B, nh, nkv);
+    const bool attn_rotates = decode_attn && attention_rotates(T, B, H, d);
     RowAux aux{};
-    if (decode_attn) {
+    if (attn_rotates) {
         aux.cs = reinterpret_cast<float2*>(ws.h); aux.positions = positions; aux.half = d / 2; aux.base = c->rope_base;
-        const bool device_chunk = fused_select_norm_fits(T, M_max);   // the calls whose first kernel sees all cache lengths
+    }
+    if (decode_attn) {
+        // the calls whose first kernel sees all cache lengths (and whose ranges do not cover new keys)
+        const bool device_chunk = attn_rotates && fused_select_norm_fits(T, M_max);
         const int ranges = attention_splits(M_max, nh, nkv, kv->cap, device_chunk, &aux.target);
         if (2 * nkv <= I && ranges > 1) {
             aux.arrive = reinterpret_cast<int32_t*>(ws.act);
@@ -291,7 +295,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         Prof pr(ctx, stream, 3);
         HIP_TRY(launch_gemm_w4a16(qg, stream));
     }
-    if (!decode_attn) {
+    if (!attn_rotates) {
         Prof pr(ctx, stream, 4);
         RopeArgs r{};
         r.qkv = ws.qkv; r.nh = nh; r.nkv = nkv; r.d = d; r.base = c->rope_base;
@@ -307,7 +311,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         a.B = B; a.cu_exec = ws.cu_exec; a.row_seq = ws.row_seq;
         if (kv) { a.k_cache = kv->k_cache; a.v_cache = kv->v_cache; a.cap = kv->cap; }
         a.kv_old = ws.kv_old; a.T = T; a.items = ws.items; a.n_items = ws.scalars + 1; a.partials = ws.attn_part;
-        a.cs = aux.cs; a.arrive = aux.arrive; a.chunk = aux.chunk;
+        a.decode = decode_attn; a.cs = aux.cs; a.arrive = aux.arrive; a.chunk = aux.chunk;
         HIP_TRY(launch_attention(a, stream));
     }
     {

@@ -181,16 +181,17 @@ struct AttnArgs {
     const int32_t* cu_exec;    // [B+1]
     const int32_t* row_seq;    // [rows]
     // cache (nullable): when given, keys/values are read from the cache only (launch_rope_append has appended the new
-    // rows; decode-style calls append them here)
+    // rows; calls with `cs` append them here)
     void* k_cache; void* v_cache; int cap;
     const int32_t* kv_old;     // [B]
     int T;                     // tokens in the call
     void* items;               // scratch: (max_rows / kAttnBQ + B + 1) x int4 work list of the prefill kernel, 16-byte aligned
     int32_t* n_items;          // scratch [1]
-    // decode-style calls (attention_is_decode): q and k of the new rows arrive unrotated, the kernel rotates them with this
-    // table (RowAux) and appends the new keys and values to the cache
+    bool decode;               // attention_is_decode: one workgroup per (row, kv head)
+    // of those, the calls that attention_rotates names: q and k of the new rows arrive unrotated, the kernel rotates them
+    // with this table (RowAux) and appends the new keys and values to the cache.  Else null, launch_rope_append came before.
     const float2* cs;
-    const int32_t* chunk;      // nullable: keys per range (RowAux); else every row is cut into equally many ranges
+    const int32_t* chunk;      // nullable: keys per range (RowAux, only with cs); else every row is cut into equally many ranges
     int32_t* arrive;           // nullable: max_rows x nkv zeroed counters (RowAux); without them keys are not split
     float* partials;           // scratch (nullable): min(max_rows, kAttnSplitRows) x nh x kAttnSplitMax x (d + 2) fp32,
                                // lets the decode kernel cut long caches into key ranges when there are few rows
@@ -199,6 +200,13 @@ constexpr int kAttnBQ = 128;   // executed rows per prefill-attention workgroup
 constexpr int kAttnSplitRows = 128;   // decode attention splits the keys only up to this many rows
 constexpr int kAttnSplitMax = 8;      // and into at most this many ranges
 bool attention_is_decode(bool cache, int T, int B, int nh, int nkv);
+// Decode-style calls whose attention kernel also rotates and appends.  (The rows' table lies in the buffer of the residual: head_dim
+// must not exceed hidden.)  The kernel rotates a sequence's new keys again for each of its rows, so a long new part beside many
+// single tokens costs more than the launch that it saves; T - B bounds the longest if no sequence is empty.  Layers on 1000 cached
+// keys, us, rotating inside / before: 7B shape 4 x 4 tokens 85.6 / 88.8, 31 x 1 + 65 242.4 / 242.5, 31 x 1 + 97 278 / 273,
+// 63 x 1 + 190 536 / 502, 127 x 1 + 385 1056 / 920; 8B-GQA 32 x 2 141 / 145, 31 x 1 + 97 204 / 206, 63 x 1 + 190 346 / 340.
+constexpr int kAttnFuseNew = 96;
+bool attention_rotates(int T, int B, int hidden, int head_dim);
 // Key ranges per (row, kv head) of a decode-style call (1 = not split).  device_chunk: the ranges' length is set on the device
 // (RowAux::chunk) and the result is the bound on their number; target (nullable): workgroups that run at once.
 int attention_splits(int max_rows, int nh, int nkv, int cap, bool device_chunk, int* target);

@@ -94,6 +94,25 @@ def test_decode_attention_rotates_and_appends(qt, rep, d):
     _cache_case(qt, shape, [40, 0, 1, 3] + [0] * 8, [70, 5, 640, 0] + [1] * 8, [70, 5, 640, 0] + [1] * 8, 641, 510 + rep, 1.0)
 
 
+@pytest.mark.parametrize("rep", [1, 2, 4, 8])
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_attention_after_a_separate_append(qt, rep, d):
+    # more than 96 new tokens beyond one per sequence: rotation and append are a launch of their own; keys not split (134
+    # rows), and split into equally many ranges per row (67 rows), with an empty sequence, fresh and very short caches
+    shape = si.LayerShape(256, 2 * rep, 2, d, 128, 4, 32, "fp16")
+    lens = [100, 0] + [1] * 34
+    old = [300, 9] + [int(v) for v in np.random.default_rng(rep * d).integers(0, 640, size=34)]
+    old[5], old[6] = 0, 1
+    _cache_case(qt, shape, lens, old, old, 641, 520 + rep, 1.0)
+    _cache_case(qt, shape, lens, old, old, 641, 530 + rep, 0.5)
+
+
+@pytest.mark.parametrize("lens,old,cap", [([1, 1, 1], [300, 0, 77], 304), ([2, 0, 3], [63, 5, 700], 704), ([1] * 140, [90] * 140, 96)])
+def test_decode_attention_of_heads_wider_than_the_hidden_size(qt, lens, old, cap):
+    # the rotary table has no room in the residual's buffer: the same decode kernel, rotation and append before it
+    _cache_case(qt, si.LayerShape(64, 4, 2, 128, 136, 4, 32, "bf16"), lens, old, old, cap, 540 + len(lens), 1.0)
+
+
 def test_decode_rows_that_do_not_fit_the_cache(qt):
     # five new rows, room for two: the others are dropped, see what the cache holds, and the counter stops at the capacity
     shape = si.LayerShape(256, 4, 2, 64, 344, 4, 32, "fp16")
