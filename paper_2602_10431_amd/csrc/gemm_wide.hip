@@ -40,13 +40,13 @@ gemm_wide_kernel(GemmDev p) {
     __shared__ __attribute__((aligned(16))) char smem[kABytes > kSlabBytes ? kABytes : kSlabBytes];
     half_t* As = reinterpret_cast<half_t*>(smem);
 
-    // workgroup -> (column block, row chunk, k-part); the chunks of a column block get ids 8 apart: the same XCD's L2 serves
-    // their weights
-    const int within = blockIdx.x % (8 * p.row_chunks);
-    const int tile_n = (blockIdx.x / (8 * p.row_chunks)) * 8 + (within & 7);
+    // workgroup -> (column block, row chunk, k-part): all column blocks (padded to a multiple of 8, so that the chunks of one
+    // are served by the same XCD's L2) of the first chunk, then of the next.
+    const int tiles_pad = (p.tiles_n + 7) & ~7;
+    const int chunk = blockIdx.x / tiles_pad, tile_n = blockIdx.x - chunk * tiles_pad;
     const int ks = blockIdx.y;
     if (tile_n >= p.tiles_n) return;
-    const int row0 = (within >> 3) * p.chunk_rows;
+    const int row0 = chunk * p.chunk_rows;
     const int M = min((p.count ? min(*p.count, p.M_max) : p.M_max) - row0, p.chunk_rows);
     if (M <= 0) return;
     const int tid = threadIdx.x, lane = tid & 63;
