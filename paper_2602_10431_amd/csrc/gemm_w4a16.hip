@@ -324,10 +324,12 @@ static hipError_t launch_small_rows(GemmDev& d, const GemmArgs& a, bool parts_ok
 // the latency of its k-tiles) and the 128-row kernel does not.  Linears, us, 64-row / 128-row kernel: 6144 x 4096 at 320 rows (one
 // round) 25.6 / 30.6, at 400 rows 36.6 / 33.1, at 640 rows 42.6 / 39.0; 8192 x 4096 at 257 / 512 rows 35.9 / 28.1, 43.6 / 40.0;
 // 4096 x 4096 at 500 rows (one round) 26.1 / 30.9, 640 and 900 rows 36.4 / 32.1, 42.4 / 39.3; 12288 x 4096 at 500 rows (two rounds
-// of either) 59.7 / 67.0.
+// of either) 59.7 / 67.0.  A short K leaves the 128-row kernel's k-slices too few rounds to pay for their meeting: 4096 columns at 800
+// rows, K = 512 / 1024 / 2048 / 4096: 11.4 / 12.7, 15.2 / 17.1, 24.5 / 24.1, 41.5 / 37.8; 8192 columns at 320 rows 10.1 / 12.2,
+// 14.2 / 15.8, 22.2 / 21.8, 39.5 / 34.3.
 static bool wide_round(const GemmDev& d) {
     const int cus = resident_workgroups(1), cols = (d.vf_total + 3) / 4;
-    return d.M_max > kGemmWideRows && cols * ((d.M_max + 63) / 64) > cus && cols * ((d.M_max + 127) / 128) <= cus;
+    return d.KT >= 32 && d.M_max > kGemmWideRows && cols * ((d.M_max + 63) / 64) > cus && cols * ((d.M_max + 127) / 128) <= cus;
 }
 
 // Residual outputs above 64 rows on the 128-row kernel: the number of K parts, as many as one round of the chip takes and the

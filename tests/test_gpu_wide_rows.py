@@ -74,20 +74,24 @@ def test_stack_with_k_parts_equals_layer_by_layer_calls(qt):
 
 # three to six row chunks; the parts' buffer of the first shape (1.6 M floats) holds two parts up to 315 rows and none beyond, the
 # narrow one takes four parts at 513 rows, two at 768 and the ordinary path at 769; at 801 rows of the first shape the 128-row
-# kernel saves a round: it takes q|k|v, and the down-proj with one part (the o-proj has no room for one)
+# kernel saves a round for q|k|v (K of 41 k-tiles; the down-proj's 27 are too few), and with a longer down-proj for that one too,
+# with one part (the o-proj has no room for one)
+LONG_DOWN = si.LayerShape(2568, 24, 24, 64, 2056, 4, 64, "bf16")
 NARROW = si.LayerShape(1032, 32, 8, 64, 1096, 4, 128, "fp16")
 
 
 @pytest.mark.parametrize("shape,T,mode,val", [(SHAPE, 257, "ratio", 1.0), (SHAPE, 315, "ratio", 1.0), (SHAPE, 316, "ratio", 1.0),
                                               (SHAPE, 310, "threshold", 0.5), (NARROW, 513, "ratio", 1.0),
                                               (NARROW, 768, "threshold", 0.5), (NARROW, 769, "ratio", 1.0),
-                                              (SHAPE, 801, "ratio", 1.0), (SHAPE, 801, "threshold", 0.5)])
+                                              (SHAPE, 801, "ratio", 1.0), (SHAPE, 801, "threshold", 0.5),
+                                              (LONG_DOWN, 801, "ratio", 1.0), (LONG_DOWN, 801, "threshold", 0.3)])
 def test_layer_with_k_parts_in_more_row_chunks(qt, shape, T, mode, val):
     _check_layer(qt, shape, T, [T // 3, 0, T - T // 3], mode, val, seed=T)
 
 
 # the 128-row kernel fills one round where the 64-row kernel needs two: from the first row count above 256 to a full round of
-# 256 workgroups, and 261, which go elsewhere
+# 256 workgroups, and 261, which go elsewhere, as do K of less than 32 k-tiles
 @pytest.mark.parametrize("M,N,bits,G", [(257, 8200, 4, 128), (385, 6152, 3, 32), (1000, 4096, 2, 64), (1025, 3592, 4, 64)])
-def test_linear_that_fills_one_round_of_128_row_workgroups(qt, M, N, bits, G):
-    test_linear_of_a_hundred_rows(qt, M, N, 328, G, bits)
+@pytest.mark.parametrize("K", [328, 2008])
+def test_linear_that_fills_one_round_of_128_row_workgroups(qt, M, N, bits, G, K):
+    test_linear_of_a_hundred_rows(qt, M, N, K, G, bits)
