@@ -384,6 +384,18 @@ static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t str
     return launch_gemm_skinny(d, a.epilogue, stream);
 }
 
+// At most kFewRows rows: the outputs whose 16-column groups need a second round of workgroups that is mostly empty.  us, few-row /
+// 17-to-64-row kernel, 12 and 16 rows: store 20480 columns (320 workgroups) K = 4096 18.2 / 17.6, 18.7 / 17.5; 5120 22.8 / 20.2, 23.6 /
+// 20.1; 8192 33.8 / 29.9, 35.6 / 31.6 (8 rows 20.1 / 20.6 at 5120); 32000 (500) 22.6 / 23.5, 23.1 / 23.7; 15360 (240) 16 rows 12.3 / 12.8.
+// Gate/up 14336 (448), 14 and 16 rows: K = 2048 16 rows 10.9 / 12.6; 4096 20.9 / 21.6, 20.9 / 21.2; 5120 23.5 / 24.1, 24.6 / 24.1; 8192
+// 37.4 / 38.8, 38.9 / 36.1; 18944 (592) 4096 16 rows 27.2 / 35.7.
+static bool few_overflows(const GemmDev& d, int epilogue) {
+    const int cus = resident_workgroups(1);
+    if (epilogue == EPI_SWIGLU_F16) return d.M_max > 14 && d.KT >= 80 && d.vf_total > 3 * cus && d.vf_total <= 4 * cus;
+    const int groups = (d.vf_total + 1) / 2;
+    return epilogue == EPI_STORE_F16 && d.M_max > 8 && groups > cus && 2 * groups <= 3 * cus;
+}
+
 hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     if (a.M_max <= 0) return hipSuccess;
     GemmDev d{};
@@ -417,7 +429,7 @@ hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     // Few rows: the weight stream dominates and 128-row tiles cannot fill the chip.  Each range has a kernel of its own:
     // gemm_few.h, launch_small_rows, launch_mid_rows.
     if (a.n_parts) *a.n_parts = 0;
-    if (d.M_max <= kFewRows) return launch_gemm_few(d, a.epilogue, a.pro, resident_workgroups(1), stream);
+    if (d.M_max <= kFewRows && !few_overflows(d, a.epilogue)) return launch_gemm_few(d, a.epilogue, a.pro, resident_workgroups(1), stream);
     if (d.M_max <= kGemmPartRows) return launch_small_rows(d, a, true, stream);
     if (d.M_max <= kGemmWideRows) return launch_mid_rows(d, a, stream);
     if (wide_parts(d, a) > 0) return launch_wide_parts(d, a, stream);

@@ -1,5 +1,5 @@
-"""GPU parity of the linears at 65 to 256 rows (run with -m gpu): the 128-row x 128-column K-sliced kernel in its three
-epilogues, and the shapes next to it that stay on the other kernels.  References and tolerances as in the other GPU tests."""
+"""GPU parity of the linears at 65 to 256 rows, and at 9 to 16 rows of very wide outputs (run with -m gpu): the 128-row x
+128-column K-sliced kernel in its three epilogues, and the shapes next to it that stay on the other kernels.  References and tolerances as in the other GPU tests."""
 import pytest
 import torch
 
@@ -45,6 +45,17 @@ def test_swiglu_of_a_hundred_rows(qt, M, I, K, G, bits):
     d = [orc.dequantize(*orc.quantize_rtn(W.numpy(), bits, G), G).T for W in (Wg, Wu)]
     want = orc.silu(to_f64(A) @ d[0]) * (to_f64(A) @ d[1])
     check_parity(orc.parity_error(to_f64(out), want), "fp16", ("swiglu", M, I, K))
+
+
+# 9 to 16 rows: widths whose 16-column groups overflow one round of workgroups a little go to the kernel of 17 to 64 rows
+@pytest.mark.parametrize("M,N,K", [(8, 20488, 136), (9, 20488, 136), (16, 24576, 72), (16, 24584, 72)])
+def test_few_row_linear_past_one_round(qt, M, N, K):
+    test_linear_of_a_hundred_rows(qt, M, N, K, 64, 4)
+
+
+@pytest.mark.parametrize("M", [14, 15, 16])
+def test_few_row_swiglu_past_one_round(qt, M):
+    test_swiglu_of_a_hundred_rows(qt, M, 12304, 5064, 128, 4)
 
 
 # hidden 2568: 21 column blocks, two row chunks, the o- and down-proj leave K parts (27 k-tiles with a ragged last one)
