@@ -354,28 +354,46 @@ static hipError_t launch_wide_parts(GemmDev& d, const GemmArgs& a, hipStream_t s
     return launch_gemm_wide(d, EPI_PARTIAL_F32, *a.n_parts, stream);
 }
 
-// 65 to kGemmWideRows rows.  Measured with 4-bit group-128 weights on 7B-, 8B-GQA- and 13B-shaped linears (us at 66 / 128 /
-// 150 / 256 rows; "wide" counts its workgroups per 128-row chunk, one workgroup per CU):
-//   gate/up, 172 to 224 wide workgroups per chunk: wide 28-38 / 36-48 / 55-70 / 72-90, mid 37-48 / 38-49 / 58-75 / 63-85, skinny
-//     36-55 / 40-60 / 55-81 / 73-105; 88 workgroups (hidden 2048): skinny 15 / 16, wide 17 / 22 / 18 / 22, mid 21 at any
-//   q|k|v 6144 to 15360 wide: decode 18-31 / 18-32 / 21-52 / 24-60, skinny 22-37 / 24-41 / 30-53 / 35-74, wide 27-32 / 34-43 /
-//     27-37 / 34-50 (best at two chunks once they fill the chip); 3072 and 4096 wide: skinny 8-12 / 8-14 / 13-22 / 15-24, decode
-//     10-17 / 10-18 / 11-18 / 11-19
-//   residual outputs with K cut over workgroups (fp32 parts, added by the next kernel): 13B down-proj at 77 rows 59.5 -> 31.5 + 5.3,
-//     o-proj 31.7 -> 18.1 (+ 3.6 in RMSNorm 2); with fewer than 40 column blocks x chunks the four parts do not fill the chip and skinny is level or better.
+// 65 to kGemmWideRows rows.  Measured with 4-bit group-128 weights, us, cold, launches of a graph (K = 4096 unless stated).
+// The 64-row-chunk kernel (skinny) is the fastest where its workgroups run at once, one per CU (two per CU for gate/up):
+//   store, 96 / 160 rows, skinny / decode / wide: 2048 columns 11.8 / 16.8 / 26, 12.3 / 17.4 / 26; 2560 columns (240 workgroups at 160
+//     rows) 12.0 / 17.0 / 26, 12.7 / 18.5 / 27; 3072 columns (288 at 160 rows) 12.2 / 17.2 / 26, 20.5 / 17.6 / 27; 8192 columns
+//     (two fragments per workgroup, 256 at 96 rows) 18.3 / 18.9 / 27, 28.7 / 24.5 / 28; but with K = 1024 9.9 / 9.3, 512 8.5 / 6.9
+//   gate/up, 128 / 192 / 256 rows, skinny / wide / mid: 2816 columns (176 to 352 workgroups) 16.0 / 31 / 37, 24 / 27 / 37, 25 / 33 / 37;
+//     5632 (352, 528, 704) 25.7 / 33 / 38, 37 / 30 / 39, 39 / 34 / 38; 8192 (512 at 65 to 128 rows) 65 rows 28.7 / 28.1 / 38, 128 rows
+//     30.5 / 34 / 38, with K = 2048 17.2 / 18.4, 19.0 / 21.8
+// Beyond that, gate/up:
+//   one round of wide workgroups (128 rows x 128 columns, one per CU): 5632 and 8192 columns (176 and 256) at 224 rows, wide / mid:
+//     34 / 39, 41 / 46, with K = 2048 22.0 / 23.1, 24.8 / 26.2, K = 1024 16.0 / 15.6, 17.2 / 16.7; 11008 columns at 65 / 96 / 128 rows, skinny / wide / mid:
+//     43 / 31 / 41, 39 / 32 / 41, 41 / 38 / 41; 14336: 54 / 35 / 45, 52 / 36 / 46, 53 / 43 / 46; 18944 (296 workgroups): 64 / 58 / 67,
+//     66 / 62 / 67, 68 / 76 / 68
+//   129 to 192 rows: 11008 (344 workgroups) 59 / 59 / 65, K = 2048 34 / 35 / 35, K = 1024 21.5 / 25 / 22; 14336 (448) 76 / 63 / 68, K = 1024
+//     26 / 26 / 24; 18944 (592, three rounds) 91 / 91 / 77;   193 to 256 rows: 11008 77 / 74 / 68, 14336 91 / 80 / 76
+// Beyond that, store: 6144 columns at 96 / 160 rows, decode / wide / mid 18 / 27 / 24, 21 / 27 / 24; 12288: 24 / 28 / 26, 45 / 29 / 37.
+// Residual outputs with K cut over workgroups (fp32 parts, added by the next kernel): 13B down-proj at 77 rows 59.5 -> 31.5 + 5.3,
+//   o-proj 31.7 -> 18.1 (+ 3.6 in RMSNorm 2); with fewer than 40 column blocks x chunks the four parts do not fill the chip and skinny is level or better.
 static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t stream) {
     const int cus = resident_workgroups(1);
     const int chunks = d.M_max > kGemmWideRows / 2 ? 2 : 1;
     const int blocks = ((d.vf_total + 3) / 4) * chunks;              // wide workgroups
+    const int frags = a.epilogue == EPI_SWIGLU_F16 || d.vf_total >= 256 ? 2 : 1;   // per skinny workgroup
+    // (a device-side count: as if half of the bound executed; the other chunks leave at once.  Hidden 2048, 130 to 192 tokens in
+    // threshold mode, gate/up on the wide kernel: 4 to 9 % of the layer)
+    const int skinny = ((d.vf_total + frags - 1) / frags) * (d.count && !d.rows_exact ? 2 : (d.M_max + 63) / 64);
     if (a.epilogue == EPI_SWIGLU_F16) {
-        if (chunks == 1 && (blocks < cus / 2 || blocks > cus)) return blocks > cus ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_skinny(d, a.epilogue, stream);
-        if (d.M_max > 192) return launch_gemm_mid(d, a.epilogue, stream);
-        return launch_gemm_wide(d, a.epilogue, 1, stream);
+        if (skinny < 2 * cus || (skinny == 2 * cus && (d.M_max > 96 || d.KT <= 32))) return launch_gemm_skinny(d, a.epilogue, stream);
+        if (blocks <= cus) {                                         // one round of wide workgroups
+            return d.M_max > 192 && d.KT < 32 ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_wide(d, a.epilogue, 1, stream);
+        }
+        if (chunks == 1) return d.M_max <= 96 && d.KT >= 64 ? launch_gemm_wide(d, a.epilogue, 1, stream) : launch_gemm_mid(d, a.epilogue, stream);
+        if (d.M_max > 192 || blocks > 2 * cus) return launch_gemm_mid(d, a.epilogue, stream);
+        if (d.KT <= 32 && 2 * blocks <= 3 * cus) return launch_gemm_skinny(d, a.epilogue, stream);
+        return d.KT <= 16 ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_wide(d, a.epilogue, 1, stream);
     }
     if (a.epilogue == EPI_STORE_F16) {
+        if (skinny <= cus && (frags == 1 || d.KT >= 64)) return launch_gemm_skinny(d, a.epilogue, stream);
         if (blocks > cus) return launch_gemm_mid(d, a.epilogue, stream);
         if (8 * blocks >= 5 * cus) return launch_gemm_wide(d, a.epilogue, 1, stream);
-        if (chunks == 1 && d.vf_total < 192) return launch_gemm_skinny(d, a.epilogue, stream);
         int nwn;
         gemm_decode_plan(d, a.epilogue, 1, &nwn);
         return launch_gemm_decode(d, a.epilogue, nwn, 1, stream);

@@ -47,6 +47,23 @@ def test_swiglu_of_a_hundred_rows(qt, M, I, K, G, bits):
     check_parity(orc.parity_error(to_f64(out), want), "fp16", ("swiglu", M, I, K))
 
 
+# Each arm of the rules: narrow and very narrow outputs whose 64-row chunks run at once (one fragment per workgroup; two, with
+# K of 64 k-tiles), just past one round, and above 192 rows.
+@pytest.mark.parametrize("M,N,K,G,bits", [(129, 8, 136, 128, 4), (256, 1032, 328, 32, 3), (192, 2728, 72, 64, 4), (193, 2056, 520, 64, 2),
+                                          (97, 8192, 4104, 128, 4), (129, 8192, 4104, 128, 4)])
+def test_narrow_linear_of_a_hundred_rows(qt, M, N, K, G, bits):
+    test_linear_of_a_hundred_rows(qt, M, N, K, G, bits)
+
+
+# gate/up: two workgroups per CU of 64-row chunks (up to 512, and one more), one round of wide workgroups above 192 rows with K of
+# 32 k-tiles and with less, a second round with little K (64-row chunks, 64-row tiles), more than a round at 65 to 96 rows
+@pytest.mark.parametrize("M,I,K,G,bits", [(256, 4096, 72, 32, 4), (256, 4104, 72, 64, 3), (200, 4104, 2056, 128, 4), (256, 8192, 2056, 64, 2),
+                                          (65, 8192, 520, 128, 4), (129, 11008, 136, 128, 4), (192, 12296, 72, 64, 4), (150, 12296, 1096, 32, 4),
+                                          (96, 16392, 4104, 128, 4)])
+def test_swiglu_of_a_hundred_rows_in_each_arm(qt, M, I, K, G, bits):
+    test_swiglu_of_a_hundred_rows(qt, M, I, K, G, bits)
+
+
 # 9 to 16 rows: widths whose 16-column groups overflow one round of workgroups a little go to the kernel of 17 to 64 rows
 @pytest.mark.parametrize("M,N,K", [(8, 20488, 136), (9, 20488, 136), (16, 24576, 72), (16, 24584, 72)])
 def test_few_row_linear_past_one_round(qt, M, N, K):
