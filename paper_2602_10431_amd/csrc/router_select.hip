@@ -138,13 +138,13 @@ hipError_t launch_reduce_scatter_score(const float* part, int n_parts, int part_
 // z = l_e - l_b (the two-class softmax gives p_0 = sigmoid(z)).  All sums in fp64, one rounding to fp32, so
 // the executed set is reproducible exactly as for the linear router.
 //
-// The first layer is a [T x H] x [H x R] product in fp64 on the vector ALUs.  A workgroup owns 16 tokens (four
-// per wave) and walks H in chunks of 512 columns: the W1 chunk of 4 hidden units is staged in LDS once per
-// workgroup (two buffers, the next chunk's global loads are issued before the current one is consumed, one
-// barrier per chunk), a lane holds 8 consecutive columns of its four tokens, and every staged weight is
-// converted to fp64 once and used for four tokens (16 accumulators of two registers each per lane, two
-// workgroups per CU; 8 units per pass would spill).  The walk repeats per group of 4 units (x then comes
-// from L2).
+// The first layer is a [T x H] x [H x R] product in fp64 on the vector ALUs.  A workgroup owns 4 x kMlpTW tokens (kMlpTW =
+// 1, 2 or 4 per wave, by the number of tokens: launch_router_mlp) and walks H in chunks of 512 columns: the W1 chunk of 4
+// hidden units is staged in LDS once per workgroup (two buffers, the next chunk's global loads are issued before the current
+// one is consumed, one barrier per chunk), a lane holds 8 consecutive columns of its tokens, and every staged weight is
+// converted to fp64 once and used for all of them (at four tokens 16 accumulators of two registers each per lane, two
+// workgroups per CU; 8 units per pass would spill).  A token's sums do not depend on kMlpTW.  The walk repeats per group of 4
+// units (x then comes from L2).
 constexpr int kMlpRC = 4;         // hidden units per pass
 constexpr int kMlpKC = 512;       // columns per staged chunk
 constexpr int kMlpWL = (kMlpRC * kMlpKC / 4) / 256;   // float4 loads per thread per chunk

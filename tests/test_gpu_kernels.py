@@ -211,6 +211,13 @@ def test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype):
     assert np.array_equal(z.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("T", [1023, 2048, 2049, 4095, 4096, 4097, 5003])
+@pytest.mark.parametrize("H,R,dtype", [(72, 5, "fp16"), (520, 4, "bf16")])
+def test_mlp_router_scores_are_bit_exact_in_every_token_form(qt, T, H, R, dtype):
+    # one, two (above 2048 tokens) and four (above 4096) tokens per wave, at the edges and with ragged last workgroups
+    test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype)
+
+
 @pytest.mark.parametrize("K,G,bits", [(40, 32, 4), (72, 64, 3), (264, 128, 2), (320, 32, 3), (384, 128, 4), (456, 64, 2)])
 def test_large_tile_gemm_short_and_ragged_k(qt, K, G, bits):
     # 2600 rows x 2048 columns is past the 64-row-tile regime, so these run the 128 x 256 tiles: one to eight
