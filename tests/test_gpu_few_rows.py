@@ -8,7 +8,7 @@ import torch
 import synth_inputs as si
 from oracle import qtale_oracle as orc
 from tests.helpers import cfg_dict, check_parity, oracle_layer, to_f64
-from tests.test_gpu_layer import _cache_case, _run_layer
+from tests.test_gpu_layer import _cache_case, _check_layer, _run_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -81,6 +81,16 @@ def test_selection_inside_the_first_gemm(qt, router, mode, val):
     assert torch.equal(got[skipped], x[skipped])
     if len(widx):
         check_parity(orc.parity_error(to_f64(got)[widx], want[widx]), shape.act_dtype, ("few tokens", router, mode, val), hidden=shape.hidden)
+
+
+# Workgroup shapes of the launches that select and normalise (16-column fragments of q|k|v: up to 512, 768, more; pairs of
+# gate and up: up to 512, 768, more), and a hidden size whose row takes two passes of the 768-thread workgroups
+@pytest.mark.parametrize("H,nh,nkv,I,bits,dtype", [(256, 40, 20, 4104, 4, "bf16"), (128, 80, 40, 8200, 3, "fp16"), (256, 120, 60, 12296, 4, "fp16"),
+                                                   (6152, 80, 40, 8200, 4, "bf16")])
+@pytest.mark.parametrize("T,mode,val", [(1, "ratio", 1.0), (3, "threshold", 0.5), (4, "ratio", 0.5), (4, "threshold", 0.5)])
+def test_fused_prologues_in_every_workgroup_shape(qt, H, nh, nkv, I, bits, dtype, T, mode, val):
+    shape = si.LayerShape(H, nh, nkv, 64, I, bits, 64, dtype)
+    _check_layer(qt, shape, T, [T // 2, 0, T - T // 2], mode, val, seed=600 + T, std=1.28 / H ** 0.5, starts=[0, 5, 9])
 
 
 @pytest.mark.parametrize("rep", [1, 2, 4, 8])
