@@ -93,6 +93,20 @@ def test_fused_prologues_in_every_workgroup_shape(qt, H, nh, nkv, I, bits, dtype
     _check_layer(qt, shape, T, [T // 2, 0, T - T // 2], mode, val, seed=600 + T, std=1.28 / H ** 0.5, starts=[0, 5, 9])
 
 
+@pytest.mark.parametrize("rep", [1, 4])
+@pytest.mark.parametrize("d", [64, 128])
+def test_decode_calls_of_more_than_256_tokens(qt, rep, d):
+    # selection and normalisation are launches of their own, and the normalising one leaves the rotary table and the cleared
+    # counters; with 90 executed rows the keys are split into equally many ranges per row (no length from the device); empty,
+    # very short and full caches.  Two tokens per sequence: the same with rotation and append before the attention kernel.
+    shape = si.LayerShape(256, rep, 1, d, 344, 4, 32, "fp16")
+    old = [int(v) for v in np.random.default_rng(rep + d).integers(0, 511, size=300)]
+    old[:6] = [0, 1, 511, 2, 0, 63]
+    _cache_case(qt, shape, [1] * 300, old, old, 512, 550 + rep, 1.0)
+    _cache_case(qt, shape, [1] * 300, old, old, 512, 560 + rep, 0.3)
+    _cache_case(qt, shape, [2] * 150, old[:150], old[:150], 513, 570 + rep, 0.4)
+
+
 @pytest.mark.parametrize("rep", [1, 2, 4, 8])
 @pytest.mark.parametrize("d", [64, 128])
 def test_decode_attention_rotates_and_appends(qt, rep, d):

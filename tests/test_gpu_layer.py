@@ -262,7 +262,7 @@ def test_random_prefill_layer_configurations(qt):
 @pytest.mark.parametrize("nh,nkv,d", [(4, 4, 64), (8, 2, 128), (4, 1, 128)])
 def test_decode_attention_with_split_key_ranges(qt, nh, nkv, d):
     # few rows against long caches: the decode attention kernel cuts each (row, kv head) into key ranges that
-    # separate workgroups stream and a merge kernel combines; one sequence is so short that most of its ranges
+    # separate workgroups stream and the last of them to arrive combines; one sequence is so short that most of its ranges
     # are empty, one call has several new rows per sequence, one cache is exactly full after the append
     shape = si.LayerShape(256, nh, nkv, d, 512, 4, 32, "fp16")
     _cache_case(qt, shape, [1, 1, 1], [1500, 1030, 7], [1500, 1030, 7], 1600, 61, 1.0)
