@@ -376,8 +376,12 @@ hipError_t launch_gemm_skinny(GemmDev& d, int epilogue, hipStream_t stream);
 int gemm_decode_plan(const GemmDev& d, int epilogue, int split_max, int* nwn_out);
 hipError_t launch_gemm_decode(GemmDev& d, int epilogue, int nwn, int split, hipStream_t stream);
 hipError_t launch_gemm_few(const GemmDev& d, int epilogue, const FewPrologue* pro, int cus, hipStream_t stream);   // at most kFewRows rows
-// 65 to 256 rows; EPI_STORE_F16, EPI_SWIGLU_F16 and (any ksplit, out = fp32 [ksplit][M_max][ldo]) EPI_PARTIAL_F32.
-int gemm_wide_blocks(const GemmDev& d);     // workgroups without a K split
+// Any row count (the rules in gemm_w4a16.hip send it 65 rows and more); EPI_STORE_F16, EPI_SWIGLU_F16 and (any ksplit, out =
+// fp32 [ksplit][M_max][ldo]) EPI_PARTIAL_F32.
+constexpr int kWideRows = 128, kWideFrags = 4;   // rows and 32-column fragments of a workgroup
+inline int gemm_wide_cols(const GemmDev& d) { return (d.vf_total + kWideFrags - 1) / kWideFrags; }
+inline int gemm_wide_chunks(const GemmDev& d) { return (d.M_max + kWideRows - 1) / kWideRows; }
+inline int gemm_wide_blocks(const GemmDev& d) { return gemm_wide_cols(d) * gemm_wide_chunks(d); }   // workgroups without a K split
 hipError_t launch_gemm_wide(GemmDev& d, int epilogue, int ksplit, hipStream_t stream);
 hipError_t launch_gemm_mid(GemmDev& d, int epilogue, hipStream_t stream);
 

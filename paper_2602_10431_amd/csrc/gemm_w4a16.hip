@@ -310,7 +310,7 @@ static hipError_t launch_small_rows(GemmDev& d, const GemmArgs& a, bool parts_ok
         gemm_decode_plan(d, a.epilogue, 1, &nwn);
         return launch_gemm_decode(d, a.epilogue, nwn, 1, stream);
     }
-    if (parts_ok && a.part && a.n_parts) {
+    if (parts_ok && a.part && a.n_parts && a.part_floats >= kGemmPartMax * static_cast<size_t>(d.M_max) * a.ldo) {
         int nwn;
         const int split = gemm_decode_plan(d, EPI_PARTIAL_F32, kGemmPartMax, &nwn);
         d.out = a.part;
@@ -328,8 +328,8 @@ static hipError_t launch_small_rows(GemmDev& d, const GemmArgs& a, bool parts_ok
 // rows, K = 512 / 1024 / 2048 / 4096: 11.4 / 12.7, 15.2 / 17.1, 24.5 / 24.1, 41.5 / 37.8; 8192 columns at 320 rows 10.1 / 12.2,
 // 14.2 / 15.8, 22.2 / 21.8, 39.5 / 34.3.
 static bool wide_round(const GemmDev& d) {
-    const int cus = resident_workgroups(1), cols = (d.vf_total + 3) / 4;
-    return d.KT >= 32 && d.M_max > kGemmWideRows && cols * ((d.M_max + 63) / 64) > cus && cols * ((d.M_max + 127) / 128) <= cus;
+    const int cus = resident_workgroups(1), cols = gemm_wide_cols(d);   // 128 columns: also the 64-row kernel's tile
+    return d.KT >= 32 && d.M_max > kGemmWideRows && cols * ((d.M_max + 63) / 64) > cus && gemm_wide_blocks(d) <= cus;
 }
 
 // Residual outputs above 64 rows on the 128-row kernel: the number of K parts, as many as one round of the chip takes and the
@@ -341,7 +341,7 @@ static bool wide_round(const GemmDev& d) {
 constexpr int kGemmPartsMaxRows = 768;
 static int wide_parts(const GemmDev& d, const GemmArgs& a) {
     if (!a.part || !a.n_parts) return 0;
-    const int blocks = ((d.vf_total + 3) / 4) * ((d.M_max + 127) / 128);
+    const int blocks = gemm_wide_blocks(d);
     const size_t room = a.part_floats / (static_cast<size_t>(d.M_max) * a.ldo);
     const int parts = std::min(static_cast<int>(std::min<size_t>(kGemmPartMax, room)), resident_workgroups(1) / std::max(blocks, 1));
     if (d.M_max <= kGemmPartsMaxRows && blocks >= 40 && parts >= 2 && d.KT >= 4 * parts) return parts;
@@ -374,8 +374,7 @@ static hipError_t launch_wide_parts(GemmDev& d, const GemmArgs& a, hipStream_t s
 //   o-proj 31.7 -> 18.1 (+ 3.6 in RMSNorm 2); with fewer than 40 column blocks x chunks the four parts do not fill the chip and skinny is level or better.
 static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t stream) {
     const int cus = resident_workgroups(1);
-    const int chunks = d.M_max > kGemmWideRows / 2 ? 2 : 1;
-    const int blocks = ((d.vf_total + 3) / 4) * chunks;              // wide workgroups
+    const int chunks = gemm_wide_chunks(d), blocks = gemm_wide_blocks(d);
     const int frags = a.epilogue == EPI_SWIGLU_F16 || d.vf_total >= 256 ? 2 : 1;   // per skinny workgroup
     // (a device-side count: as if half of the bound executed; the other chunks leave at once.  Hidden 2048, 130 to 192 tokens in
     // threshold mode, gate/up on the wide kernel: 4 to 9 % of the layer)

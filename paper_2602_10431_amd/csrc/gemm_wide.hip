@@ -1,5 +1,5 @@
-// W4A16 / W3A16 / W2A16 GEMM for 65 to 256 executed rows (large decode batches, short prompts), and
-// for more rows where its workgroups fill the chip once: C[M][N] = A[M][K] x W'[N][K]^T
+// W4A16 / W3A16 / W2A16 GEMM for the wide outputs at 65 to 256 executed rows (large decode batches, short prompts), and for
+// more rows where its workgroups fill the chip once (the rules are in gemm_w4a16.hip): C[M][N] = A[M][K] x W'[N][K]^T
 // with the weights dequantized once per 128-row chunk (Sec. 4.1 weights; rows gathered per App. B.2).
 //
 // At these sizes a linear is a few dozen 128 x 256 tiles, so the prefill kernel leaves most CUs idle, while 64-row chunks of
@@ -25,14 +25,14 @@
 
 namespace qtale {
 
-constexpr int kWideNC = 2, kWideNK = 4, kWideFM = 4;
-constexpr int kWideRows = kWideFM * 32;
+constexpr int kWideNC = 2, kWideNK = 4, kWideFM = kWideRows / 32;
 
 template <int BITS, int GPT, bool SWIGLU>
 __global__ void __launch_bounds__(kWideNC * kWideNK * 64, 2)
 gemm_wide_kernel(GemmDev p) {
     using WB = WBits<BITS>;
-    constexpr int NC = kWideNC, NK = kWideNK, FM = kWideFM, FN = 2, NW = NC * NK;
+    constexpr int NC = kWideNC, NK = kWideNK, FM = kWideFM, FN = kWideFrags / kWideNC, NW = NC * NK;
+    static_assert(FN == 2 && FM == 4 && NK == FM, "gate and up, or two columns; the row fragments are met by one slice each");
     constexpr int TEAM = NC * 64;
     constexpr int kTileHalves = kWideRows * kLdsStride;
     constexpr int SSTR = 36;                                     // slab row stride (floats)
@@ -252,13 +252,11 @@ static hipError_t launch_kind(const GemmDev& d, int epilogue, hipStream_t stream
     return hipGetLastError();
 }
 
-int gemm_wide_blocks(const GemmDev& d) { return ((d.vf_total + 3) / 4) * ((d.M_max + kWideRows - 1) / kWideRows); }
-
 hipError_t launch_gemm_wide(GemmDev& d, int epilogue, int ksplit, hipStream_t stream) {
-    d.tiles_n = (d.vf_total + 3) / 4;
+    d.tiles_n = gemm_wide_cols(d);
     if (d.tiles_n == 0) return hipSuccess;
     // the chunks share the row fragments evenly: 150 rows are 96 + 54, five fragments and not six
-    d.row_chunks = (d.M_max + kWideRows - 1) / kWideRows;
+    d.row_chunks = gemm_wide_chunks(d);
     d.chunk_rows = (((d.M_max + 31) / 32 + d.row_chunks - 1) / d.row_chunks) * 32;
     d.ksplit = ksplit;
     d.epi_rt = epilogue;

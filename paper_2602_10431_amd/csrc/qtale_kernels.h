@@ -114,7 +114,7 @@ hipError_t launch_reduce_scatter(const float* part, int n_parts, const float* h,
 
 // ---- W4A16 / W3A16 GEMM ---------------------------------------------------------------------------------
 enum GemmEpilogue { EPI_STORE_F16 = 0, EPI_RESID_F32 = 1, EPI_SWIGLU_F16 = 2, EPI_RESID_SCATTER = 3,
-                    EPI_PARTIAL_F32 = 4 };   // fp32 partial tiles [parts][M_max][ldo], decode kernel only
+                    EPI_PARTIAL_F32 = 4 };   // fp32 partial tiles [parts][M_max][ldo]: decode and wide kernels
 
 struct GemmWeights {
     const void* prepacked;
@@ -128,7 +128,7 @@ struct GemmArgs {
     int rows_exact;            // nonzero: the row count equals M_max (ratio mode); zero: M_max is a bound, the count is read on the device
     int K;
     int group;
-    int bits;                  // 4 or 3
+    int bits;                  // 4, 3 or 2
     int n_w;                   // number of weight matrices: 1, 2 (gate/up interleaved), 3 (q|k|v concatenated)
     GemmWeights w[3];
     int epilogue;
