@@ -159,6 +159,24 @@ def test_decode_rows_that_do_not_fit_the_cache(qt):
     assert torch.isfinite(full).all()
 
 
+@pytest.mark.parametrize("lens,absent", [([1, 1], {"router", "select", "norm1", "rope_append", "norm2"}), ([1] * 8, {"norm1", "rope_append"}),
+                                         ([110] + [1] * 40, {"norm1"}), ([1] * 300, {"rope_append"})])
+def test_profile_classes_of_fused_calls(qt, lens, absent):
+    # which classes have launches of their own, as include/qtale.h describes them
+    shape = si.LayerShape(256, 4, 2, 64, 344, 4, 32, "fp16")
+    T, B = sum(lens), len(lens)
+    lw = qt.quantize_layer(si.layer_tensors(shape, 0, 12, unit_gains=False, std=0.08), 4, 32)
+    kc, vc = si.kv_cache(shape, B, 160, 0, 12)
+    kv = qt.KVCache.from_token_major(kc.cuda(), vc.cuda(), torch.full((B,), 40, dtype=torch.int32).cuda(), 2)
+    offs, pos = si.ragged_sequences(lens, [40] * B)
+    ctx = qt.Context()
+    qt.qtale_profile_enable(ctx, True)
+    qt.qtale_layer_forward(ctx, qt.cfg_from_shape(shape), lw, si.hidden_states(shape, T, 12).cuda(), offs.cuda(), pos.cuda(), kv=kv)
+    prof = qt.qtale_profile_read(ctx)
+    assert {name for name, (_, n) in prof.items() if n == 0} == absent
+    assert all(n <= 1 for _, n in prof.values())
+
+
 def test_few_row_stack_is_the_same_on_every_run(qt):
     # the last range to arrive combines the key ranges: whichever that is, the bits are the same
     shape = si.LayerShape(256, 8, 2, 64, 344, 4, 32, "bf16")
