@@ -76,6 +76,41 @@ def test_graph_replays_match_eager_decode_steps(qt, mode, val):
         assert torch.equal(kvs2[l].k.cpu(), want_k[l])
 
 
+# three tokens: selection and both normalisations inside the GEMM launches; twelve: split keys with the range length made on the
+# device; 300 at ratio 0.1: split into equally many ranges; one long new part: rotation and append before the split kernel
+@pytest.mark.parametrize("lens,ratio", [([1] * 3, 1.0), ([1] * 12, 0.67), ([1] * 300, 0.1), ([110, 1, 0] + [1] * 40, 0.4)])
+def test_graph_replays_with_split_keys_match_eager_calls(qt, lens, ratio):
+    # the arrival counters and range lengths lie in workspace that other kernels overwrite: every replay rebuilds them
+    shape = si.LayerShape(256, 2, 1, 64, 344, 4, 32, "bf16")
+    L, B, T, cap, steps = 2, len(lens), sum(lens), 900, 3
+    old = [int(v) for v in np.random.default_rng(B).integers(0, 560, size=B)]
+    old[:2] = [560, 0]
+    fresh_stack = _decode_setup(qt, shape, L, B, cap, 43, old)
+    offs, _ = si.ragged_sequences(lens)
+    offs = offs.cuda()
+    seq = torch.repeat_interleave(torch.arange(B), torch.tensor(lens))
+    pos0 = torch.tensor(old)[seq] + torch.cat([torch.arange(n) for n in lens])
+    xs = [si.hidden_states(shape, T, 43, slot="x_step", extra=i) for i in range(steps)]
+    ctx = qt.Context()
+    qt.qtale_set_exec_ratio(ctx, ratio)
+    stack, kvs = fresh_stack()
+    stack2, kvs2 = fresh_stack()
+    x_buf, pos_buf = torch.zeros_like(xs[0]).cuda(), torch.zeros(T, dtype=torch.int32, device="cuda")
+    graph = qt.StackGraph(ctx, stack2, x_buf, offs, pos_buf)
+    for i in range(steps):
+        x, pos = xs[i].cuda(), (pos0 + 110 * i).to(torch.int32).cuda()
+        x_buf.copy_(x)
+        pos_buf.copy_(pos)
+        qt.qtale_stack_forward(ctx, stack, x, offs, pos)
+        torch.cuda.synchronize()
+        graph.launch()
+        noise = float(torch.randn(4096, device="cuda").square().sum().item())
+        assert noise > 0
+        assert torch.equal(x_buf, x), i
+    for a, b in zip(kvs, kvs2):
+        assert torch.equal(a.kv_len, b.kv_len) and torch.equal(a.k, b.k) and torch.equal(a.v, b.v)
+
+
 def test_graph_prefill_replay_and_rejections(qt):
     shape = si.C1
     L, T = 2, 160
