@@ -14,7 +14,8 @@
 //     its way into LDS.
 //   * decode: one workgroup per (executed row, kv head); lanes stream K and V rows with 16-byte loads,
 //     16 (or 8) lanes per key, online softmax per lane group, merged at the end.  Bandwidth-bound.  It also
-//     rotates the query and the call's own keys (table of the normalising kernel) and appends the new row; with
+//     rotates the query and the call's own keys (table of the normalising kernel) and appends the new row, unless a call
+//     has a long new part (attention_rotates); with
 //     few rows the cached keys are cut into ranges and the workgroup that arrives last combines them.
 #include <algorithm>
 #include <type_traits>

@@ -1,4 +1,5 @@
-// W4A16 / W3A16 / W2A16 GEMM for decode steps (17 to 64 executed rows; wide outputs to 256 in 64-row chunks): C[M][N] = A[M][K] x W'[N][K]^T with the
+// W4A16 / W3A16 / W2A16 GEMM for decode steps (17 to 64 executed rows; some outputs from 9 rows, some to 256 in 64-row chunks: the
+// rules are in gemm_w4a16.hip): C[M][N] = A[M][K] x W'[N][K]^T with the
 // weights streamed once (Sec. 4.1 weights; the rows are the executed tokens gathered per App. B.2).
 //
 // What bounds this shape on gfx950 is not the matrix cores and not HBM alone but how much of each a CU can
