@@ -401,16 +401,25 @@ static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t str
     return launch_gemm_skinny(d, a.epilogue, stream);
 }
 
-// At most kFewRows rows: the outputs whose 16-column groups need a second round of workgroups that is mostly empty.  us, few-row /
-// 17-to-64-row kernel, 12 and 16 rows: store 20480 columns (320 workgroups) K = 4096 18.2 / 17.6, 18.7 / 17.5; 5120 22.8 / 20.2, 23.6 /
-// 20.1; 8192 33.8 / 29.9, 35.6 / 31.6 (8 rows 20.1 / 20.6 at 5120); 32000 (500) 22.6 / 23.5, 23.1 / 23.7; 15360 (240) 16 rows 12.3 / 12.8.
-// Gate/up 14336 (448), 14 and 16 rows: K = 2048 16 rows 10.9 / 12.6; 4096 20.9 / 21.6, 20.9 / 21.2; 5120 23.5 / 24.1, 24.6 / 24.1; 8192
-// 37.4 / 38.8, 38.9 / 36.1; 18944 (592) 4096 16 rows 27.2 / 35.7.
-static bool few_overflows(const GemmDev& d, int epilogue) {
+// Rows up to which the few-row kernel takes an output: kFewRows, less where its 16-column groups need a second round of
+// workgroups that is mostly empty.  us, few-row / 17-to-64-row kernel.  Group 128, 12 and 16 rows: store 20480 columns (320
+// workgroups) K = 4096 18.2 / 17.6, 18.7 / 17.5; 5120 22.8 / 20.2, 23.6 / 20.1; 8192 33.8 / 29.9, 35.6 / 31.6 (8 rows 20.1 / 20.6
+// at 5120); 32000 (500) 22.6 / 23.5, 23.1 / 23.7; 15360 (240) 16 rows 12.3 / 12.8.  Gate/up 14336 (448), 14 and 16 rows: K = 2048
+// 16 rows 10.9 / 12.6; 4096 20.9 / 21.6, 20.9 / 21.2; 5120 23.5 / 24.1, 24.6 / 24.1; 8192 37.4 / 38.8, 38.9 / 36.1; 18944 (592)
+// 4096 16 rows 27.2 / 35.7.  Group 32 (twice the scales per step): gate/up 14336 at 4, 9, 14 rows K = 4096 18.2 / 20.6, 20.8 / 20.7,
+// 22.5 / 20.7 (2 bit 14 rows 16.9 / 18.5), 16384 (512) 12 and 16 rows 22.1 / 24.8, 23.3 / 24.6; 14336 x 8192 33.4 / 34.7,
+// 38.5 / 33.9, 41.7 / 34.7 (2 bit 33.4 / 30.9); store 20480 x 8192 at 2, 4, 8 rows 29.8 / 30.5, 29.4 / 28.1, 31.8 / 27.8 (3 bit
+// 27.8 / 29.2, 27.4 / 27.7, 29.7 / 27.6).
+static int few_rows_limit(const GemmDev& d, int epilogue) {
     const int cus = resident_workgroups(1);
-    if (epilogue == EPI_SWIGLU_F16) return d.M_max > 14 && d.KT >= 80 && d.vf_total > 3 * cus && d.vf_total <= 4 * cus;
+    const bool g32 = d.gshift == 5, long_k = d.KT >= 80;
+    if (epilogue == EPI_SWIGLU_F16 && d.vf_total > 3 * cus && d.vf_total <= 4 * cus) {
+        if (long_k) return !g32 ? 14 : d.bits == 2 ? 12 : 8;
+        if (d.KT >= 48 && g32 && d.bits > 2 && 2 * d.vf_total <= 7 * cus) return d.bits == 4 ? 10 : 13;
+    }
     const int groups = (d.vf_total + 1) / 2;
-    return epilogue == EPI_STORE_F16 && d.M_max > 8 && groups > cus && 2 * groups <= 3 * cus;
+    if (epilogue == EPI_STORE_F16 && groups > cus && 2 * groups <= 3 * cus) return !g32 || !long_k || d.bits == 2 ? 8 : d.bits == 4 ? 2 : 5;
+    return kFewRows;
 }
 
 hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
@@ -446,7 +455,8 @@ hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     // Few rows: the weight stream dominates and 128-row tiles cannot fill the chip.  Each range has a kernel of its own:
     // gemm_few.h, launch_small_rows, launch_mid_rows.
     if (a.n_parts) *a.n_parts = 0;
-    if (d.M_max <= kFewRows && !few_overflows(d, a.epilogue)) return launch_gemm_few(d, a.epilogue, a.pro, resident_workgroups(1), stream);
+    // (a launch that makes its own activations is this kernel's alone)
+    if (d.M_max <= (a.pro ? kFewRows : few_rows_limit(d, a.epilogue))) return launch_gemm_few(d, a.epilogue, a.pro, resident_workgroups(1), stream);
     if (d.M_max <= kGemmPartRows) return launch_small_rows(d, a, true, stream);
     if (d.M_max <= kGemmWideRows) return launch_mid_rows(d, a, stream);
     if (wide_parts(d, a) > 0) return launch_wide_parts(d, a, stream);

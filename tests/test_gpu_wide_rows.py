@@ -70,9 +70,20 @@ def test_few_row_linear_past_one_round(qt, M, N, K):
     test_linear_of_a_hundred_rows(qt, M, N, K, 64, 4)
 
 
-@pytest.mark.parametrize("M", [14, 15, 16])
-def test_few_row_swiglu_past_one_round(qt, M):
-    test_swiglu_of_a_hundred_rows(qt, M, 12304, 5064, 128, 4)
+@pytest.mark.parametrize("M,K,G,bits", [(14, 5064, 128, 4), (15, 5064, 128, 4), (16, 5064, 128, 4), (8, 5064, 32, 4), (9, 5064, 32, 3),
+                                        (13, 5064, 32, 2), (11, 3080, 32, 4), (14, 3080, 32, 3)])
+def test_few_row_swiglu_past_one_round(qt, M, K, G, bits):
+    test_swiglu_of_a_hundred_rows(qt, M, 12304, K, G, bits)
+
+
+@pytest.mark.parametrize("M,bits", [(2, 4), (3, 4), (5, 3), (6, 3), (9, 2)])
+def test_few_row_linear_past_one_round_with_small_groups(qt, M, bits):
+    test_linear_of_a_hundred_rows(qt, M, 20488, 5064, 32, bits)
+
+
+def test_fused_call_of_a_width_past_one_round(qt):
+    # three tokens, 20480 columns of q|k|v, groups of 32: the launch that selects and normalises stays on the few-row kernel
+    _check_layer(qt, si.LayerShape(5120, 160, 80, 64, 64, 4, 32, "bf16"), 3, [2, 1], "ratio", 1.0, seed=77)
 
 
 # hidden 2568: 21 column blocks, two row chunks, the o- and down-proj leave K parts (27 k-tiles with a ragged last one)
