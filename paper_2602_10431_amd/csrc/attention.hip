@@ -801,7 +801,9 @@ bool attention_is_decode(bool cache, int T, int B, int nh, int nkv) {
     return cache && T <= 4 * B && (rep == 1 || rep == 2 || rep == 4 || rep == 8);
 }
 
-bool attention_rotates(int T, int B, int hidden, int head_dim) { return hidden >= head_dim && T - B <= kAttnFuseNew; }
+bool attention_rotates(int T, int B, int rep, int hidden, int head_dim) {
+    return hidden >= head_dim && T - B <= kAttnFuseNew && (rep > 1 || T <= kAttnFuseTokens);
+}
 
 // Few rows: cut the cached keys.  With the ranges' length set on the device they are equally long over all rows and fill the chip
 // once (`target`: what the split kernel's registers let a CU hold); sequences of different lengths cut into equally many

@@ -218,7 +218,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     // Decode-style attention mostly rotates and appends by itself: the first kernels leave it the rows' rotary table (in the
     // buffer of the residual h, which is written after attention) and cleared arrival counters (in the buffer of act).
     const bool decode_attn = attention_is_decode(kv != nullptr, T, B, nh, nkv);
-    const bool attn_rotates = decode_attn && attention_rotates(T, B, H, d);
+    const bool attn_rotates = decode_attn && attention_rotates(T, B, nh / nkv, H, d);
     RowAux aux{};
     if (attn_rotates) {
         aux.cs = reinterpret_cast<float2*>(ws.h); aux.positions = positions; aux.half = d / 2; aux.base = c->rope_base;

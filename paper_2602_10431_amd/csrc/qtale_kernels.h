@@ -202,11 +202,16 @@ constexpr int kAttnSplitMax = 8;      // and into at most this many ranges
 bool attention_is_decode(bool cache, int T, int B, int nh, int nkv);
 // Decode-style calls whose attention kernel also rotates and appends.  (The rows' table lies in the buffer of the residual: head_dim
 // must not exceed hidden.)  The kernel rotates a sequence's new keys again for each of its rows, so a long new part beside many
-// single tokens costs more than the launch that it saves; T - B bounds the longest if no sequence is empty.  Layers on 1000 cached
+// single tokens costs more than the launch that it saves.  T - B bounds the longest new part if no sequence is empty, T if most
+// are (idle slots of a fixed batch).  Layers on 1000 cached
 // keys, us, rotating inside / before: 7B shape 4 x 4 tokens 85.6 / 88.8, 31 x 1 + 65 242.4 / 242.5, 31 x 1 + 97 278 / 273,
 // 63 x 1 + 190 536 / 502, 127 x 1 + 385 1056 / 920; 8B-GQA 32 x 2 141 / 145, 31 x 1 + 97 204 / 206, 63 x 1 + 190 346 / 340.
+// One sequence of 140 / 200 / 256 / 350 tokens beside empty ones, 300 cached keys: 32 heads of 64 (rep 1) 98.6 / 87.2, 122.5 / 97.8, 149 /
+// 110, 227 / 157 (before the fusion 99.8, 113, 128, 177); grouped heads (rep 2 to 8) lose at most 4 to 13 % to the separate launch and
+// were slower before the fusion, so there the pure decode calls decide, which gain 1 to 5 % from it (rep 1, 200 tokens: 2 %).
 constexpr int kAttnFuseNew = 96;
-bool attention_rotates(int T, int B, int hidden, int head_dim);
+constexpr int kAttnFuseTokens = 160;   // one query head per kv head
+bool attention_rotates(int T, int B, int rep, int hidden, int head_dim);
 // Key ranges per (row, kv head) of a decode-style call (1 = not split).  device_chunk: the ranges' length is set on the device
 // (RowAux::chunk) and the result is the bound on their number; target (nullable): workgroups that run at once.
 int attention_splits(int max_rows, int nh, int nkv, int cap, bool device_chunk, int* target);

@@ -131,6 +131,16 @@ def test_decode_attention_after_a_separate_append(qt, rep, d):
     _cache_case(qt, shape, lens, old, old, 641, 530 + rep, 0.5)
 
 
+@pytest.mark.parametrize("B", [160, 161])
+@pytest.mark.parametrize("rep", [1, 2])
+def test_decode_attention_beside_idle_sequences(qt, B, rep):
+    # one long new part and empty sequences around it, at the token count where one query head per kv head changes its route
+    shape = si.LayerShape(256, 2 * rep, 2, 64, 128, 4, 32, "fp16")
+    lens, old = [0] * B, [7] * B
+    lens[3], old[3] = B, 100
+    _cache_case(qt, shape, lens, old, old, 300, 545 + rep, 1.0)
+
+
 @pytest.mark.parametrize("lens,old,cap", [([1, 1, 1], [300, 0, 77], 304), ([2, 0, 3], [63, 5, 700], 704), ([1] * 140, [90] * 140, 96)])
 def test_decode_attention_of_heads_wider_than_the_hidden_size(qt, lens, old, cap):
     # the rotary table has no room in the residual's buffer: the same decode kernel, rotation and append before it
