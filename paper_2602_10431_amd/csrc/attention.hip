@@ -12,7 +12,7 @@
 //     one query column (softmax statistics are per lane), and the probabilities, still in the MFMA
 //     accumulator layout, are fed straight back as the B operand of O^T = V^T P^T; V is transposed on
 //     its way into LDS.
-//   * decode: one workgroup per (executed row, kv head); lanes stream K and V rows with 16-byte loads,
+//   * decode (grouped queries: attention_gqa.hip): one workgroup per (executed row, kv head); lanes stream K and V rows with 16-byte loads,
 //     16 (or 8) lanes per key, online softmax per lane group, merged at the end.  Bandwidth-bound.  It also
 //     rotates the query and the call's own keys (table of the normalising kernel) and appends the new row, unless a call
 //     has a long new part (attention_rotates); with
@@ -20,36 +20,11 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "qtale_dev.h"
-#include "qtale_kernels.h"
+#include "attn_common.h"
 
 namespace qtale {
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kNegBig = -1.0e30f;
-
-struct AttnDev {
-    const half_t* qkv;
-    half_t* out;
-    int nh, nkv, width;          // width = (nh + 2 nkv) * d
-    const int32_t* count;
-    const int32_t* cu_exec;
-    const int32_t* row_seq;
-    const int4* items;           // prefill work list: (sequence or -1, query tile, first compact row, rows) per item
-    const int32_t* n_items;
-    int items_max;               // host bound on the number of work items (row stride of the logical grid)
-    half_t* k_cache;
-    half_t* v_cache;
-    const int32_t* kv_old;
-    int cap;
-    float scale_log2;            // log2(e) / sqrt(d)
-    const float2* cs;            // decode: [row][D / 2] (cos, sin) at the row's position
-    int32_t* arrive;             // decode, split keys: [row][kv head] ranges done so far
-    const int32_t* chunk;        // decode, split keys: cached keys per range (nullable: n_split ranges of equal length per row)
-    float* part;                 // decode, split keys: [row][head][split][D + 2] fp32 (numerators, maximum, denominator)
-    int n_split;                 // key ranges per (row, kv head); 1 = no split
-};
-
 template <int D>
 __global__ void __launch_bounds__(256, 2)
 flash_prefill_kernel(AttnDev p) {
@@ -468,11 +443,7 @@ __device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b) {
     return acc;
 }
 
-// Accesses that are coherent across the XCDs (and with the counter they are used with).
-__device__ __forceinline__ void agent_store(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ __forceinline__ float agent_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// Decode-style attention: workgroup = (executed row, kv head); REP query heads share the kv head.  The kernel also
+// Decode-style attention, one query head per kv head: workgroup = (executed row, head).  The kernel also
 // does what a launch of its own would do before it (rotary embedding and cache append: 5 us per layer for a few KB):
 // the queries are rotated as they are read, the call's own keys (rows row_begin .. i of the same sequence) are rotated
 // from the compact buffer, and the workgroup appends its own row's key and value.  The cached keys are streamed.
@@ -483,8 +454,8 @@ __device__ __forceinline__ float agent_load(const float* p) { return __hip_atomi
 // combines the ranges in range order, so the result does not depend on who that is.
 // FUSED = false: rope_append_kernel has rotated and appended already, the queries are read as they are and all keys from the
 // cache (attention_rotates says when).
-template <int D, int REP, bool SPLIT, bool FUSED>
-__global__ void __launch_bounds__(256, SPLIT ? 1 : REP == 1 ? 8 : 1)
+template <int D, bool SPLIT, bool FUSED>
+__global__ void __launch_bounds__(256, SPLIT ? 1 : 8)
 attn_decode_kernel(AttnDev p) {
     constexpr int LPK = D / 8;            // lanes per key (each lane owns 8 of the D columns)
     constexpr int KPW = 64 / LPK;         // keys per wave per step
@@ -508,14 +479,11 @@ attn_decode_kernel(AttnDev p) {
             out[e] = static_cast<half_t>(fmaf(static_cast<float>(mine[e]), cs[e].x, sign * (static_cast<float>(other[e]) * cs[e].y)));
     };
     const half_t* row_i = p.qkv + static_cast<size_t>(i) * p.width;
-    half8_t qa[REP], qb[REP], ka{}, kb_{}, v_own{};
+    half8_t qa, qb{}, ka{}, kb_{}, v_own{};
     float2 cs_i[8];
-#pragma unroll
-    for (int r = 0; r < REP; ++r) {
-        qa[r] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + r) * D + sub * 8);
-        if (FUSED) qb[r] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + r) * D + psub * 8);
-    }
+    qa = *reinterpret_cast<const half8_t*>(row_i + hk * D + sub * 8);
     if (FUSED) {
+        qb = *reinterpret_cast<const half8_t*>(row_i + hk * D + psub * 8);
         ka = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + sub * 8);
         kb_ = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + psub * 8);
         v_own = *reinterpret_cast<const half8_t*>(row_i + (p.nh + p.nkv + hk) * D + sub * 8);
@@ -536,23 +504,15 @@ attn_decode_kernel(AttnDev p) {
     const int n_new = max(min(own + 1, p.cap - old), 0);         // new keys that fit the cache; later ones are not seen
 
     const int step = 4 * KPW;             // keys per workgroup step
-    int key_lo = 0, key_hi = n_cached;    // this workgroup's range of the cached keys
-    int ranges = 1;                       // ranges of this (row, kv head); the grid holds n_split
-    if (SPLIT) {
-        const int gran = UNR * step;
-        const int per = p.chunk ? *p.chunk : ((n_cached + p.n_split - 1) / p.n_split + gran - 1) / gran * gran;
-        ranges = max((n_cached + per - 1) / max(per, 1), 1);
-        if (static_cast<int>(blockIdx.z) >= ranges) return;
-        key_lo = min(static_cast<int>(blockIdx.z) * per, n_cached);
-        key_hi = min(key_lo + per, n_cached);
-    }
+    const KeyRange range = decode_key_range<SPLIT>(p, n_cached, UNR * step);
+    if (SPLIT && range.none) return;
+    const int key_lo = range.lo, key_hi = range.hi;
     // Keys past the end of the range are clamped to its last one and masked (so the last step's request for the next one does
-    // not read the neighbouring range: half as much again at 128 keys per range).  kAhead: the keys and values of the next step are requested
-    // before the current step is consumed, so the memory pipe never drains while the lanes do their dot products and
-    // exponentials.  One query head per kv head without split keys runs eight workgroups per CU on 64 registers, which do not
-    // hold two steps (asked to, the compiler loaded one row after the other, a round trip each: 16 rows x 32 heads x 1000 keys
-    // 58 us, 4 x 4 rows 44): the step's loads are issued together at its start and the other workgroups fill the wait.
-    constexpr bool kAhead = SPLIT || REP > 1;
+    // not read the neighbouring range: half as much again at 128 keys per range).  With split keys the next step is requested
+    // before the current one is consumed, so the memory pipe never drains while the lanes do their dot products and
+    // exponentials.  Without, eight workgroups per CU run on 64 registers, which do not hold two steps (asked to, the compiler
+    // loaded one row after the other, a round trip each: 16 rows x 32 heads x 1000 keys 58 us, 4 x 4 rows 44): the step's loads
+    // are issued together at its start and the other workgroups fill the wait.
     // Addresses are a uniform base that walks with the step plus a 32-bit lane offset inside it.
     half8_t kn[UNR], vn[UNR];
     const int last = max(key_hi - 1, 0);                         // an empty cache: slot 0, loaded and not used
@@ -579,15 +539,13 @@ attn_decode_kernel(AttnDev p) {
         __builtin_amdgcn_sched_barrier(0);
     }
 
-    half8_t qh[REP], k_own{};
-#pragma unroll
-    for (int r = 0; r < REP; ++r) {
-        if (FUSED) rotate(qa[r], qb[r], cs_i, qh[r]);
-        else qh[r] = qa[r];
+    half8_t qh = qa, k_own{};
+    if (FUSED) {
+        rotate(qa, qb, cs_i, qh);
+        rotate(ka, kb_, cs_i, k_own);
     }
-    if (FUSED) rotate(ka, kb_, cs_i, k_own);
 
-    float m_run[REP], l_run[REP], o[REP][8];
+    float m_run, l_run, o[8];
     // The row's own key starts the sums of one lane group of range 0 (and goes into the cache); the other groups start
     // empty.
     const bool mine = FUSED && (!SPLIT || blockIdx.z == 0) && wave == 0 && slot == 0 && own < n_new;
@@ -596,14 +554,10 @@ attn_decode_kernel(AttnDev p) {
         *reinterpret_cast<half8_t*>(p.k_cache + at) = k_own;
         *reinterpret_cast<half8_t*>(p.v_cache + at) = v_own;
     }
+    m_run = mine ? key_group_sum<LPK>(dot8(qh, k_own)) * p.scale_log2 : kNegBig;
+    l_run = mine ? 1.0f : 0.0f;
 #pragma unroll
-    for (int r = 0; r < REP; ++r) {
-        const float acc = FUSED ? key_group_sum<LPK>(dot8(qh[r], k_own)) * p.scale_log2 : 0.0f;
-        m_run[r] = mine ? acc : kNegBig;
-        l_run[r] = mine ? 1.0f : 0.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[r][e] = mine ? static_cast<float>(v_own[e]) : 0.0f;
-    }
+    for (int e = 0; e < 8; ++e) o[e] = mine ? static_cast<float>(v_own[e]) : 0.0f;
     // the sequence's other new keys (none in a decode step of one token per sequence)
     if (FUSED && own > 0 && (!SPLIT || blockIdx.z == 0)) {
         const int n_other = min(own, n_new);
@@ -621,27 +575,23 @@ attn_decode_kernel(AttnDev p) {
             if (!SPLIT) __builtin_amdgcn_sched_barrier(0);      // one round trip per step
             half8_t kr;
             rotate(ja, jo, cs, kr);
+            const float acc = key_group_sum<LPK>(dot8(qh, kr)) * p.scale_log2;
+            const float s = ok ? acc : kNegBig;
+            const float mx = fmaxf(m_run, s);
+            const float alpha = exp2f(m_run - mx);
+            const float pv = ok ? exp2f(s - mx) : 0.0f;
+            m_run = mx;
+            l_run = l_run * alpha + pv;
 #pragma unroll
-            for (int r = 0; r < REP; ++r) {
-                const float acc = key_group_sum<LPK>(dot8(qh[r], kr)) * p.scale_log2;
-                const float s = ok ? acc : kNegBig;
-                const float mx = fmaxf(m_run[r], s);
-                const float alpha = exp2f(m_run[r] - mx);
-                const float pv = ok ? exp2f(s - mx) : 0.0f;
-                m_run[r] = mx;
-                l_run[r] = l_run[r] * alpha + pv;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[r][e] = fmaf(pv, static_cast<float>(vv[e]), o[r][e] * alpha);
-            }
+            for (int e = 0; e < 8; ++e) o[e] = fmaf(pv, static_cast<float>(vv[e]), o[e] * alpha);
         }
     }
 
-    if (kAhead && !SPLIT) fetch(key_lo);
     for (int kb = key_lo; kb < key_hi; kb += UNR * step) {     // trip count is uniform over the workgroup
         const int k0 = kb + wave * KPW + slot;
         half8_t kv[UNR], vv[UNR];
         bool ok[UNR];
-        if (!kAhead) {
+        if (!SPLIT) {
             fetch(kb);
             __builtin_amdgcn_sched_barrier(0);                  // all eight loads before the first wait
         }
@@ -651,115 +601,72 @@ attn_decode_kernel(AttnDev p) {
             kv[u] = kn[u];
             vv[u] = vn[u];
         }
-        if (kAhead) fetch(kb + UNR * step);                    // past the end: one redundant, unused fetch
+        if (SPLIT) fetch(kb + UNR * step);                     // past the end: one redundant, unused fetch
+        float s[UNR];
+        float mx = m_run;
 #pragma unroll
-        for (int r = 0; r < REP; ++r) {
-            float s[UNR];
-            float mx = m_run[r];
+        for (int u = 0; u < UNR; ++u) {
+            const float acc = key_group_sum<LPK>(dot8(qh, kv[u])) * p.scale_log2;
+            s[u] = ok[u] ? acc : kNegBig;
+            mx = fmaxf(mx, s[u]);
+        }
+        const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
+        m_run = mx;
+        l_run *= alpha;
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const float acc = key_group_sum<LPK>(dot8(qh[r], kv[u])) * p.scale_log2;
-                s[u] = ok[u] ? acc : kNegBig;
-                mx = fmaxf(mx, s[u]);
-            }
-            const float alpha = __builtin_amdgcn_exp2f(m_run[r] - mx);
-            m_run[r] = mx;
-            float lsum = l_run[r] * alpha;
+        for (int e = 0; e < 8; ++e) o[e] *= alpha;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[r][e] *= alpha;
+        for (int u = 0; u < UNR; ++u) {
+            const float pv = ok[u] ? __builtin_amdgcn_exp2f(s[u] - mx) : 0.0f;
+            l_run += pv;
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
-                const float pv = ok[u] ? __builtin_amdgcn_exp2f(s[u] - mx) : 0.0f;
-                lsum += pv;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[r][e] = fmaf(pv, static_cast<float>(vv[u][e]), o[r][e]);
-            }
-            l_run[r] = lsum;
+            for (int e = 0; e < 8; ++e) o[e] = fmaf(pv, static_cast<float>(vv[u][e]), o[e]);
         }
     }
 
     // merge the key slots of a wave (lanes that own the same columns), then the four waves through LDS
-    __shared__ float sm[4][REP][D + 2];
+    __shared__ float sm[4][D + 2];
 #pragma unroll
-    for (int r = 0; r < REP; ++r) {
+    for (int off = LPK; off < 64; off <<= 1) {
+        const float m2 = __shfl_xor(m_run, off, 64);
+        const float l2 = __shfl_xor(l_run, off, 64);
+        const float mn = fmaxf(m_run, m2);
+        const float a1 = exp2f(m_run - mn), a2 = exp2f(m2 - mn);
 #pragma unroll
-        for (int off = LPK; off < 64; off <<= 1) {
-            const float m2 = __shfl_xor(m_run[r], off, 64);
-            const float l2 = __shfl_xor(l_run[r], off, 64);
-            const float mn = fmaxf(m_run[r], m2);
-            const float a1 = exp2f(m_run[r] - mn), a2 = exp2f(m2 - mn);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float o2 = __shfl_xor(o[r][e], off, 64);
-                o[r][e] = o[r][e] * a1 + o2 * a2;
-            }
-            l_run[r] = l_run[r] * a1 + l2 * a2;
-            m_run[r] = mn;
+        for (int e = 0; e < 8; ++e) {
+            const float o2 = __shfl_xor(o[e], off, 64);
+            o[e] = o[e] * a1 + o2 * a2;
         }
-        if (slot == 0) {
+        l_run = l_run * a1 + l2 * a2;
+        m_run = mn;
+    }
+    if (slot == 0) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sm[wave][r][sub * 8 + e] = o[r][e];
-            if (sub == 0) { sm[wave][r][D] = m_run[r]; sm[wave][r][D + 1] = l_run[r]; }
-        }
+        for (int e = 0; e < 8; ++e) sm[wave][sub * 8 + e] = o[e];
+        if (sub == 0) { sm[wave][D] = m_run; sm[wave][D + 1] = l_run; }
     }
     __syncthreads();
-    for (int c = tid; c < REP * D; c += 256) {
-        const int r = c / D, e = c % D;
+    if (tid < D) {
         float mn = kNegBig;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mn = fmaxf(mn, sm[w][r][D]);
+        for (int w = 0; w < 4; ++w) mn = fmaxf(mn, sm[w][D]);
         float num = 0.0f, den = 0.0f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const float a = exp2f(sm[w][r][D] - mn);
-            num += sm[w][r][e] * a;
-            den += sm[w][r][D + 1] * a;
+            const float a = exp2f(sm[w][D] - mn);
+            num += sm[w][tid] * a;
+            den += sm[w][D + 1] * a;
         }
         if (SPLIT) {
             // an empty range leaves num = 0, den = 0 and the maximum at its initial value: it drops out of the merge
-            float* dst = p.part + ((static_cast<size_t>(i) * p.nh + hk * REP + r) * p.n_split + blockIdx.z) * (D + 2);
-            agent_store(dst + e, num);
-            if (e == 0) { agent_store(dst + D, mn); agent_store(dst + D + 1, den); }
+            float* dst = p.part + ((static_cast<size_t>(i) * p.nh + hk) * p.n_split + blockIdx.z) * (D + 2);
+            agent_store(dst + tid, num);
+            if (tid == 0) { agent_store(dst + D, mn); agent_store(dst + D + 1, den); }
         } else {
-            p.out[static_cast<size_t>(i) * (p.nh * D) + (hk * REP + r) * D + e] = static_cast<half_t>(num / den);
+            p.out[static_cast<size_t>(i) * (p.nh * D) + hk * D + tid] = static_cast<half_t>(num / den);
         }
     }
-    if (SPLIT) {
-        // The range that arrives last combines all of them: out = sum_s num_s 2^(m_s - m) / sum_s den_s 2^(m_s - m).  Nobody
-        // waits: a workgroup counts itself in and leaves unless it is the last.  The ranges may have run on different
-        // XCDs, whose L2s are not coherent with each other for plain accesses: the partial sums are written and read with
-        // agent-scope accesses (they go past the L2), and every thread's stores have completed (vmcnt 0, then the barrier)
-        // before thread 0 counts.  A release fence instead would write back a whole L2 per workgroup.
-        __shared__ int s_arrived;
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) s_arrived = __hip_atomic_fetch_add(p.arrive + static_cast<size_t>(i) * p.nkv + hk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (s_arrived != ranges - 1) return;
-        for (int c = tid; c < REP * D; c += 256) {
-            const int r = c / D, e = c % D;
-            const float* src = p.part + (static_cast<size_t>(i) * p.nh + hk * REP + r) * p.n_split * (D + 2);
-            float num_s[kAttnSplitMax], m_s[kAttnSplitMax], den_s[kAttnSplitMax];
-            float mn = kNegBig;
-#pragma unroll
-            for (int s = 0; s < kAttnSplitMax; ++s) {            // all ranges are requested before any is used
-                const float* ps = src + min(s, ranges - 1) * (D + 2);
-                num_s[s] = agent_load(ps + e);
-                m_s[s] = agent_load(ps + D);
-                den_s[s] = agent_load(ps + D + 1);
-            }
-#pragma unroll
-            for (int s = 0; s < kAttnSplitMax; ++s) mn = fmaxf(mn, m_s[s]);
-            float num = 0.0f, den = 0.0f;
-#pragma unroll
-            for (int s = 0; s < kAttnSplitMax; ++s) {
-                const float a = s < ranges ? exp2f(m_s[s] - mn) : 0.0f;
-                num += num_s[s] * a;
-                den += den_s[s] * a;
-            }
-            p.out[static_cast<size_t>(i) * (p.nh * D) + (hk * REP + r) * D + e] = static_cast<half_t>(num / den);
-        }
-    }
+    if (SPLIT) combine_key_ranges<D, 1>(p, i, hk, range.ranges, tid);
 }
 
 // CUs of the current device (queried once per device).
@@ -775,25 +682,13 @@ static int attn_cus() {
     return cus[dev];
 }
 
-template <int D, bool SPLIT, bool FUSED>
-static hipError_t launch_decode_rep(const AttnDev& d, int rep, int rows, int nkv, hipStream_t stream) {
-    const dim3 grid(nkv, rows, SPLIT ? d.n_split : 1), block(256);
-    switch (rep) {
-        case 1: hipLaunchKernelGGL((attn_decode_kernel<D, 1, SPLIT, FUSED>), grid, block, 0, stream, d); break;
-        case 2: hipLaunchKernelGGL((attn_decode_kernel<D, 2, SPLIT, FUSED>), grid, block, 0, stream, d); break;
-        case 4: hipLaunchKernelGGL((attn_decode_kernel<D, 4, SPLIT, FUSED>), grid, block, 0, stream, d); break;
-        case 8: hipLaunchKernelGGL((attn_decode_kernel<D, 8, SPLIT, FUSED>), grid, block, 0, stream, d); break;
-        default: return hipErrorInvalidValue;
-    }
+template <int D, bool FUSED>
+static hipError_t launch_decode_d(const AttnDev& d, int rows, hipStream_t stream) {
+    const bool split = d.n_split > 1;
+    const dim3 grid(d.nkv, rows, split ? d.n_split : 1), block(256);
+    if (split) hipLaunchKernelGGL((attn_decode_kernel<D, true, FUSED>), grid, block, 0, stream, d);
+    else hipLaunchKernelGGL((attn_decode_kernel<D, false, FUSED>), grid, block, 0, stream, d);
     return hipGetLastError();
-}
-
-template <int D>
-static hipError_t launch_decode_d(const AttnDev& d, int rep, int rows, int nkv, hipStream_t stream) {
-    if (!d.cs) return d.n_split <= 1 ? launch_decode_rep<D, false, false>(d, rep, rows, nkv, stream)
-                                     : launch_decode_rep<D, true, false>(d, rep, rows, nkv, stream);
-    return d.n_split <= 1 ? launch_decode_rep<D, false, true>(d, rep, rows, nkv, stream)
-                          : launch_decode_rep<D, true, true>(d, rep, rows, nkv, stream);
 }
 
 bool attention_is_decode(bool cache, int T, int B, int nh, int nkv) {
@@ -842,8 +737,9 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
         d.part = a.partials;
         d.n_split = a.partials && a.arrive ? attention_splits(a.max_rows, a.nh, a.nkv, a.cap, a.chunk != nullptr, nullptr) : 1;
         const int rep = a.nh / a.nkv;
-        return a.d == 128 ? launch_decode_d<128>(d, rep, a.max_rows, a.nkv, stream)
-                          : launch_decode_d<64>(d, rep, a.max_rows, a.nkv, stream);
+        if (rep > 1) return launch_attn_decode_gqa(d, rep, a.d, a.max_rows, stream);
+        if (a.d == 128) return d.cs ? launch_decode_d<128, true>(d, a.max_rows, stream) : launch_decode_d<128, false>(d, a.max_rows, stream);
+        return d.cs ? launch_decode_d<64, true>(d, a.max_rows, stream) : launch_decode_d<64, false>(d, a.max_rows, stream);
     }
     const int items_max = (a.max_rows + kAttnBQ - 1) / kAttnBQ + a.B;
     d.items_max = items_max;

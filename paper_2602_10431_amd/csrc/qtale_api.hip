@@ -232,7 +232,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
             aux.n_arrive = M_max * nkv;
             if (device_chunk) {
                 aux.chunk = ws.scalars + 2;
-                aux.nkv = nkv; aux.gran = d == 128 ? 64 : 128; aux.max_ranges = ranges;
+                aux.nkv = nkv; aux.gran = nh > nkv ? kAttnGqaStep : d == 128 ? 64 : 128; aux.max_ranges = ranges;
             }
         }
     }

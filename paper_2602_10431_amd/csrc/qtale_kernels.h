@@ -199,6 +199,7 @@ struct AttnArgs {
 constexpr int kAttnBQ = 128;   // executed rows per prefill-attention workgroup
 constexpr int kAttnSplitRows = 128;   // decode attention splits the keys only up to this many rows
 constexpr int kAttnSplitMax = 8;      // and into at most this many ranges
+constexpr int kAttnGqaStep = 128;     // grouped queries: keys per step of a workgroup, its ranges are multiples of it
 bool attention_is_decode(bool cache, int T, int B, int nh, int nkv);
 // Decode-style calls whose attention kernel also rotates and appends.  (The rows' table lies in the buffer of the residual: head_dim
 // must not exceed hidden.)  The kernel rotates a sequence's new keys again for each of its rows, so a long new part beside many
