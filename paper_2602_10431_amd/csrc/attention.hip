@@ -528,8 +528,8 @@ attn_decode_kernel(AttnDev p) {
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const uint32_t off = static_cast<uint32_t>(min(lane_key + u * step, last - first) * D + sub * 8) * 2u;
-            kn[u] = *reinterpret_cast<Piece>(reinterpret_cast<Bytes>(ks) + off);
-            vn[u] = *reinterpret_cast<Piece>(reinterpret_cast<Bytes>(vs) + off);
+            kn[u] = stream_load(reinterpret_cast<Piece>(reinterpret_cast<Bytes>(ks) + off));
+            vn[u] = stream_load(reinterpret_cast<Piece>(reinterpret_cast<Bytes>(vs) + off));
         }
     };
     // Few workgroups (SPLIT): latency counts and registers do not, the stream starts before anything else is computed.  Many
