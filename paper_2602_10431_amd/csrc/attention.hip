@@ -25,7 +25,7 @@
 namespace qtale {
 
 constexpr float kLog2e = 1.4426950408889634f;
-template <int D>
+template <int D, bool SPLIT>
 __global__ void __launch_bounds__(256, 2)
 flash_prefill_kernel(AttnDev p) {
     constexpr int KS = D / 16;          // k-steps of the QK^T product
@@ -50,17 +50,25 @@ flash_prefill_kernel(AttnDev p) {
     // heads outermost the long items of the last head started when most of the work was done: about a third of the
     // kernel time at two sequences of 4096 tokens was an idle tail), and the workgroups that run at the same time
     // belong to a few (sequence, head) pairs and similar key ranges, which the L2 serves.
+    // With split keys the whole list repeats per range: the ranges that do not exist (most items have fewer than n_split) end
+    // the grid and do not hold up the others.
+    const int zs = SPLIT ? p.n_split : 1;
     int h, item;
     if ((p.nh & 7) == 0) {
-        const int hx = p.nh >> 3;                                // heads per XCD; gridDim.x = 8 * hx * items_max
+        const int hx = p.nh >> 3;                                // heads per XCD; gridDim.x = 8 * hx * items_max * zs
         const int local = blockIdx.x >> 3;
         item = local / hx;
         h = (blockIdx.x & 7) * hx + (local - item * hx);
     } else {
         const int per_xcd = gridDim.x >> 3;
         const int L = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-        h = L / p.items_max;
-        item = L - h * p.items_max;
+        h = L / (p.items_max * zs);
+        item = L - h * (p.items_max * zs);
+    }
+    int z = 0;
+    if (SPLIT) {
+        z = item / p.items_max;
+        item -= z * p.items_max;
     }
     if (h >= p.nh) return;
     const int4 it = p.items[item];           // one load tells the workgroup everything (unused slots hold -1)
@@ -91,7 +99,16 @@ flash_prefill_kernel(AttnDev p) {
     const int q_cnt = min(kAttnBQ, n_b - q_lo);
     int n_keys = base_len + q_lo + q_cnt;                        // keys visible to the last query
     if (p.k_cache) n_keys = min(n_keys, p.cap);
-    const int n_tiles = (n_keys + 63) / 64;
+    const int all_tiles = (n_keys + 63) / 64;
+    int t_lo = 0, n_tiles = all_tiles;                           // this workgroup's tiles
+    int ranges = 1;
+    if (SPLIT) {
+        const int per = *p.tiles;
+        ranges = (all_tiles + per - 1) / per;
+        if (z >= ranges) return;
+        t_lo = z * per;
+        n_tiles = min(t_lo + per, all_tiles);
+    }
 
     // this lane's query (column of S^T): local index inside the sequence, clamped to a valid row
     const int q_local = q_lo + min(wave * 32 + l32, q_cnt - 1);
@@ -180,15 +197,15 @@ flash_prefill_kernel(AttnDev p) {
     // Tile t+1 is parked in the other LDS buffer and tile t+2 requested before tile t is computed: one barrier per
     // tile, a whole tile time to cover the latency of a fetch, and the staging of one wave overlaps the MFMAs of the
     // others.
-    fetch(0, kregs, vregs);
-    stage(0, kregs, vregs);
-    if (n_tiles > 1) fetch(1, kregs, vregs);
+    fetch(t_lo, kregs, vregs);
+    stage(t_lo & 1, kregs, vregs);
+    if (t_lo + 1 < n_tiles) fetch(t_lo + 1, kregs, vregs);
     __syncthreads();
     // this lane's row of a V^T fragment: row l32, shifted by the row's skew; key group lhi (v_rd0) or 1 - lhi (v_rd1:
     // fragments whose swizzle flips bit 0 of the key group)
     const int v_row = l32 * VSTR + 16 * ((l32 >> 4) & 1);
     const int v_rd0 = v_row + 4 * lhi, v_rd1 = v_row + 4 * (1 - lhi);
-    for (int tile = 0; tile < n_tiles; ++tile) {
+    for (int tile = t_lo; tile < n_tiles; ++tile) {
         if (tile + 1 < n_tiles) stage((tile + 1) & 1, kregs, vregs);
         if (tile + 2 < n_tiles) fetch(tile + 2, kregs, vregs);
         const half_t* Ks = Ks2[tile & 1];
@@ -220,10 +237,10 @@ flash_prefill_kernel(AttnDev p) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int key = key0 + kf * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3);
-                        if (key >= limit) st[kf][r] = kNegBig;
+                        if (key >= limit) st[kf][r] = -INFINITY;   // a range may hold no visible key of this query
                     }
             }
-            float mx = kNegBig;
+            float mx = -INFINITY;
 #pragma unroll
             for (int kf = 0; kf < 2; ++kf)
 #pragma unroll
@@ -246,8 +263,10 @@ flash_prefill_kernel(AttnDev p) {
                     float2_t pv;
                     pv[0] = __builtin_amdgcn_exp2f(fmaf(st[kf][r], sc, -m_new));
                     pv[1] = __builtin_amdgcn_exp2f(fmaf(st[kf][r + 1], sc, -m_new));
-                    psum += pv[0] + pv[1];
                     const half2_t ph = __builtin_convertvector(pv, half2_t);   // one packed conversion per pair
+                    // the denominator adds the probabilities as the product sees them: their rounding cancels where one key
+                    // dominates, and a pair costs one instruction
+                    psum = __builtin_amdgcn_fdot2(ph, half2_t{static_cast<half_t>(1.0f), static_cast<half_t>(1.0f)}, psum, false);
                     pf[kf * 2 + (r >> 3)][r & 7] = ph[0];
                     pf[kf * 2 + (r >> 3)][(r & 7) + 1] = ph[1];
                 }
@@ -285,7 +304,52 @@ flash_prefill_kernel(AttnDev p) {
         __syncthreads();
     }
 
-    const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    float l_tot = l_run + __shfl_xor(l_run, 32, 64);
+    if (SPLIT && ranges > 1) {
+        // This range's sums go to memory (rules of access as for the decode kernels' key ranges), two values of a lane at a
+        // time; the range that arrives last adds all of them in range order, its own from memory too, and goes on.
+        __shared__ int s_arrived;
+        constexpr int PAIRS = DF * 8 + 1;                        // pairs per lane; the last one is (reference point, denominator)
+        const size_t slot = static_cast<size_t>(item) * p.nh + h;
+        uint64_t* mine = reinterpret_cast<uint64_t*>(p.part) + ((slot * zs + z) * 4 + wave) * (PAIRS * 64) + lane;
+        auto put = [&](int at, float a, float c) {
+            __hip_atomic_store(mine + at * 64, static_cast<uint64_t>(__float_as_uint(a)) | (static_cast<uint64_t>(__float_as_uint(c)) << 32),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+#pragma unroll
+        for (int df = 0; df < DF; ++df)
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) put(df * 8 + (r >> 1), o[df][r], o[df][r + 1]);
+        put(PAIRS - 1, m_run, l_tot);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) s_arrived = __hip_atomic_fetch_add(p.arrive + slot, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (s_arrived != ranges - 1) return;
+        const uint64_t* first = reinterpret_cast<const uint64_t*>(p.part) + (slot * zs * 4 + wave) * (PAIRS * 64) + lane;
+        auto get = [&](int s, int at) { return __hip_atomic_load(first + static_cast<size_t>(s) * (4 * PAIRS * 64) + at * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        m_run = kNegBig;
+        l_tot = 0.0f;
+#pragma unroll
+        for (int df = 0; df < DF; ++df)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[df][r] = 0.0f;
+        for (int s = 0; s < ranges; ++s) {
+            uint64_t v[PAIRS];
+#pragma unroll
+            for (int at = 0; at < PAIRS; ++at) v[at] = get(s, at);
+            const float m_s = __uint_as_float(static_cast<uint32_t>(v[PAIRS - 1])), l_s = __uint_as_float(static_cast<uint32_t>(v[PAIRS - 1] >> 32));
+            const float m_new = fmaxf(m_run, m_s);
+            const float a = __builtin_amdgcn_exp2f(m_run - m_new), c = __builtin_amdgcn_exp2f(m_s - m_new);
+            m_run = m_new;
+            l_tot = l_tot * a + l_s * c;
+#pragma unroll
+            for (int df = 0; df < DF; ++df)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    o[df][r] = o[df][r] * a + __uint_as_float(static_cast<uint32_t>(v[df * 8 + (r >> 1)] >> (32 * (r & 1)))) * c;
+        }
+    }
     const float inv = 1.0f / l_tot;
     if (wave * 32 + l32 < q_cnt) {
         half_t* orow = p.out + static_cast<size_t>(row_begin + q_local) * (p.nh * D) + h * D;
@@ -299,116 +363,6 @@ flash_prefill_kernel(AttnDev p) {
                 *reinterpret_cast<half4_t*>(orow + df * 32 + 8 * g + 4 * lhi) = v;
             }
     }
-}
-
-// Builds the prefill work list: one item per (sequence, tile of kAttnBQ executed rows), carrying the sequence's
-// first compact row and row count so that the attention workgroups need no further lookups; the slots up to
-// items_max that no tile uses are marked with sequence -1.  The list is sorted by query tile index, highest
-// first, across all sequences (the tile index is the item's length in keys up to the cached prefix): a counting
-// sort over the tiles-per-sequence histogram.  `levels` is the host bound on tiles per sequence (<= kItemLevels).
-constexpr int kItemLevels = 1024;
-
-__global__ void __launch_bounds__(256)
-attn_items_kernel(const int32_t* __restrict__ cu_exec, int B, int4* __restrict__ items, int items_max,
-                  int32_t* __restrict__ n_items, int levels) {
-    __shared__ int cnt[kItemLevels + 1];      // first: sequences with exactly n tiles; then: sequences with more than n
-    __shared__ int offs[kItemLevels + 1];     // items of the tile indices above q
-    __shared__ int fill[kItemLevels + 1];
-    __shared__ int s_total;
-    const int tid = threadIdx.x, lane = tid & 63;
-    for (int i = tid; i <= levels; i += 256) { cnt[i] = 0; fill[i] = 0; }
-    __syncthreads();
-    for (int b = tid; b < B; b += 256) {
-        const int nt = min((cu_exec[b + 1] - cu_exec[b] + kAttnBQ - 1) / kAttnBQ, levels);
-        atomicAdd(&cnt[nt], 1);
-    }
-    __syncthreads();
-    if (tid < 64) {
-        // two suffix sums over the levels, one wave: lane l owns a chunk of consecutive levels
-        const int chunk = (levels + 64) / 64;
-        const int lo = lane * chunk, hi = min(lo + chunk, levels + 1);
-        int own = 0;
-        for (int n = lo; n < hi; ++n) own += cnt[n];
-        int above = 0;                                           // sum of the chunks of the lanes above
-        {
-            int incl = own;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_down(incl, o, 64);
-                if (lane + o < 64) incl += t;
-            }
-            above = incl - own;
-        }
-        int own2 = 0;
-        for (int n = hi - 1; n >= lo; --n) {
-            const int h = cnt[n];
-            cnt[n] = above;                                      // sequences with more than n tiles
-            own2 += above;
-            above += h;
-        }
-        int above2 = 0;
-        {
-            int incl = own2;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_down(incl, o, 64);
-                if (lane + o < 64) incl += t;
-            }
-            above2 = incl - own2;
-        }
-        for (int n = hi - 1; n >= lo; --n) {
-            offs[n] = above2;                                    // items with a tile index above n
-            above2 += cnt[n];
-        }
-        if (lane == 0) s_total = above2;                         // lane 0 ends below level 0: all items
-    }
-    __syncthreads();
-    for (int b = tid; b < B; b += 256) {
-        const int first = cu_exec[b];
-        const int rows = cu_exec[b + 1] - first;
-        const int nt = min((rows + kAttnBQ - 1) / kAttnBQ, levels);
-        if (nt == 0) continue;
-        const int pos = cnt[nt] + atomicAdd(&fill[nt], 1);        // place among the sequences, most tiles first
-        for (int q = 0; q < nt; ++q) items[offs[q] + pos] = make_int4(b, q, first, rows);
-    }
-    const int used = s_total;
-    for (int i = used + tid; i < items_max; i += 256) items[i] = make_int4(-1, 0, 0, 0);
-    if (tid == 0) *n_items = used;
-}
-
-// The same list for calls whose sequences could have more than kItemLevels query tiles: sequence by sequence, each
-// sequence's tiles longest first.
-__global__ void __launch_bounds__(256)
-attn_items_by_sequence_kernel(const int32_t* __restrict__ cu_exec, int B, int4* __restrict__ items, int items_max,
-                              int32_t* __restrict__ n_items) {
-    __shared__ int s_wave[4];
-    __shared__ int s_base;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (threadIdx.x == 0) s_base = 0;
-    __syncthreads();
-    for (int b0 = 0; b0 < B; b0 += 256) {
-        const int b = b0 + threadIdx.x;
-        const int first = b < B ? cu_exec[b] : 0;
-        const int rows = b < B ? cu_exec[b + 1] - first : 0;
-        const int nt = (rows + kAttnBQ - 1) / kAttnBQ;
-        int incl = nt;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int t = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += t;
-        }
-        if (lane == 63) s_wave[wave] = incl;
-        __syncthreads();
-        int start = s_base + incl - nt;
-        for (int w = 0; w < wave; ++w) start += s_wave[w];
-        for (int q = 0; q < nt; ++q) items[start + q] = make_int4(b, nt - 1 - q, first, rows);   // longest tiles first
-        __syncthreads();
-        if (threadIdx.x == 0) s_base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-        __syncthreads();
-    }
-    const int used = s_base;
-    for (int i = used + threadIdx.x; i < items_max; i += 256) items[i] = make_int4(-1, 0, 0, 0);
-    if (threadIdx.x == 0) *n_items = used;
 }
 
 // Sum over the LPK (8 or 16) adjacent lanes that share a key, left in every one of them.  Data-parallel-primitive
@@ -712,6 +666,26 @@ int attention_splits(int max_rows, int nh, int nkv, int cap, bool device_chunk, 
     return std::max(1, device_chunk ? most : std::min(most, (4 * attn_cus() + wgs - 1) / wgs));
 }
 
+size_t attention_prefill_floats(int items_max, int nh, int d) {
+    return static_cast<size_t>(items_max) * nh * (4 * 64 * (d / 2 + 2));
+}
+
+AttnList attention_prefill_plan(int max_rows, int B, int nh, int d, int max_keys, size_t floats) {
+    AttnList l{};
+    l.B = B;
+    l.items_max = static_cast<int>((static_cast<long>(max_rows) + static_cast<long>(kAttnBQ - 1) * B) / kAttnBQ);   // sum of the sequences' tiles, each rounded up
+    l.levels = (max_rows + kAttnBQ - 1) / kAttnBQ;
+    l.heads = nh;
+    l.target = attn_cus() * (d == 64 ? 3 : 2);
+    // no more ranges than the scratch holds, than the longest sequence has tiles for, or than fill the chip (a workgroup whose
+    // range does not exist costs its launch: 8 x 84 rows on 300 keys with 16 ranges in the grid 173 -> 179 us)
+    const long pairs = static_cast<long>(l.items_max) * nh;
+    const size_t room = floats / std::max<size_t>(attention_prefill_floats(l.items_max, nh, d), 1);
+    const long wanted = std::min<long>({kAttnTileSplitMax, (static_cast<long>(max_keys) + 64 * kAttnTileRange - 1) / (64 * kAttnTileRange), l.target / std::max(pairs, 1l) + 1});
+    l.n_split = 2l * l.levels * nh >= l.target ? 1 : static_cast<int>(std::max<size_t>(std::min<size_t>(wanted, room), 1));
+    return l;
+}
+
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
     if (a.max_rows == 0) return hipSuccess;
     AttnDev d{};
@@ -723,8 +697,6 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
     d.count = a.count;
     d.cu_exec = a.cu_exec;
     d.row_seq = a.row_seq;
-    d.items = reinterpret_cast<const int4*>(a.items);
-    d.n_items = a.n_items;
     d.k_cache = reinterpret_cast<half_t*>(a.k_cache);
     d.v_cache = reinterpret_cast<half_t*>(a.v_cache);
     d.kv_old = a.kv_old;
@@ -741,22 +713,20 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
         if (a.d == 128) return d.cs ? launch_decode_d<128, true>(d, a.max_rows, stream) : launch_decode_d<128, false>(d, a.max_rows, stream);
         return d.cs ? launch_decode_d<64, true>(d, a.max_rows, stream) : launch_decode_d<64, false>(d, a.max_rows, stream);
     }
-    const int items_max = (a.max_rows + kAttnBQ - 1) / kAttnBQ + a.B;
-    d.items_max = items_max;
-    const int levels = (a.max_rows + kAttnBQ - 1) / kAttnBQ;
-    if (levels <= kItemLevels)
-        hipLaunchKernelGGL(attn_items_kernel, dim3(1), dim3(256), 0, stream, a.cu_exec, a.B,
-                           reinterpret_cast<int4*>(a.items), items_max, a.n_items, levels);
-    else
-        hipLaunchKernelGGL(attn_items_by_sequence_kernel, dim3(1), dim3(256), 0, stream, a.cu_exec, a.B,
-                           reinterpret_cast<int4*>(a.items), items_max, a.n_items);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const dim3 grid(8 * ((items_max * a.nh + 7) / 8)), block(256);
-    if (a.d == 128)
-        hipLaunchKernelGGL(flash_prefill_kernel<128>, grid, block, 0, stream, d);
-    else
-        hipLaunchKernelGGL(flash_prefill_kernel<64>, grid, block, 0, stream, d);
+    d.items = reinterpret_cast<const int4*>(a.list->items);
+    d.items_max = a.list->items_max;
+    d.n_split = a.list->n_split;
+    d.tiles = a.list->tiles;
+    d.arrive = a.list->arrive;
+    d.part = a.partials;
+    const dim3 grid(8 * ((d.items_max * d.n_split * a.nh + 7) / 8)), block(256);
+    if (a.d == 128) {
+        if (d.n_split > 1) hipLaunchKernelGGL((flash_prefill_kernel<128, true>), grid, block, 0, stream, d);
+        else hipLaunchKernelGGL((flash_prefill_kernel<128, false>), grid, block, 0, stream, d);
+    } else {
+        if (d.n_split > 1) hipLaunchKernelGGL((flash_prefill_kernel<64, true>), grid, block, 0, stream, d);
+        else hipLaunchKernelGGL((flash_prefill_kernel<64, false>), grid, block, 0, stream, d);
+    }
     return hipGetLastError();
 }
 

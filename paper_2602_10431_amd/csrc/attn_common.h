@@ -16,18 +16,18 @@ struct AttnDev {
     const int32_t* cu_exec;
     const int32_t* row_seq;
     const int4* items;           // prefill work list: (sequence or -1, query tile, first compact row, rows) per item
-    const int32_t* n_items;
     int items_max;               // host bound on the number of work items (row stride of the logical grid)
+    const int32_t* tiles;        // prefill, split keys: key tiles per range
     half_t* k_cache;
     half_t* v_cache;
     const int32_t* kv_old;
     int cap;
     float scale_log2;            // log2(e) / sqrt(d)
     const float2* cs;            // decode: [row][D / 2] (cos, sin) at the row's position
-    int32_t* arrive;             // decode, split keys: [row][kv head] ranges done so far
+    int32_t* arrive;             // split keys: ranges done so far, [row][kv head] or (prefill) [item][head]
     const int32_t* chunk;        // decode, split keys: cached keys per range (nullable: n_split ranges of equal length per row)
-    float* part;                 // decode, split keys: [row][head][split][D + 2] fp32 (numerators, reference point, denominator)
-    int n_split;                 // key ranges per (row, kv head); 1 = no split
+    float* part;                 // split keys, decode: [row][head][split][D + 2] fp32 (numerators, reference point, denominator)
+    int n_split;                 // bound on the key ranges per (row, kv head) or item; 1 = no split
 };
 
 // Accesses that are coherent across the XCDs (and with the counter they are used with).
@@ -90,6 +90,140 @@ __device__ __forceinline__ void combine_key_ranges(const AttnDev& p, int i, int 
             den += den_s[s] * a;
         }
         p.out[static_cast<size_t>(i) * (p.nh * D) + (hk * REP + r) * D + e] = static_cast<half_t>(num / den);
+    }
+}
+
+// The prefill work list (AttnList), built by 256 threads: one item per (sequence, tile of kAttnBQ executed rows), carrying the
+// sequence's first compact row and row count so that the attention workgroups need no further lookups.  The list is sorted by query tile index, highest
+// first, across all sequences (the tile index is the item's length in keys up to the cached prefix): a counting
+// sort over the tiles-per-sequence histogram.  `levels` is the host bound on tiles per sequence (<= kItemLevels).
+constexpr int kItemLevels = 1024;
+
+__device__ __forceinline__ int attn_build_sorted(const AttnList& a, int4* __restrict__ items) {
+    __shared__ int cnt[kItemLevels + 1];      // first: sequences with exactly n tiles; then: sequences with more than n
+    __shared__ int offs[kItemLevels + 1];     // items of the tile indices above q
+    __shared__ int fill[kItemLevels + 1];
+    __shared__ int s_total;
+    const int tid = threadIdx.x, lane = tid & 63, levels = a.levels;
+    for (int i = tid; i <= levels; i += 256) { cnt[i] = 0; fill[i] = 0; }
+    __syncthreads();
+    for (int b = tid; b < a.B; b += 256) {
+        const int nt = min((a.cu_exec[b + 1] - a.cu_exec[b] + kAttnBQ - 1) / kAttnBQ, levels);
+        atomicAdd(&cnt[nt], 1);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        // two suffix sums over the levels, one wave: lane l owns a chunk of consecutive levels
+        const int chunk = (levels + 64) / 64;
+        const int lo = lane * chunk, hi = min(lo + chunk, levels + 1);
+        int own = 0;
+        for (int n = lo; n < hi; ++n) own += cnt[n];
+        int above = 0;                                           // sum of the chunks of the lanes above
+        {
+            int incl = own;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_down(incl, o, 64);
+                if (lane + o < 64) incl += t;
+            }
+            above = incl - own;
+        }
+        int own2 = 0;
+        for (int n = hi - 1; n >= lo; --n) {
+            const int h = cnt[n];
+            cnt[n] = above;                                      // sequences with more than n tiles
+            own2 += above;
+            above += h;
+        }
+        int above2 = 0;
+        {
+            int incl = own2;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int t = __shfl_down(incl, o, 64);
+                if (lane + o < 64) incl += t;
+            }
+            above2 = incl - own2;
+        }
+        for (int n = hi - 1; n >= lo; --n) {
+            offs[n] = above2;                                    // items with a tile index above n
+            above2 += cnt[n];
+        }
+        if (lane == 0) s_total = above2;                         // lane 0 ends below level 0: all items
+    }
+    __syncthreads();
+    for (int b = tid; b < a.B; b += 256) {
+        const int first = a.cu_exec[b];
+        const int rows = a.cu_exec[b + 1] - first;
+        const int nt = min((rows + kAttnBQ - 1) / kAttnBQ, levels);
+        if (nt == 0) continue;
+        const int pos = cnt[nt] + atomicAdd(&fill[nt], 1);        // place among the sequences, most tiles first
+        for (int q = 0; q < nt; ++q) items[offs[q] + pos] = make_int4(b, q, first, rows);
+    }
+    return s_total;
+}
+
+// The same list for calls whose sequences could have more than kItemLevels query tiles: sequence by sequence, each
+// sequence's tiles longest first.
+__device__ __forceinline__ int attn_build_by_sequence(const AttnList& a, int4* __restrict__ items) {
+    __shared__ int s_wave[4];
+    __shared__ int s_base;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) s_base = 0;
+    __syncthreads();
+    for (int b0 = 0; b0 < a.B; b0 += 256) {
+        const int b = b0 + threadIdx.x;
+        const int first = b < a.B ? a.cu_exec[b] : 0;
+        const int rows = b < a.B ? a.cu_exec[b + 1] - first : 0;
+        const int nt = (rows + kAttnBQ - 1) / kAttnBQ;
+        int incl = nt;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int t = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += t;
+        }
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        int start = s_base + incl - nt;
+        for (int w = 0; w < wave; ++w) start += s_wave[w];
+        for (int q = 0; q < nt; ++q) items[start + q] = make_int4(b, nt - 1 - q, first, rows);   // longest tiles first
+        __syncthreads();
+        if (threadIdx.x == 0) s_base += s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
+        __syncthreads();
+    }
+    return s_base;
+}
+
+
+// List, length of the key ranges and cleared counters, by one workgroup of 256 threads.  A launch of its own for this took 4.6 us
+// of every prefill call.
+__device__ __forceinline__ void attn_build_list(const AttnList& a) {
+    __shared__ int s_tiles, s_longest;
+    int4* items = reinterpret_cast<int4*>(a.items);
+    if (threadIdx.x == 0) { s_tiles = 0; s_longest = 0; }
+    const int used = a.levels <= kItemLevels ? attn_build_sorted(a, items) : attn_build_by_sequence(a, items);
+    for (int i = used + threadIdx.x; i < a.items_max; i += 256) items[i] = make_int4(-1, 0, 0, 0);   // unused slots
+    if (a.n_split <= 1) return;
+    for (int i = threadIdx.x; i < a.items_max * a.heads; i += 256) a.arrive[i] = 0;
+    __syncthreads();
+    // key tiles of all items, and of the longest
+    int tiles = 0, longest = 0;
+    for (int b = threadIdx.x; b < a.B; b += 256) {
+        const int rows = a.cu_exec[b + 1] - a.cu_exec[b], old = a.kv_old ? a.kv_old[b] : 0;
+        for (int q = 0; q < rows; q += kAttnBQ) {
+            const int keys = old + min(q + kAttnBQ, rows);
+            const int n = ((a.kv_old ? min(keys, a.cap) : keys) + 63) / 64;
+            tiles += n;
+            longest = max(longest, n);
+        }
+    }
+    atomicAdd(&s_tiles, tiles);
+    atomicMax(&s_longest, longest);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int fill = static_cast<int>((static_cast<long>(s_tiles) * a.heads + a.target - 1) / a.target);   // the ranges fill the chip once
+        const bool cut = 2l * used * a.heads < a.target;
+        *a.tiles = cut ? max(max(fill, (s_longest + a.n_split - 1) / a.n_split), kAttnTileRange) : max(s_longest, 1);
     }
 }
 

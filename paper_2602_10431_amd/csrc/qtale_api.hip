@@ -38,7 +38,7 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 struct Workspace {
     float* z;
     int32_t* idx;
-    int32_t* scalars;      // [0] count, [1] n_items, [2] keys per range of decode attention
+    int32_t* scalars;      // [0] count, [2] keys (decode) or key tiles (prefill) per range of attention
     int32_t* cu_exec;
     int32_t* row_seq;
     int32_t* kv_old;
@@ -295,13 +295,26 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         Prof pr(ctx, stream, 3);
         HIP_TRY(launch_gemm_w4a16(qg, stream));
     }
+    // Prefill attention: the work list comes from the launch before it, the partial sums of key ranges go to what lies free until
+    // the o-proj: the buffers from h to the parts of the GEMMs, which adjoin (the ranges' counters first)
+    AttnList list{};
+    float* a_part = ws.attn_part;
+    if (!decode_attn) {
+        const size_t counters = align_up((static_cast<size_t>(M_max) / kAttnBQ + B + 1) * nh * 4, 256);
+        const size_t room = static_cast<size_t>(reinterpret_cast<char*>(ws.inv) - reinterpret_cast<char*>(ws.h));
+        list = attention_prefill_plan(M_max, B, nh, d, kv ? kv->cap : M_max, room > counters ? (room - counters) / 4 : 0);
+        list.cu_exec = ws.cu_exec; list.items = ws.items; list.tiles = ws.scalars + 2;
+        if (kv) { list.kv_old = ws.kv_old; list.cap = kv->cap; }
+        list.arrive = reinterpret_cast<int32_t*>(ws.h);
+        a_part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws.h) + counters);
+    }
     if (!attn_rotates) {
         Prof pr(ctx, stream, 4);
         RopeArgs r{};
         r.qkv = ws.qkv; r.nh = nh; r.nkv = nkv; r.d = d; r.base = c->rope_base;
         r.idx = ws.idx; r.positions = positions; r.count = count; r.max_rows = M_max;
         if (kv) { r.k_cache = kv->k_cache; r.v_cache = kv->v_cache; r.cap = kv->cap; }
-        r.row_seq = ws.row_seq; r.cu_exec = ws.cu_exec; r.kv_old = ws.kv_old;
+        r.row_seq = ws.row_seq; r.cu_exec = ws.cu_exec; r.kv_old = ws.kv_old; r.list = list;
         HIP_TRY(launch_rope_append(r, stream));
     }
     {
@@ -310,7 +323,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
         a.qkv = ws.qkv; a.out = ws.attn; a.nh = nh; a.nkv = nkv; a.d = d; a.count = count; a.max_rows = M_max;
         a.B = B; a.cu_exec = ws.cu_exec; a.row_seq = ws.row_seq;
         if (kv) { a.k_cache = kv->k_cache; a.v_cache = kv->v_cache; a.cap = kv->cap; }
-        a.kv_old = ws.kv_old; a.T = T; a.items = ws.items; a.n_items = ws.scalars + 1; a.partials = ws.attn_part;
+        a.kv_old = ws.kv_old; a.T = T; a.list = &list; a.partials = a_part;
         a.decode = decode_attn; a.cs = aux.cs; a.arrive = aux.arrive; a.chunk = aux.chunk;
         HIP_TRY(launch_attention(a, stream));
     }

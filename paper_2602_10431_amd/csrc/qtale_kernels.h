@@ -89,6 +89,23 @@ hipError_t launch_gather_rmsnorm(const void* x, int bf16, int H, const int32_t* 
 hipError_t launch_rmsnorm_f32(const float* h, int H, const int32_t* count, int max_rows, const void* gain,
                               int gain_bf16, float eps, void* out_f16, hipStream_t stream);
 
+// Work list of the prefill attention kernel, built by one workgroup of the launch before it (launch_rope_append): one item per
+// (sequence, tile of kAttnBQ executed rows), {sequence or -1, query tile, first compact row, rows}, longest first.  The keys of
+// an item may be cut into ranges (attention_prefill_plan).
+struct AttnList {
+    const int32_t* cu_exec;    // [B+1]; null: no list is wanted
+    int B;
+    void* items;               // [items_max] x int4, 16-byte aligned
+    int items_max;             // host bound on the number of items
+    int levels;                // host bound on the query tiles of a sequence
+    const int32_t* kv_old;     // [B] cached keys of each sequence (null without a cache)
+    int cap;
+    int heads, target;         // query heads, workgroups that run at once
+    int n_split;               // bound on the key ranges of an item; 1: not cut, the rest is unused
+    int32_t* tiles;            // out: key tiles per range
+    int32_t* arrive;           // [items_max x heads] counters to clear
+};
+
 struct RopeArgs {
     void* qkv;                 // [rows][(nh+2nkv)*d] fp16, q and k rotated in place
     int nh, nkv, d;
@@ -100,6 +117,7 @@ struct RopeArgs {
     // optional cache append
     void* k_cache; void* v_cache; int cap;
     const int32_t* row_seq; const int32_t* cu_exec; const int32_t* kv_old;
+    AttnList list;             // cu_exec null: attention needs no list
 };
 hipError_t launch_rope_append(const RopeArgs& a, hipStream_t stream);
 
@@ -185,18 +203,29 @@ struct AttnArgs {
     void* k_cache; void* v_cache; int cap;
     const int32_t* kv_old;     // [B]
     int T;                     // tokens in the call
-    void* items;               // scratch: (max_rows / kAttnBQ + B + 1) x int4 work list of the prefill kernel, 16-byte aligned
-    int32_t* n_items;          // scratch [1]
+    const AttnList* list;      // prefill: what launch_rope_append has built
     bool decode;               // attention_is_decode: one workgroup per (row, kv head)
     // of those, the calls that attention_rotates names: q and k of the new rows arrive unrotated, the kernel rotates them
     // with this table (RowAux) and appends the new keys and values to the cache.  Else null, launch_rope_append came before.
     const float2* cs;
-    const int32_t* chunk;      // nullable: keys per range (RowAux, only with cs); else every row is cut into equally many ranges
-    int32_t* arrive;           // nullable: max_rows x nkv zeroed counters (RowAux); without them keys are not split
-    float* partials;           // scratch (nullable): min(max_rows, kAttnSplitRows) x nh x kAttnSplitMax x (d + 2) fp32,
-                               // lets the decode kernel cut long caches into key ranges when there are few rows
+    const int32_t* chunk;      // decode, nullable: keys per range (RowAux, only with cs); else every row is cut into equally many ranges
+    int32_t* arrive;           // decode, nullable: max_rows x nkv zeroed counters (RowAux); without them keys are not split
+    float* partials;           // scratch (nullable) of the key ranges.  Decode: min(max_rows, kAttnSplitRows) x nh x kAttnSplitMax x
+                               // (d + 2) fp32; prefill: attention_prefill_floats() per range
 };
 constexpr int kAttnBQ = 128;   // executed rows per prefill-attention workgroup
+// Prefill: items_max, levels, heads, target and n_split of the list for a call of at most max_rows executed rows in B sequences
+// whose longest has at most max_keys keys; `floats` is the scratch that the partial sums may take (attention_prefill_floats per
+// range).  Keys are cut where the (query tile, head) pairs are fewer than half of the workgroups that run at once, into ranges of
+// at least kAttnTileRange tiles of 64 keys: a range's sums are 34 or 68 KB that go past the L2 and back.  Layers, us, not cut / cut
+// into ranges that fill the chip: 100 rows on 2000 keys, 32 heads of 128 197 / 155, of 64 109 / 84; 300 rows on 3000 keys 322 /
+// 263; 2 x 560 rows on 1400 keys, heads of 64 (320 pairs for 768 slots) 280 / 258; but 1200 rows on 1000 keys, heads of 128 (320
+// for 512) 722 / 732, heads of 64 (512 for 768) 307 / 311; ranges of at least 4, 8 and 12 tiles: 1000 rows of the 7B shape (8
+// tiles at most) 317, 315, 316, 100 rows on 2000 keys 155, 157, 162, without a bound the former loses 14.
+AttnList attention_prefill_plan(int max_rows, int B, int nh, int d, int max_keys, size_t floats);
+size_t attention_prefill_floats(int items_max, int nh, int d);
+constexpr int kAttnTileRange = 8;
+constexpr int kAttnTileSplitMax = 16;   // key ranges per item
 constexpr int kAttnSplitRows = 128;   // decode attention splits the keys only up to this many rows
 constexpr int kAttnSplitMax = 8;      // and into at most this many ranges
 constexpr int kAttnGqaStep = 128;     // grouped queries: keys per step of a workgroup, its ranges are multiples of it

@@ -3,6 +3,7 @@
 // All are bandwidth-bound: 16-byte loads, one workgroup per row, fp32 reductions.
 #include "qtale_dev.h"
 #include "qtale_kernels.h"
+#include "attn_common.h"
 #include "row_aux.h"
 
 namespace qtale {
@@ -301,12 +302,29 @@ hipError_t launch_reduce_scatter(const float* part, int n_parts, const float* h,
 __global__ void __launch_bounds__(256)
 rope_append_kernel(RopeArgs a) {
     __shared__ float cs[64], sn[64];              // head_dim <= 128
-    const int i = blockIdx.x;
+    const int extra = a.list.cu_exec ? 1 : 0;     // the first workgroup builds the list of the attention kernel
+    if (static_cast<int>(blockIdx.x) < extra) {
+        attn_build_list(a.list);
+        return;
+    }
+    const int i = blockIdx.x - extra;
     if (i >= *a.count) return;
     const int t = a.idx[i];
     const int d = a.d, half = d >> 1;
     const int width = (a.nh + 2 * a.nkv) * d;
     half_t* row = reinterpret_cast<half_t*>(a.qkv) + static_cast<size_t>(i) * width;
+    const int cph = half >> 3;                     // 8-pair chunks per head
+    const int items = (a.nh + a.nkv) * cph;
+    // the thread's first chunks are requested before the angles are evaluated
+    constexpr int KEEP = 2;
+    half8_t lo[KEEP], hi[KEEP];
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u) {
+        const int w = min(static_cast<int>(threadIdx.x) + u * 256, items - 1);
+        const half_t* hp = row + static_cast<size_t>(w / cph) * d + (w % cph) * 8;
+        lo[u] = *reinterpret_cast<const half8_t*>(hp);
+        hi[u] = *reinterpret_cast<const half8_t*>(hp + half);
+    }
     // cache layout [B][n_kv_heads][cap][d]: entry (b, head, slot) starts at ((b * nkv + head) * cap + slot) * d
     half_t* kdst = nullptr;                       // entry (b, head 0, slot); heads are head_step halves apart
     half_t* vdst = nullptr;
@@ -329,13 +347,9 @@ rope_append_kernel(RopeArgs a) {
         sn[p] = static_cast<float>(s);
     }
     __syncthreads();
-    const int cph = half >> 3;                     // 8-pair chunks per head
-    const int items = (a.nh + a.nkv) * cph;
-    for (int w = threadIdx.x; w < items; w += blockDim.x) {
+    auto rotate = [&](int w, const half8_t& lo, const half8_t& hi) {
         const int hd = w / cph, p0 = (w % cph) * 8;
         half_t* hp = row + static_cast<size_t>(hd) * d;
-        const half8_t lo = *reinterpret_cast<const half8_t*>(hp + p0);
-        const half8_t hi = *reinterpret_cast<const half8_t*>(hp + p0 + half);
         half8_t rlo, rhi;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -350,6 +364,13 @@ rope_append_kernel(RopeArgs a) {
             *reinterpret_cast<half8_t*>(kdst + (hd - a.nh) * head_step + p0) = rlo;
             *reinterpret_cast<half8_t*>(kdst + (hd - a.nh) * head_step + p0 + half) = rhi;
         }
+    };
+#pragma unroll
+    for (int u = 0; u < KEEP; ++u)
+        if (static_cast<int>(threadIdx.x) + u * 256 < items) rotate(threadIdx.x + u * 256, lo[u], hi[u]);
+    for (int w = threadIdx.x + KEEP * 256; w < items; w += 256) {
+        const half_t* hp = row + static_cast<size_t>(w / cph) * d + (w % cph) * 8;
+        rotate(w, *reinterpret_cast<const half8_t*>(hp), *reinterpret_cast<const half8_t*>(hp + half));
     }
     if (vdst) {
         const half8_t* vsrc = reinterpret_cast<const half8_t*>(row + static_cast<size_t>(a.nh + a.nkv) * d);
@@ -361,7 +382,7 @@ rope_append_kernel(RopeArgs a) {
 
 hipError_t launch_rope_append(const RopeArgs& a, hipStream_t stream) {
     if (a.max_rows == 0) return hipSuccess;
-    hipLaunchKernelGGL(rope_append_kernel, dim3(a.max_rows), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL(rope_append_kernel, dim3(a.max_rows + (a.list.cu_exec ? 1 : 0)), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
