@@ -99,7 +99,8 @@ __device__ __forceinline__ void combine_key_ranges(const AttnDev& p, int i, int 
 // sort over the tiles-per-sequence histogram.  `levels` is the host bound on tiles per sequence (<= kItemLevels).
 constexpr int kItemLevels = 1024;
 
-__device__ __forceinline__ int attn_build_sorted(const AttnList& a, int4* __restrict__ items) {
+template <class Rows>
+__device__ __forceinline__ int attn_build_sorted(const AttnList& a, int4* __restrict__ items, Rows&& rows_of) {
     __shared__ int cnt[kItemLevels + 1];      // first: sequences with exactly n tiles; then: sequences with more than n
     __shared__ int offs[kItemLevels + 1];     // items of the tile indices above q
     __shared__ int fill[kItemLevels + 1];
@@ -108,7 +109,8 @@ __device__ __forceinline__ int attn_build_sorted(const AttnList& a, int4* __rest
     for (int i = tid; i <= levels; i += 256) { cnt[i] = 0; fill[i] = 0; }
     __syncthreads();
     for (int b = tid; b < a.B; b += 256) {
-        const int nt = min((a.cu_exec[b + 1] - a.cu_exec[b] + kAttnBQ - 1) / kAttnBQ, levels);
+        int first;
+        const int nt = min((rows_of(b, first) + kAttnBQ - 1) / kAttnBQ, levels);
         atomicAdd(&cnt[nt], 1);
     }
     __syncthreads();
@@ -153,8 +155,8 @@ __device__ __forceinline__ int attn_build_sorted(const AttnList& a, int4* __rest
     }
     __syncthreads();
     for (int b = tid; b < a.B; b += 256) {
-        const int first = a.cu_exec[b];
-        const int rows = a.cu_exec[b + 1] - first;
+        int first;
+        const int rows = rows_of(b, first);
         const int nt = min((rows + kAttnBQ - 1) / kAttnBQ, levels);
         if (nt == 0) continue;
         const int pos = cnt[nt] + atomicAdd(&fill[nt], 1);        // place among the sequences, most tiles first
@@ -165,7 +167,8 @@ __device__ __forceinline__ int attn_build_sorted(const AttnList& a, int4* __rest
 
 // The same list for calls whose sequences could have more than kItemLevels query tiles: sequence by sequence, each
 // sequence's tiles longest first.
-__device__ __forceinline__ int attn_build_by_sequence(const AttnList& a, int4* __restrict__ items) {
+template <class Rows>
+__device__ __forceinline__ int attn_build_by_sequence(const AttnList& a, int4* __restrict__ items, Rows&& rows_of) {
     __shared__ int s_wave[4];
     __shared__ int s_base;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -173,8 +176,8 @@ __device__ __forceinline__ int attn_build_by_sequence(const AttnList& a, int4* _
     __syncthreads();
     for (int b0 = 0; b0 < a.B; b0 += 256) {
         const int b = b0 + threadIdx.x;
-        const int first = b < a.B ? a.cu_exec[b] : 0;
-        const int rows = b < a.B ? a.cu_exec[b + 1] - first : 0;
+        int first = 0;
+        const int rows = b < a.B ? rows_of(b, first) : 0;
         const int nt = (rows + kAttnBQ - 1) / kAttnBQ;
         int incl = nt;
 #pragma unroll
@@ -200,8 +203,20 @@ __device__ __forceinline__ int attn_build_by_sequence(const AttnList& a, int4* _
 __device__ __forceinline__ void attn_build_list(const AttnList& a) {
     __shared__ int s_tiles, s_longest;
     int4* items = reinterpret_cast<int4*>(a.items);
-    if (threadIdx.x == 0) { s_tiles = 0; s_longest = 0; }
-    const int used = a.levels <= kItemLevels ? attn_build_sorted(a, items) : attn_build_by_sequence(a, items);
+    const int tid = threadIdx.x;
+    if (tid == 0) { s_tiles = 0; s_longest = 0; }
+    // sequence tid's rows and cache length are loaded once, together (every trip to memory is a third of this workgroup's time)
+    int own_first = 0, own_end = 0, own_old = 0;
+    if (tid < a.B) {
+        own_first = a.cu_exec[tid];
+        own_end = a.cu_exec[tid + 1];
+        if (a.n_split > 1 && a.kv_old) own_old = a.kv_old[tid];
+    }
+    auto rows_of = [&](int b, int& first) {
+        first = b == tid ? own_first : a.cu_exec[b];
+        return (b == tid ? own_end : a.cu_exec[b + 1]) - first;
+    };
+    const int used = a.levels <= kItemLevels ? attn_build_sorted(a, items, rows_of) : attn_build_by_sequence(a, items, rows_of);
     for (int i = used + threadIdx.x; i < a.items_max; i += 256) items[i] = make_int4(-1, 0, 0, 0);   // unused slots
     if (a.n_split <= 1) return;
     for (int i = threadIdx.x; i < a.items_max * a.heads; i += 256) a.arrive[i] = 0;
@@ -209,7 +224,8 @@ __device__ __forceinline__ void attn_build_list(const AttnList& a) {
     // key tiles of all items, and of the longest
     int tiles = 0, longest = 0;
     for (int b = threadIdx.x; b < a.B; b += 256) {
-        const int rows = a.cu_exec[b + 1] - a.cu_exec[b], old = a.kv_old ? a.kv_old[b] : 0;
+        int first;
+        const int rows = rows_of(b, first), old = !a.kv_old ? 0 : b == tid ? own_old : a.kv_old[b];
         for (int q = 0; q < rows; q += kAttnBQ) {
             const int keys = old + min(q + kAttnBQ, rows);
             const int n = ((a.kv_old ? min(keys, a.cap) : keys) + 63) / 64;

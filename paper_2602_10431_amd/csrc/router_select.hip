@@ -138,118 +138,82 @@ hipError_t launch_reduce_scatter_score(const float* part, int n_parts, int part_
 // z = l_e - l_b (the two-class softmax gives p_0 = sigmoid(z)).  All sums in fp64, one rounding to fp32, so
 // the executed set is reproducible exactly as for the linear router.
 //
-// The first layer is a [T x H] x [H x R] product in fp64 on the vector ALUs.  A workgroup owns 4 x kMlpTW tokens (kMlpTW =
-// 1, 2 or 4 per wave, by the number of tokens: launch_router_mlp) and walks H in chunks of 512 columns: the W1 chunk of 4
-// hidden units is staged in LDS once per workgroup (two buffers, the next chunk's global loads are issued before the current
-// one is consumed, one barrier per chunk), a lane holds 8 consecutive columns of its tokens, and every staged weight is
-// converted to fp64 once and used for all of them (at four tokens 16 accumulators of two registers each per lane, two
-// workgroups per CU; 8 units per pass would spill).  A token's sums do not depend on kMlpTW.  The walk repeats per group of 4
-// units (x then comes from L2).
-constexpr int kMlpRC = 4;         // hidden units per pass
-constexpr int kMlpKC = 512;       // columns per staged chunk
-constexpr int kMlpWL = (kMlpRC * kMlpKC / 4) / 256;   // float4 loads per thread per chunk
+// The first layer is a [T x H] x [H x R] product on the fp64 matrix instruction (16 hidden units x 16 tokens x 4 columns).  It is
+// bound by latency: 46 MFLOP and 6 MB at 1400 tokens, so what counts is that a workgroup has all its loads in flight at once.
+// A workgroup owns 16 tokens and its 16 waves split the columns: of 32 neighbouring columns lane (j, g) = (lane % 16, lane / 16)
+// takes columns 8 g .. 8 g + 7 of unit row j and of token row j (64 to 128 contiguous bytes per row and instruction), one column per
+// instruction: the order of the columns inside a sum is free.  The waves' sums meet in LDS in wave order; hidden units beyond 16
+// take another turn, with the tokens from L1 / L2.  us in a stream, 16 units, before (vector ALUs, 4 to 16 tokens per workgroup,
+// weights staged 512 columns at a time) / now: H = 2048, 700 / 1400 / 4000 / 16000 tokens 16.3 / 10.0, 19.4 / 10.2, 25.3 / 10.7,
+// 73 / 39; 4096 26.3 / 17.3, 31.2 / 17.4, 39.3 / 17.5, 120 / 67; 5120 30.8 / 21.9, 36.4 / 22.0, 47 / 24, 134 / 88.  Above 4096
+// tokens the fp64 rate bounds it, below the H / 4 instructions of one workgroup.
+constexpr int kMlpWaves = 16, kMlpUnits = 16, kMlpTokens = 16;
 
-template <bool BF16, int kMlpTW>
-__global__ void __launch_bounds__(256, 2)
+template <bool BF16>
+__global__ void __launch_bounds__(kMlpWaves * 64)
 router_mlp_kernel(const uint16_t* __restrict__ x, int T, int H, const float* __restrict__ W1,
                   const float* __restrict__ b1, const float* __restrict__ W2, const float* __restrict__ b2, int R,
                   float* __restrict__ z) {
-    __shared__ __attribute__((aligned(16))) float Ws[2][kMlpRC][kMlpKC];
+    typedef double double4_t __attribute__((ext_vector_type(4)));
+    __shared__ double part[kMlpWaves][kMlpUnits * kMlpTokens];
+    __shared__ double act[kMlpUnits][kMlpTokens];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int t0 = blockIdx.x * (4 * kMlpTW) + wave * kMlpTW;
-    const uint16_t* xrow[kMlpTW];
+    const int j = lane & 15, g = lane >> 4;
+    const int t0 = blockIdx.x * kMlpTokens;
+    const uint16_t* xrow = x + static_cast<size_t>(min(t0 + j, T - 1)) * H;
+    double le = 0.0, lb = 0.0;                                   // threads 0 .. 15: the two logits of token t0 + tid
+    for (int rg = 0; rg < R; rg += kMlpUnits) {
+        const float* wrow = W1 + static_cast<size_t>(min(rg + j, R - 1)) * H;    // units past R: their sums are not used
+        double4_t acc = {0.0, 0.0, 0.0, 0.0};
+        constexpr int U = 4;                                     // pieces of 32 columns in flight per wave
+        for (int c0 = wave * 32; c0 < H; c0 += kMlpWaves * 32 * U) {
+            u32x4_t xv[U];
+            float4_t w0[U], w1[U];
 #pragma unroll
-    for (int i = 0; i < kMlpTW; ++i) xrow[i] = x + static_cast<size_t>(min(t0 + i, T - 1)) * H;
-
-    double le[kMlpTW], lb[kMlpTW];
-#pragma unroll
-    for (int i = 0; i < kMlpTW; ++i) { le[i] = 0.0; lb[i] = 0.0; }
-
-    float4 wreg[kMlpWL];
-    u32x4_t xreg[kMlpTW];
-    auto fetch = [&](int rc, int kb) {                         // global -> registers for chunk (rc, kb)
-#pragma unroll
-        for (int it = 0; it < kMlpWL; ++it) {
-            const int c = it * 256 + tid;
-            const int row = c / (kMlpKC / 4), col = (c % (kMlpKC / 4)) * 4;
-            wreg[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (rc + row < R && kb + col < H)
-                wreg[it] = *reinterpret_cast<const float4*>(W1 + static_cast<size_t>(rc + row) * H + kb + col);
-        }
-        const int k = kb + lane * 8;
-#pragma unroll
-        for (int i = 0; i < kMlpTW; ++i) {
-            xreg[i] = u32x4_t{0u, 0u, 0u, 0u};
-            if (k < H) xreg[i] = *reinterpret_cast<const u32x4_t*>(xrow[i] + k);
-        }
-    };
-
-    const int n_kb = (H + kMlpKC - 1) / kMlpKC;
-    const int n_rc = (R + kMlpRC - 1) / kMlpRC;
-    const int n_chunks = n_rc * n_kb;                          // walked as one sequence: rc-major, kb-minor
-    fetch(0, 0);
-    int buf = 0;
-    double acc[kMlpTW][kMlpRC];
-    for (int ch = 0; ch < n_chunks; ++ch) {
-        const int rc = (ch / n_kb) * kMlpRC, kbi = ch % n_kb;
-        if (kbi == 0) {
-#pragma unroll
-            for (int i = 0; i < kMlpTW; ++i)
-#pragma unroll
-                for (int r = 0; r < kMlpRC; ++r) acc[i][r] = 0.0;
-        }
-        // park this chunk's weights, expand this chunk's activations
-#pragma unroll
-        for (int it = 0; it < kMlpWL; ++it) {
-            const int c = it * 256 + tid;
-            *reinterpret_cast<float4*>(&Ws[buf][c / (kMlpKC / 4)][(c % (kMlpKC / 4)) * 4]) = wreg[it];
-        }
-        double xd[kMlpTW][8];
-#pragma unroll
-        for (int i = 0; i < kMlpTW; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                xd[i][2 * j] = static_cast<double>(act_to_float<BF16>(static_cast<uint16_t>(xreg[i][j] & 0xffffu)));
-                xd[i][2 * j + 1] = static_cast<double>(act_to_float<BF16>(static_cast<uint16_t>(xreg[i][j] >> 16)));
-            }
-        __syncthreads();          // chunk staged; the other buffer (read in the previous iteration) is free again
-        if (ch + 1 < n_chunks) fetch(((ch + 1) / n_kb) * kMlpRC, ((ch + 1) % n_kb) * kMlpKC);
-#pragma unroll
-        for (int r = 0; r < kMlpRC; ++r) {
-            const float4 w0 = *reinterpret_cast<const float4*>(&Ws[buf][r][lane * 8]);
-            const float4 w1 = *reinterpret_cast<const float4*>(&Ws[buf][r][lane * 8 + 4]);
-            const double wd[8] = {static_cast<double>(w0.x), static_cast<double>(w0.y), static_cast<double>(w0.z),
-                                  static_cast<double>(w0.w), static_cast<double>(w1.x), static_cast<double>(w1.y),
-                                  static_cast<double>(w1.z), static_cast<double>(w1.w)};
-#pragma unroll
-            for (int i = 0; i < kMlpTW; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[i][r] = fma(xd[i][j], wd[j], acc[i][r]);
-        }
-        buf ^= 1;
-        if (kbi == n_kb - 1) {
-            // hidden units of this pass: full sums, bias, ReLU, then their share of the two logits (in unit order)
-#pragma unroll
-            for (int r = 0; r < kMlpRC; ++r) {
-                const bool live = rc + r < R;
-                const double bias = live ? static_cast<double>(b1[rc + r]) : 0.0;
-                const double we = live ? static_cast<double>(W2[rc + r]) : 0.0;
-                const double wb = live ? static_cast<double>(W2[R + rc + r]) : 0.0;
-#pragma unroll
-                for (int i = 0; i < kMlpTW; ++i) {
-                    const double u = fmax(wave_sum(acc[i][r]) + bias, 0.0);
-                    le[i] = fma(we, u, le[i]);
-                    lb[i] = fma(wb, u, lb[i]);
+            for (int u = 0; u < U; ++u) {
+                const int col = c0 + u * (kMlpWaves * 32) + 8 * g;
+                xv[u] = u32x4_t{0u, 0u, 0u, 0u};
+                w0[u] = w1[u] = float4_t{0.f, 0.f, 0.f, 0.f};
+                if (col < H) {                                   // H % 8 == 0: the 8 columns are all in or all out
+                    xv[u] = *reinterpret_cast<const u32x4_t*>(xrow + col);
+                    w0[u] = *reinterpret_cast<const float4_t*>(wrow + col);
+                    w1[u] = *reinterpret_cast<const float4_t*>(wrow + col + 4);
                 }
             }
-        }
-    }
-    if (lane == 0) {
-        const double be = static_cast<double>(b2[0]), bb = static_cast<double>(b2[1]);
 #pragma unroll
-        for (int i = 0; i < kMlpTW; ++i)
-            if (t0 + i < T) z[t0 + i] = static_cast<float>((le[i] + be) - (lb[i] + bb));
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int s = 0; s < 8; ++s) {
+                    const uint32_t word = xv[u][s >> 1];
+                    const double a = static_cast<double>(s < 4 ? w0[u][s] : w1[u][s - 4]);
+                    const double b = static_cast<double>(act_to_float<BF16>(static_cast<uint16_t>(s & 1 ? word >> 16 : word & 0xffffu)));
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
+                }
+        }
+        // register r of lane (j, g) is unit 4 r + g of token j
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave][(4 * r + g) * kMlpTokens + j] = acc[r];
+        __syncthreads();
+        if (tid < kMlpUnits * kMlpTokens) {
+            double sum = 0.0;
+#pragma unroll
+            for (int w = 0; w < kMlpWaves; ++w) sum += part[w][tid];
+            const int unit = rg + tid / kMlpTokens;
+            act[tid / kMlpTokens][tid % kMlpTokens] = unit < R ? fmax(sum + static_cast<double>(b1[unit]), 0.0) : 0.0;
+        }
+        __syncthreads();
+        if (tid < kMlpTokens) {
+#pragma unroll
+            for (int r = 0; r < kMlpUnits; ++r) {                // in unit order
+                const int unit = min(rg + r, R - 1);             // past R: the hidden value is 0
+                const double u = act[r][tid];
+                le = fma(static_cast<double>(W2[unit]), u, le);
+                lb = fma(static_cast<double>(W2[R + unit]), u, lb);
+            }
+        }
+        __syncthreads();                                         // act and part are rewritten by the next turn
     }
+    if (tid < kMlpTokens && t0 + tid < T) z[t0 + tid] = static_cast<float>((le + static_cast<double>(b2[0])) - (lb + static_cast<double>(b2[1])));
 }
 
 // Few tokens (decode steps): one workgroup per token, the 256 threads split H (8 columns each per 2048-column
@@ -319,28 +283,17 @@ hipError_t launch_router_mlp(const void* x, int bf16, int T, int H, const float*
                              const float* b2, int R, float* z, hipStream_t stream) {
     if (T == 0) return hipSuccess;
     const uint16_t* xp = reinterpret_cast<const uint16_t*>(x);
-    if (T <= 512) {                                            // too few tokens to fill the chip 16 per workgroup
-        if (bf16)
-            hipLaunchKernelGGL(router_mlp_small_kernel<true>, dim3(T), dim3(256), 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
-        else
-            hipLaunchKernelGGL(router_mlp_small_kernel<false>, dim3(T), dim3(256), 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
+    // One workgroup per token up to two per CU: 16 of 16 columns of the matrix instruction for a few tokens are mostly idle.
+    // us, per token / matrix: H = 2048, 1 / 100 / 256 / 512 tokens 8.0 / 8.9, 8.5 / 9.7, 8.8 / 9.7, 10.6 / 10.0; 4096 8.9 / 14.2,
+    // 9.6 / 16.8, 10.2 / 16.9, 13.6 / 17.1.
+    if (T <= 512) {
+        if (bf16) hipLaunchKernelGGL(router_mlp_small_kernel<true>, dim3(T), dim3(256), 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
+        else hipLaunchKernelGGL(router_mlp_small_kernel<false>, dim3(T), dim3(256), 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
         return hipGetLastError();
     }
-    // kMlpTW tokens per wave: four reuse every converted weight four times, but 16 tokens per workgroup need 16 tokens per CU; with
-    // fewer tokens the workgroups get smaller until they number about two per CU (1400 tokens x 2048 columns x 16 units: 28 us
-    // at four tokens per wave, 19 at one; 1000 x 4096 40 -> 27).  A token's sums are the same bits either way.
-    auto go = [&](auto bf, auto tw) {
-        constexpr int TW = decltype(tw)::value;
-        hipLaunchKernelGGL((router_mlp_kernel<decltype(bf)::value, TW>), dim3((T + 4 * TW - 1) / (4 * TW)), dim3(256), 0, stream, xp, T, H, W1, b1,
-                           W2, b2, R, z);
-    };
-    auto by_tokens = [&](auto bf) {
-        if (T > 4096) go(bf, std::integral_constant<int, 4>{});
-        else if (T > 2048) go(bf, std::integral_constant<int, 2>{});
-        else go(bf, std::integral_constant<int, 1>{});
-    };
-    if (bf16) by_tokens(std::true_type{});
-    else by_tokens(std::false_type{});
+    const dim3 grid((T + kMlpTokens - 1) / kMlpTokens), block(kMlpWaves * 64);
+    if (bf16) hipLaunchKernelGGL(router_mlp_kernel<true>, grid, block, 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
+    else hipLaunchKernelGGL(router_mlp_kernel<false>, grid, block, 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
     return hipGetLastError();
 }
 

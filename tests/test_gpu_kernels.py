@@ -218,6 +218,14 @@ def test_mlp_router_scores_are_bit_exact_in_every_token_form(qt, T, H, R, dtype)
     test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype)
 
 
+@pytest.mark.parametrize("T", [512, 513, 529])
+@pytest.mark.parametrize("H,R,dtype", [(8, 1, "fp16"), (2056, 17, "bf16"), (520, 16, "fp16")])
+def test_mlp_router_scores_are_bit_exact_on_both_sides_of_the_matrix_form(qt, T, H, R, dtype):
+    # one workgroup per token up to 512; above, 16 tokens x 16 units on the fp64 matrix instruction: ragged last tokens and
+    # units, columns that end inside a wave's 32
+    test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype)
+
+
 @pytest.mark.parametrize("K,G,bits", [(40, 32, 4), (72, 64, 3), (264, 128, 2), (320, 32, 3), (384, 128, 4), (456, 64, 2)])
 def test_large_tile_gemm_short_and_ragged_k(qt, K, G, bits):
     # 2600 rows x 2048 columns is past the 64-row-tile regime, so these run the 128 x 256 tiles: one to eight
