@@ -198,6 +198,12 @@ __device__ __forceinline__ int attn_build_by_sequence(const AttnList& a, int4* _
 }
 
 
+__device__ __forceinline__ int tiles_per_range(const AttnList& a, int used, int tiles, int longest) {
+    const int fill = static_cast<int>((static_cast<long>(tiles) * a.heads + a.target - 1) / a.target);   // the ranges fill the chip once
+    const bool cut = 2l * used * a.heads < a.target;
+    return cut ? max(max(fill, (longest + a.n_split - 1) / a.n_split), kAttnTileRange) : max(longest, 1);
+}
+
 // List, length of the key ranges and cleared counters, by one workgroup of 256 threads.  A launch of its own for this took 4.6 us
 // of every prefill call.
 __device__ __forceinline__ void attn_build_list(const AttnList& a) {
@@ -216,6 +222,34 @@ __device__ __forceinline__ void attn_build_list(const AttnList& a) {
         first = b == tid ? own_first : a.cu_exec[b];
         return (b == tid ? own_end : a.cu_exec[b + 1]) - first;
     };
+    if (a.B <= 64 && a.levels <= 64) {
+        // One wave, a sequence per lane: the items of query tile q are the sequences with more than q tiles, in sequence order
+        if (a.n_split > 1)
+            for (int i = tid; i < a.items_max * a.heads; i += 256) a.arrive[i] = 0;
+        if (tid >= 64) return;
+        const int rows = tid < a.B ? own_end - own_first : 0, nt = min((rows + kAttnBQ - 1) / kAttnBQ, a.levels);
+        int used = 0, tiles = 0, longest = 0;
+        for (int q = a.levels - 1; q >= 0; --q) {
+            const unsigned long long m = __ballot(nt > q);
+            if (nt > q) {
+                items[used + __popcll(m & ((1ull << tid) - 1ull))] = make_int4(tid, q, own_first, rows);
+                const int keys = own_old + min((q + 1) * kAttnBQ, rows);
+                const int n = ((a.kv_old ? min(keys, a.cap) : keys) + 63) / 64;
+                tiles += n;
+                longest = max(longest, n);
+            }
+            used += __popcll(m);
+        }
+        for (int i = used + tid; i < a.items_max; i += 64) items[i] = make_int4(-1, 0, 0, 0);
+        if (a.n_split <= 1) return;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            tiles += __shfl_xor(tiles, o, 64);
+            longest = max(longest, __shfl_xor(longest, o, 64));
+        }
+        if (tid == 0) *a.tiles = tiles_per_range(a, used, tiles, longest);
+        return;
+    }
     const int used = a.levels <= kItemLevels ? attn_build_sorted(a, items, rows_of) : attn_build_by_sequence(a, items, rows_of);
     for (int i = used + threadIdx.x; i < a.items_max; i += 256) items[i] = make_int4(-1, 0, 0, 0);   // unused slots
     if (a.n_split <= 1) return;
@@ -236,11 +270,7 @@ __device__ __forceinline__ void attn_build_list(const AttnList& a) {
     atomicAdd(&s_tiles, tiles);
     atomicMax(&s_longest, longest);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const int fill = static_cast<int>((static_cast<long>(s_tiles) * a.heads + a.target - 1) / a.target);   // the ranges fill the chip once
-        const bool cut = 2l * used * a.heads < a.target;
-        *a.tiles = cut ? max(max(fill, (s_longest + a.n_split - 1) / a.n_split), kAttnTileRange) : max(s_longest, 1);
-    }
+    if (threadIdx.x == 0) *a.tiles = tiles_per_range(a, used, s_tiles, s_longest);
 }
 
 // The decode form for 2, 4 or 8 query heads per kv head (attention_gqa.hip); for one it is in attention.hip.
