@@ -382,7 +382,8 @@ constexpr int kWideRows = 128, kWideFrags = 4;   // rows and 32-column fragments
 inline int gemm_wide_cols(const GemmDev& d) { return (d.vf_total + kWideFrags - 1) / kWideFrags; }
 inline int gemm_wide_chunks(const GemmDev& d) { return (d.M_max + kWideRows - 1) / kWideRows; }
 inline int gemm_wide_blocks(const GemmDev& d) { return gemm_wide_cols(d) * gemm_wide_chunks(d); }   // workgroups without a K split
-hipError_t launch_gemm_wide(GemmDev& d, int epilogue, int ksplit, hipStream_t stream);
+// slices: 4, or 2 (two workgroups per CU)
+hipError_t launch_gemm_wide(GemmDev& d, int epilogue, int ksplit, int slices, hipStream_t stream);
 hipError_t launch_gemm_mid(GemmDev& d, int epilogue, hipStream_t stream);
 
 }  // namespace qtale

@@ -332,6 +332,22 @@ static bool wide_round(const GemmDev& d) {
     return d.KT >= 32 && d.M_max > kGemmWideRows && cols * ((d.M_max + 63) / 64) > cus && gemm_wide_blocks(d) <= cus;
 }
 
+// Above 256 rows, outputs that the 128 x 256 tiles would take and the 128-row kernel with two workgroups per CU takes faster: gate/up
+// in three chunks of which the last is not full, and outputs whose tiles are a few more than the CUs (they take one round, but
+// some CUs hold two tiles and most one) while the last chunk is half empty at least.  us, tiles / this kernel: gate/up 14336 x
+// 4096 at 257, 320, 352, 384 rows 100 / 82, 101 / 89, 102 / 97, 102 / 104, 13824 x 5120 125 / 100, 124 / 110, 125 / 118, 126 / 127,
+// 11008 x 4096 at 330, 352, 384 96 / 87, 97 / 87, 96 / 99, 5632 x 2048 33 / 30, 33 / 30, 33 / 33; at 400 rows (four chunks) 144 /
+// 147, 105 / 100; tiles 1.03 to 1.17 times the CUs: store 6144 x 4096 at 1300 rows 97 / 79 (1408, full, 98 / 99), 12288 x 4096 at
+// 700 99 / 89 (768 99 / 100), 15360 x 5120 at 513 and 560 122 / 109, 122 / 108 (640 123 / 122), gate/up 5632 x 2048 at 700 53 / 44.
+// (Only where the host knows the row count: workgroups without rows leave one of the two per CU alone, which is slower than four
+// slices.)
+static bool two_slices_win(const GemmDev& d, bool swiglu, int cus) {
+    if (d.count && !d.rows_exact) return false;
+    if (swiglu && d.M_max > kGemmWideRows && d.M_max <= 352) return true;
+    const int tiles = ((d.M_max + 127) / 128) * ((d.vf_total + 7) / 8);
+    return tiles > cus && 5 * tiles <= 6 * cus && (d.M_max - 1) % 128 < 64;
+}
+
 // Residual outputs above 64 rows on the 128-row kernel: the number of K parts, as many as one round of the chip takes and the
 // caller's buffer holds (0 = another kernel).  Two or more up to kGemmPartsMaxRows, whole layer, us, without / with parts: 7B shape
 // 264 rows 250 / 225, 300 rows 252 / 233, 400 rows 315 / 306, 512 rows 324 / 320; 13B 264 rows 359 / 329; 8B-GQA 300 rows 289 /
@@ -351,7 +367,7 @@ static int wide_parts(const GemmDev& d, const GemmArgs& a) {
 static hipError_t launch_wide_parts(GemmDev& d, const GemmArgs& a, hipStream_t stream) {
     d.out = a.part;
     *a.n_parts = wide_parts(d, a);
-    return launch_gemm_wide(d, EPI_PARTIAL_F32, *a.n_parts, stream);
+    return launch_gemm_wide(d, EPI_PARTIAL_F32, *a.n_parts, 4, stream);
 }
 
 // 65 to kGemmWideRows rows.  Measured with 4-bit group-128 weights, us, cold, launches of a graph (K = 4096 unless stated).
@@ -367,6 +383,9 @@ static hipError_t launch_wide_parts(GemmDev& d, const GemmArgs& a, hipStream_t s
 //     34 / 39, 41 / 46, with K = 2048 22.0 / 23.1, 24.8 / 26.2, K = 1024 16.0 / 15.6, 17.2 / 16.7; 11008 columns at 65 / 96 / 128 rows, skinny / wide / mid:
 //     43 / 31 / 41, 39 / 32 / 41, 41 / 38 / 41; 14336: 54 / 35 / 45, 52 / 36 / 46, 53 / 43 / 46; 18944 (296 workgroups): 64 / 58 / 67,
 //     66 / 62 / 67, 68 / 76 / 68
+//   129 to 256 rows with two workgroups per CU (two k-slices), four slices or mid / two slices: 11008 (344 workgroups) 130, 160, 192, 224,
+//     256 rows 48 / 43, 48 / 43, 54 / 49, 62 / 55, 63 / 62; 14336 (448) 56 / 53, 53 / 52, 59 / 58, 68 / 63, 70 / 70; 13824 x 5120 (432)
+//     69 / 63, 65 / 62, 74 / 69, 85 / 77, 87 / 85; K = 2048 18 / 20
 //   129 to 192 rows: 11008 (344 workgroups) 59 / 59 / 65, K = 2048 34 / 35 / 35, K = 1024 21.5 / 25 / 22; 14336 (448) 76 / 63 / 68, K = 1024
 //     26 / 26 / 24; 18944 (592, three rounds) 91 / 91 / 77;   193 to 256 rows: 11008 77 / 74 / 68, 14336 91 / 80 / 76
 // Beyond that, store: 6144 columns at 96 / 160 rows, decode / wide / mid 18 / 27 / 24, 21 / 27 / 24; 12288: 24 / 28 / 26, 45 / 29 / 37.
@@ -375,6 +394,7 @@ static hipError_t launch_wide_parts(GemmDev& d, const GemmArgs& a, hipStream_t s
 static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t stream) {
     const int cus = resident_workgroups(1);
     const int chunks = gemm_wide_chunks(d), blocks = gemm_wide_blocks(d);
+    const bool exact = !d.count || d.rows_exact;
     const int frags = a.epilogue == EPI_SWIGLU_F16 || d.vf_total >= 256 ? 2 : 1;   // per skinny workgroup
     // (a device-side count: as if half of the bound executed; the other chunks leave at once.  Hidden 2048, 130 to 192 tokens in
     // threshold mode, gate/up on the wide kernel: 4 to 9 % of the layer)
@@ -382,17 +402,18 @@ static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t str
     if (a.epilogue == EPI_SWIGLU_F16) {
         if (skinny < 2 * cus || (skinny == 2 * cus && (d.M_max > 96 || d.KT <= 32))) return launch_gemm_skinny(d, a.epilogue, stream);
         if (blocks <= cus) {                                         // one round of wide workgroups
-            return d.M_max > 192 && d.KT < 32 ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_wide(d, a.epilogue, 1, stream);
+            return d.M_max > 192 && d.KT < 32 ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_wide(d, a.epilogue, 1, 4, stream);
         }
-        if (chunks == 1) return d.M_max <= 96 && d.KT >= 64 ? launch_gemm_wide(d, a.epilogue, 1, stream) : launch_gemm_mid(d, a.epilogue, stream);
+        if (chunks == 2 && blocks <= 2 * cus && d.KT >= 64 && exact) return launch_gemm_wide(d, a.epilogue, 1, 2, stream);
+        if (chunks == 1) return d.M_max <= 96 && d.KT >= 64 ? launch_gemm_wide(d, a.epilogue, 1, 4, stream) : launch_gemm_mid(d, a.epilogue, stream);
         if (d.M_max > 192 || blocks > 2 * cus) return launch_gemm_mid(d, a.epilogue, stream);
         if (d.KT <= 32 && 2 * blocks <= 3 * cus) return launch_gemm_skinny(d, a.epilogue, stream);
-        return d.KT <= 16 ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_wide(d, a.epilogue, 1, stream);
+        return d.KT <= 16 ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_wide(d, a.epilogue, 1, 4, stream);
     }
     if (a.epilogue == EPI_STORE_F16) {
         if (skinny <= cus && (frags == 1 || d.KT >= 64)) return launch_gemm_skinny(d, a.epilogue, stream);
         if (blocks > cus) return launch_gemm_mid(d, a.epilogue, stream);
-        if (8 * blocks >= 5 * cus) return launch_gemm_wide(d, a.epilogue, 1, stream);
+        if (8 * blocks >= 5 * cus) return launch_gemm_wide(d, a.epilogue, 1, 4, stream);
         int nwn;
         gemm_decode_plan(d, a.epilogue, 1, &nwn);
         return launch_gemm_decode(d, a.epilogue, nwn, 1, stream);
@@ -460,7 +481,7 @@ hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     if (d.M_max <= kGemmPartRows) return launch_small_rows(d, a, true, stream);
     if (d.M_max <= kGemmWideRows) return launch_mid_rows(d, a, stream);
     if (wide_parts(d, a) > 0) return launch_wide_parts(d, a, stream);
-    if (a.epilogue == EPI_STORE_F16 && wide_round(d)) return launch_gemm_wide(d, a.epilogue, 1, stream);
+    if (a.epilogue == EPI_STORE_F16 && wide_round(d)) return launch_gemm_wide(d, a.epilogue, 1, 4, stream);
     // A few hundred rows: so few 128 x 256 tiles that a CU holds at most one workgroup, whose k-loop then runs
     // at one memory latency per k-tile.  The 64-row kernel with its deep prefetch rings takes over while its own
     // grid fits the chip in one round (measured crossovers on 7B- and 13B-shaped linears: 2.5 workgroups per CU
@@ -470,6 +491,7 @@ hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
         const int mid_tiles = ((d.M_max + 63) / 64) * ((d.vf_total + (swiglu ? 7 : 3)) / (swiglu ? 8 : 4));
         const int cus = resident_workgroups(1);
         if (swiglu ? mid_tiles <= 2 * cus : 2 * mid_tiles <= 5 * cus) return launch_gemm_mid(d, a.epilogue, stream);
+        if ((swiglu || a.epilogue == EPI_STORE_F16) && two_slices_win(d, swiglu, cus)) return launch_gemm_wide(d, a.epilogue, 1, 2, stream);
     }
     // 128-row tiles from here on; the rows after the last full tile may go to the small-row kernels (gemm_tail_rows).
     // With a device-side count (threshold mode) the tail launch is always made and decides on the device.

@@ -17,7 +17,10 @@
 //   * narrow outputs (o-proj, down-proj) also cut K across workgroups and write fp32 partial tiles that the consumer kernel
 //     adds in order (no atomics, no fences);
 //   * row fragments past the executed rows are left out (the count may be known on the device only);
-//   * the k-slices meet in LDS, 32 columns of every wave at a time; slice s adds and stores row fragment s.
+//   * the k-slices meet in LDS, 32 columns of every wave at a time; a slice adds and stores its share of the row fragments;
+//   * outputs whose workgroups are one to two per CU take two k-slices instead of four: half the waves and LDS, so two workgroups
+//     share a CU, each with barriers of its own, and a CU that has two does not run them one after the other (gate/up of 11008
+//     columns at 150 rows, 344 workgroups: 48 -> 43 us; one alone takes 37 where four slices take 34).
 #include <algorithm>
 #include <type_traits>
 
@@ -25,14 +28,15 @@
 
 namespace qtale {
 
-constexpr int kWideNC = 2, kWideNK = 4, kWideFM = kWideRows / 32;
+constexpr int kWideNC = 2, kWideFM = kWideRows / 32;
 
-template <int BITS, int GPT, bool SWIGLU>
-__global__ void __launch_bounds__(kWideNC * kWideNK * 64, 2)
+template <int BITS, int GPT, bool SWIGLU, int NK>
+__global__ void __launch_bounds__(kWideNC * NK * 64, 2)
 gemm_wide_kernel(GemmDev p) {
     using WB = WBits<BITS>;
-    constexpr int NC = kWideNC, NK = kWideNK, FM = kWideFM, FN = kWideFrags / kWideNC, NW = NC * NK;
-    static_assert(FN == 2 && FM == 4 && NK == FM, "gate and up, or two columns; the row fragments are met by one slice each");
+    constexpr int NC = kWideNC, FM = kWideFM, FN = kWideFrags / kWideNC, NW = NC * NK;
+    constexpr int MS = FM / NK;                                  // row fragments that a slice meets
+    static_assert(FN == 2 && FM == 4 && FM % NK == 0, "gate and up, or two columns");
     constexpr int TEAM = NC * 64;
     constexpr int kTileHalves = kWideRows * kLdsStride;
     constexpr int SSTR = 36;                                     // slab row stride (floats)
@@ -188,7 +192,7 @@ gemm_wide_kernel(GemmDev p) {
     // ---- meet: wave (wc, s) adds and stores row fragment s of its column group, 32 columns of each wave at a time -----------
     float* slab = reinterpret_cast<float*>(smem);                // [wave][128 rows][36]; the last round's barrier has passed
     const int c4 = (lane & 7) * 4, rr = lane >> 3;               // this lane's 4 columns, and row inside a pass of 8
-    float4 v[FN][4];
+    float4 v[MS][FN][4];
 #pragma unroll
     for (int fn = 0; fn < FN; ++fn) {
         if (fn > 0) __syncthreads();
@@ -200,21 +204,25 @@ gemm_wide_kernel(GemmDev p) {
                 for (int r = 0; r < 16; ++r) mine[(fm * 32 + 8 * (r >> 2) + 4 * lhi + (r & 3)) * SSTR + l32] = acc[fm][fn][r];
             }
         __syncthreads();
-        if (wk < n_live) {
+#pragma unroll
+        for (int m = 0; m < MS; ++m) {
+            const int fm = wk * MS + m;
+            if (fm >= n_live) continue;
 #pragma unroll
             for (int ps = 0; ps < 4; ++ps) {
-                v[fn][ps] = make_float4(0.f, 0.f, 0.f, 0.f);
+                v[m][fn][ps] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
                 for (int s = 0; s < NK; ++s) {
-                    const float4 t = *reinterpret_cast<const float4*>(slab + (s * NC + wc) * (kWideRows * SSTR) + (wk * 32 + ps * 8 + rr) * SSTR + c4);
-                    v[fn][ps].x += t.x; v[fn][ps].y += t.y; v[fn][ps].z += t.z; v[fn][ps].w += t.w;
+                    const float4 t = *reinterpret_cast<const float4*>(slab + (s * NC + wc) * (kWideRows * SSTR) + (fm * 32 + ps * 8 + rr) * SSTR + c4);
+                    v[m][fn][ps].x += t.x; v[m][fn][ps].y += t.y; v[m][fn][ps].z += t.z; v[m][fn][ps].w += t.w;
                 }
             }
         }
     }
-    if (wk >= n_live) return;
 #pragma unroll
-    for (int fo = 0; fo < (SWIGLU ? 1 : FN); ++fo) {
+    for (int mf = 0; mf < MS * (SWIGLU ? 1 : FN); ++mf) {
+        const int m = mf % MS, fo = mf / MS;
+        if (wk * MS + m >= n_live) continue;
         const int vf = (tile_n * NC + wc) * FN + fo;
         if (vf >= p.vf_total) continue;
         int mat, f;
@@ -224,12 +232,12 @@ gemm_wide_kernel(GemmDev p) {
         const int col = (SWIGLU ? 0 : p.colbase[mat]) + ncol;
 #pragma unroll
         for (int ps = 0; ps < 4; ++ps) {
-            const int lrow = wk * 32 + ps * 8 + rr;
+            const int lrow = (wk * MS + m) * 32 + ps * 8 + rr;
             if (lrow >= M) continue;
             const size_t row = row0 + lrow;
-            float4 o = v[fo][ps];
+            float4 o = v[m][fo][ps];
             if (SWIGLU) {
-                const float4 u = v[FN - 1][ps];
+                const float4 u = v[m][FN - 1][ps];
                 o.x = silu_f(o.x) * u.x; o.y = silu_f(o.y) * u.y; o.z = silu_f(o.z) * u.z; o.w = silu_f(o.w) * u.w;
             }
             if (!SWIGLU && p.epi_rt == EPI_PARTIAL_F32) {
@@ -245,14 +253,19 @@ gemm_wide_kernel(GemmDev p) {
 }
 
 template <int BITS, int GPT>
-static hipError_t launch_kind(const GemmDev& d, int epilogue, hipStream_t stream) {
-    const dim3 grid(((d.tiles_n + 7) / 8) * 8 * d.row_chunks, d.ksplit), block(kWideNC * kWideNK * 64);
-    if (epilogue == EPI_SWIGLU_F16) hipLaunchKernelGGL((gemm_wide_kernel<BITS, GPT, true>), grid, block, 0, stream, d);
-    else hipLaunchKernelGGL((gemm_wide_kernel<BITS, GPT, false>), grid, block, 0, stream, d);
+static hipError_t launch_kind(const GemmDev& d, int epilogue, int slices, hipStream_t stream) {
+    const dim3 grid(((d.tiles_n + 7) / 8) * 8 * d.row_chunks, d.ksplit), block(kWideNC * slices * 64);
+    if (epilogue == EPI_SWIGLU_F16) {
+        if (slices == 2) hipLaunchKernelGGL((gemm_wide_kernel<BITS, GPT, true, 2>), grid, block, 0, stream, d);
+        else hipLaunchKernelGGL((gemm_wide_kernel<BITS, GPT, true, 4>), grid, block, 0, stream, d);
+    } else {
+        if (slices == 2) hipLaunchKernelGGL((gemm_wide_kernel<BITS, GPT, false, 2>), grid, block, 0, stream, d);
+        else hipLaunchKernelGGL((gemm_wide_kernel<BITS, GPT, false, 4>), grid, block, 0, stream, d);
+    }
     return hipGetLastError();
 }
 
-hipError_t launch_gemm_wide(GemmDev& d, int epilogue, int ksplit, hipStream_t stream) {
+hipError_t launch_gemm_wide(GemmDev& d, int epilogue, int ksplit, int slices, hipStream_t stream) {
     d.tiles_n = gemm_wide_cols(d);
     if (d.tiles_n == 0) return hipSuccess;
     // the chunks share the row fragments evenly: 150 rows are 96 + 54, five fragments and not six
@@ -260,9 +273,9 @@ hipError_t launch_gemm_wide(GemmDev& d, int epilogue, int ksplit, hipStream_t st
     d.chunk_rows = (((d.M_max + 31) / 32 + d.row_chunks - 1) / d.row_chunks) * 32;
     d.ksplit = ksplit;
     d.epi_rt = epilogue;
-    if (d.bits == 3) return d.gshift == 5 ? launch_kind<3, 2>(d, epilogue, stream) : launch_kind<3, 1>(d, epilogue, stream);
-    if (d.bits == 2) return d.gshift == 5 ? launch_kind<2, 2>(d, epilogue, stream) : launch_kind<2, 1>(d, epilogue, stream);
-    return d.gshift == 5 ? launch_kind<4, 2>(d, epilogue, stream) : launch_kind<4, 1>(d, epilogue, stream);
+    if (d.bits == 3) return d.gshift == 5 ? launch_kind<3, 2>(d, epilogue, slices, stream) : launch_kind<3, 1>(d, epilogue, slices, stream);
+    if (d.bits == 2) return d.gshift == 5 ? launch_kind<2, 2>(d, epilogue, slices, stream) : launch_kind<2, 1>(d, epilogue, slices, stream);
+    return d.gshift == 5 ? launch_kind<4, 2>(d, epilogue, slices, stream) : launch_kind<4, 1>(d, epilogue, slices, stream);
 }
 
 }  // namespace qtale

@@ -134,3 +134,18 @@ def test_layer_with_k_parts_in_more_row_chunks(qt, shape, T, mode, val):
 @pytest.mark.parametrize("K", [328, 2008])
 def test_linear_that_fills_one_round_of_128_row_workgroups(qt, M, N, bits, G, K):
     test_linear_of_a_hundred_rows(qt, M, N, K, G, bits)
+
+
+# two k-slices (two workgroups per CU): gate/up in two chunks with K of 64 k-tiles and more (odd numbers of rounds, every
+# remainder of the ring, a ragged last k-tile), in three chunks with a short K, and outputs whose large tiles are a few more
+# than the CUs; 1 to 4 live row fragments in the last chunk
+@pytest.mark.parametrize("M,I,K,G,bits", [(129, 8328, 4096, 128, 4), (160, 8328, 4104, 64, 3), (193, 8328, 4168, 32, 2), (256, 8328, 4352, 128, 4),
+                                          (150, 8328, 4296, 32, 4), (257, 13192, 72, 64, 4), (320, 13192, 136, 128, 2), (352, 13192, 200, 32, 3),
+                                          (353, 13192, 136, 64, 4), (700, 5640, 264, 128, 4), (644, 5640, 72, 32, 4)])
+def test_swiglu_on_two_slices(qt, M, I, K, G, bits):
+    test_swiglu_of_a_hundred_rows(qt, M, I, K, G, bits)
+
+
+@pytest.mark.parametrize("M,N,K,G,bits", [(1300, 6152, 136, 128, 4), (1313, 6152, 72, 32, 3), (700, 12296, 328, 64, 4), (705, 12296, 136, 32, 2)])
+def test_linear_on_two_slices(qt, M, N, K, G, bits):
+    test_linear_of_a_hundred_rows(qt, M, N, K, G, bits)
