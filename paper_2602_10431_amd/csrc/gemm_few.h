@@ -39,7 +39,7 @@ struct FewDev {
     FewPrologue pro;
 };
 
-template <int BITS, int GPT, bool SWIGLU, int NF, int NP, int NK, int MR, int PRO, bool ACT_BF16>
+template <int BITS, int GPT, bool SWIGLU, int NF, int NP, int NK, int MR, int PRO, bool ACT_BF16, bool NT_LOADS>
 __global__ void __launch_bounds__(NP * NK * 64)
 gemm_few_kernel(FewDev a) {
     using WB = WBits<BITS>;
@@ -133,7 +133,7 @@ gemm_few_kernel(FewDev a) {
         const int kt = min(2 * min(step, last) + th, p.KT - 1);
 #pragma unroll
         for (int fn = 0; fn < NF; ++fn) {
-            w[fn] = WB::load_lane(bptr[fn] + static_cast<size_t>(kt) * (64 * WB::kLaneBytes));
+            w[fn] = WB::template load_lane<NT_LOADS>(bptr[fn] + static_cast<size_t>(kt) * (64 * WB::kLaneBytes));
 #pragma unroll
             for (int g = 0; g < GPT; ++g) sz[fn][g] = sptr[fn][static_cast<size_t>((kt * 64 + g * 32) >> p.gshift) * npad[fn]];
         }
@@ -348,7 +348,21 @@ gemm_few_kernel(FewDev a) {
     }
 }
 
-template <int BITS, int GPT, bool SWIGLU, int NF, int NP, int NK, int MR, int PRO>
+// Layer calls of at most four rows, weights of at least 12 MB: non-temporal loads.  They are read once per call, and as ordinary loads the layers
+// of a step push each other out of the memory-side cache (256 MB) before any is used again.  Whole layer, one token unless stated,
+// us, ordinary / non-temporal, over 3, 6 and 20 layers' weights in rotation: 7B shape 53.7 / 51.2, 54.6 / 51.4, 54.6 / 53.5; 8B-GQA 52.2 /
+// 50.1, 52.7 / 50.3, 52.8 / 52.3, 4 tokens 58.6 / 56.6, 59.2 / 56.7, 59.3 / 58.9; 13B, 2 tokens 67.8 / 65.9, 67.9 / 65.6, 68.0 / 65.8.
+// What fits that cache together is better left there: smaller layers (hidden 2048, 3 layers 32.4 / 33.9, 24 layers 36.5 / 34.4; 2-bit
+// 7B 47.0 / 47.9, 51.2 / 48.1, 51.9 / 51.6) and linears called by themselves (4096 x 14336, 3 rows 8.2 / 9.8, 8.2 / 10.1, 10.6 / 10.2).
+// With 8 rows the 7B layer is level at 24 layers (66.5 / 66.8).
+static bool few_streams(const GemmDev& d) {
+    if (!d.in_layer || d.bits != 4) return false;
+    size_t bytes = 0;
+    for (int i = 0; i < d.n_w; ++i) bytes += static_cast<size_t>(d.NF[i]) * d.KT * 64 * (4 * d.bits);
+    return bytes >= (12u << 20);
+}
+
+template <int BITS, int GPT, bool SWIGLU, int NF, int NP, int NK, int MR, int PRO, bool NT_LOADS = false>
 static hipError_t few_launch(FewDev& a, int frags, hipStream_t stream) {
     constexpr int NW = NP * NK, GROUP = NP * (SWIGLU ? 1 : NF);
     a.g.tiles_n = (frags + GROUP - 1) / GROUP;
@@ -356,10 +370,10 @@ static hipError_t few_launch(FewDev& a, int frags, hipStream_t stream) {
     const size_t rows = PRO != PRO_NONE ? static_cast<size_t>(a.g.M_max) * (a.g.K + 8) * 2 : static_cast<size_t>(NW) * MR * 136 * 2;
     const size_t lds = std::max<size_t>(NW * NF * 1024, rows);
     if (PRO != PRO_NONE && a.pro.bf16) {
-        auto k = gemm_few_kernel<BITS, GPT, SWIGLU, NF, NP, NK, MR, PRO, PRO != PRO_NONE>;
+        auto k = gemm_few_kernel<BITS, GPT, SWIGLU, NF, NP, NK, MR, PRO, PRO != PRO_NONE, NT_LOADS>;
         hipLaunchKernelGGL(k, grid, block, lds, stream, a);
     } else {
-        auto k = gemm_few_kernel<BITS, GPT, SWIGLU, NF, NP, NK, MR, PRO, false>;
+        auto k = gemm_few_kernel<BITS, GPT, SWIGLU, NF, NP, NK, MR, PRO, false, NT_LOADS>;
         hipLaunchKernelGGL(k, grid, block, lds, stream, a);
     }
     return hipGetLastError();
@@ -368,7 +382,10 @@ static hipError_t few_launch(FewDev& a, int frags, hipStream_t stream) {
 template <int BITS, int GPT, bool SWIGLU, int NF, int NP, int NK>
 static hipError_t few_rows(FewDev& a, int frags, hipStream_t stream) {
     constexpr int PRO = SWIGLU ? PRO_NORM : PRO_SELECT;           // gate/up follows RMSNorm 2, q|k|v the selection
-    if (a.pro.h || a.pro.x) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO>(a, frags, stream);
+    const bool nt = few_streams(a.g);
+    if (a.pro.h || a.pro.x) return nt ? few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO, BITS == 4>(a, frags, stream)
+                                      : few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO>(a, frags, stream);
+    if (!SWIGLU && nt && a.g.M_max <= 4) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO_NONE, BITS == 4 && !SWIGLU>(a, frags, stream);
     if (a.g.M_max <= 4) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO_NONE>(a, frags, stream);
     if (a.g.M_max <= 8) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 8, PRO_NONE>(a, frags, stream);
     return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 16, PRO_NONE>(a, frags, stream);

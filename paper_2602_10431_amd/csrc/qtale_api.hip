@@ -238,7 +238,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     }
     const int qkv_w = (nh + 2 * nkv) * d;
     GemmArgs qg{};
-    qg.A = ws.nbuf; qg.count = count; qg.M_max = M_max; qg.rows_exact = ratio_mode; qg.K = H; qg.group = c->group; qg.bits = lbits; qg.n_w = 3;
+    qg.A = ws.nbuf; qg.count = count; qg.M_max = M_max; qg.rows_exact = ratio_mode; qg.in_layer = 1; qg.K = H; qg.group = c->group; qg.bits = lbits; qg.n_w = 3;
     qg.w[0] = {w->q.prepacked, w->q.N, w->q.K};
     qg.w[1] = {w->k.prepacked, w->k.N, w->k.K};
     qg.w[2] = {w->v.prepacked, w->v.N, w->v.K};
@@ -330,7 +330,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     {
         Prof pr(ctx, stream, 6);
         GemmArgs g{};
-        g.A = ws.attn; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.K = nh * d; g.group = c->group; g.bits = lbits; g.n_w = 1;
+        g.A = ws.attn; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.in_layer = 1; g.K = nh * d; g.group = c->group; g.bits = lbits; g.n_w = 1;
         g.w[0] = {w->o.prepacked, w->o.N, w->o.K};
         g.epilogue = EPI_RESID_F32; g.out = ws.h; g.ldo = H; g.resid = x; g.idx = ws.idx; g.bf16 = bf16;
         g.part = o_part; g.part_floats = o_floats; g.n_parts = &o_parts;
@@ -347,7 +347,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     {
         Prof pr(ctx, stream, 8);
         GemmArgs g{};
-        g.A = ws.nbuf; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.K = H; g.group = c->group; g.bits = lbits; g.n_w = 2;
+        g.A = ws.nbuf; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.in_layer = 1; g.K = H; g.group = c->group; g.bits = lbits; g.n_w = 2;
         g.w[0] = {w->gate.prepacked, w->gate.N, w->gate.K};
         g.w[1] = {w->up.prepacked, w->up.N, w->up.K};
         g.epilogue = EPI_SWIGLU_F16; g.out = ws.act; g.ldo = I;
@@ -360,7 +360,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     {
         Prof pr(ctx, stream, 9);
         GemmArgs g{};
-        g.A = ws.act; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.K = I; g.group = c->group; g.bits = lbits; g.n_w = 1;
+        g.A = ws.act; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.in_layer = 1; g.K = I; g.group = c->group; g.bits = lbits; g.n_w = 1;
         g.w[0] = {w->down.prepacked, w->down.N, w->down.K};
         g.epilogue = EPI_RESID_SCATTER; g.out = x; g.ldo = H; g.resid = ws.h; g.idx = ws.idx; g.bf16 = bf16;
         int d_parts = 0;
