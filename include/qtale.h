@@ -260,7 +260,8 @@ void qtale_graph_destroy(qtale_graph* graph);
  * Classes: 0 router, 1 select, 2 norm1, 3 qkv gemm, 4 rope+append, 5 attention, 6 o gemm, 7 norm2,
  * 8 gate/up gemm, 9 down gemm.  Small calls fuse some of them, and a fused step is counted in the class of the launch that
  * does it: up to 256 tokens class 2 is part of 1; with a cache and few new tokens per sequence (decode) class 4 is part
- * of 5, so that a bandwidth made from class 5 includes the rotation and the append; with at most four tokens 0 (unless the
+ * of 5, so that a bandwidth made from class 5 includes the rotation and the append (otherwise 4 also builds the work list of 5);
+ * with at most four tokens 0 (unless the
  * router is an MLP), 1 and 2 are part of 3, and 7 is part of 8.  Inside a stack a decode-sized layer's class 9 also scores the
  * next layer's tokens (its class 0).  Profiling adds event overhead; leave it off when timing whole steps. */
 enum { QTALE_PROF_CLASSES = 10 };

@@ -12,8 +12,9 @@
 //     one query column (softmax statistics are per lane), and the probabilities, still in the MFMA
 //     accumulator layout, are fed straight back as the B operand of O^T = V^T P^T; V is transposed on
 //     its way into LDS.
-//   * decode (grouped queries: attention_gqa.hip): one workgroup per (executed row, kv head); lanes stream K and V rows with 16-byte loads,
-//     16 (or 8) lanes per key, online softmax per lane group, merged at the end.  Bandwidth-bound.  It also
+//     The keys of few query tiles are cut into ranges (attention_prefill_plan).
+//   * decode (one query head per kv head; grouped queries: attention_gqa.hip): one workgroup per (executed row, head); lanes stream
+//     K and V rows with 16-byte loads, 16 (or 8) lanes per key, online softmax per lane group, merged at the end.  Bandwidth-bound.  It also
 //     rotates the query and the call's own keys (table of the normalising kernel) and appends the new row, unless a call
 //     has a long new part (attention_rotates); with
 //     few rows the cached keys are cut into ranges and the workgroup that arrives last combines them.
@@ -655,7 +656,7 @@ bool attention_rotates(int T, int B, int rep, int hidden, int head_dim) {
 }
 
 // Few rows: cut the cached keys.  With the ranges' length set on the device they are equally long over all rows and fill the chip
-// once (`target`: what the split kernel's registers let a CU hold); sequences of different lengths cut into equally many
+// once (`target`: about what a CU holds; grouped queries take the same time with two to six per CU); sequences of different lengths cut into equally many
 // ranges left the longest ones running alone (20 rows x 8 kv heads x 1500 to 4500 keys: 66 -> 59 us).  Without it (calls of more
 // than 256 tokens) every row is cut so that about four workgroups per CU stream.
 int attention_splits(int max_rows, int nh, int nkv, int cap, bool device_chunk, int* target) {

@@ -46,7 +46,7 @@ struct Workspace {
     void* nbuf;            // [T][H] fp16
     void* qkv;             // [T][(nh+2nkv)d] fp16
     void* attn;            // [T][nh d] fp16
-    float* h;              // [T][H] fp32
+    float* h;              // [T][H] fp32 (h to gemm_part adjoin: key ranges of prefill attention)
     void* act;             // [T][I] fp16
     float* attn_part;      // [min(T, kAttnSplitRows)][nh][kAttnSplitMax][d + 2] fp32: key-range partials of decode attention; K parts above 64 rows
     float* gemm_part;      // [kGemmPartMax][min(T, kGemmPartRows)][H] fp32: K-part partial tiles of the decode o-/down-proj
