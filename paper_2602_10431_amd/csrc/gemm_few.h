@@ -348,15 +348,17 @@ gemm_few_kernel(FewDev a) {
     }
 }
 
-// Layer calls of at most four rows, weights of at least 12 MB: non-temporal loads.  They are read once per call, and as ordinary loads the layers
+// Layer calls of at most eight rows, weights of at least 12 MB: non-temporal loads.  They are read once per call, and as ordinary loads the layers
 // of a step push each other out of the memory-side cache (256 MB) before any is used again.  Whole layer, one token unless stated,
 // us, ordinary / non-temporal, over 3, 6 and 20 layers' weights in rotation: 7B shape 53.7 / 51.2, 54.6 / 51.4, 54.6 / 53.5; 8B-GQA 52.2 /
 // 50.1, 52.7 / 50.3, 52.8 / 52.3, 4 tokens 58.6 / 56.6, 59.2 / 56.7, 59.3 / 58.9; 13B, 2 tokens 67.8 / 65.9, 67.9 / 65.6, 68.0 / 65.8.
 // What fits that cache together is better left there: smaller layers (hidden 2048, 3 layers 32.4 / 33.9, 24 layers 36.5 / 34.4; 2-bit
 // 7B 47.0 / 47.9, 51.2 / 48.1, 51.9 / 51.6) and linears called by themselves (4096 x 14336, 3 rows 8.2 / 9.8, 8.2 / 10.1, 10.6 / 10.2).
-// With 8 rows the 7B layer is level at 24 layers (66.5 / 66.8).
+// 5 to 8 rows: 7B, 8 rows 63.2 / 60.9, 65.5 / 61.1, 68.0 / 64.3; 8B-GQA, 8 rows 67.0 / 63.0, 67.6 / 63.3, 67.8 / 67.7; 13B, 6 rows 82.2 /
+// 77.8, 82.8 / 78.0, 82.0 / 78.8; four 8B-GQA layers of a stack 290.0 / 290.1.  16 rows: 8B-GQA 77.9 / 73.9, 79.1 / 74.3, 79.1 / 80.5, so there the
+// ordinary loads stay.
 static bool few_streams(const GemmDev& d) {
-    if (!d.in_layer || d.bits != 4) return false;
+    if (!d.in_layer || d.bits != 4 || d.M_max > 8) return false;
     size_t bytes = 0;
     for (int i = 0; i < d.n_w; ++i) bytes += static_cast<size_t>(d.NF[i]) * d.KT * 64 * (4 * d.bits);
     return bytes >= (12u << 20);
@@ -385,7 +387,8 @@ static hipError_t few_rows(FewDev& a, int frags, hipStream_t stream) {
     const bool nt = few_streams(a.g);
     if (a.pro.h || a.pro.x) return nt ? few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO, BITS == 4>(a, frags, stream)
                                       : few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO>(a, frags, stream);
-    if (!SWIGLU && nt && a.g.M_max <= 4) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO_NONE, BITS == 4 && !SWIGLU>(a, frags, stream);
+    if (nt && a.g.M_max <= 4) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO_NONE, BITS == 4>(a, frags, stream);
+    if (nt) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 8, PRO_NONE, BITS == 4>(a, frags, stream);
     if (a.g.M_max <= 4) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 4, PRO_NONE>(a, frags, stream);
     if (a.g.M_max <= 8) return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 8, PRO_NONE>(a, frags, stream);
     return few_launch<BITS, GPT, SWIGLU, NF, NP, NK, 16, PRO_NONE>(a, frags, stream);
