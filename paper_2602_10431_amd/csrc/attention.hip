@@ -113,9 +113,10 @@ flash_prefill_kernel(AttnDev p) {
 
     // this lane's query (column of S^T): local index inside the sequence, clamped to a valid row
     const int q_local = q_lo + min(wave * 32 + l32, q_cnt - 1);
-    const int limit = base_len + q_local + 1;                    // keys [0, limit) are visible
-    const int wave_hi = base_len + q_lo + min(wave * 32 + 31, q_cnt - 1) + 1;   // largest limit in the wave
-    const int wave_lo = base_len + q_lo + min(wave * 32, q_cnt - 1) + 1;        // smallest limit in the wave
+    // keys [0, limit) are visible: those up to its own, of which a full cache may have dropped the last
+    const int limit = min(base_len + q_local + 1, n_keys);
+    const int wave_hi = min(base_len + q_lo + min(wave * 32 + 31, q_cnt - 1) + 1, n_keys);   // largest limit in the wave
+    const int wave_lo = min(base_len + q_lo + min(wave * 32, q_cnt - 1) + 1, n_keys);        // smallest limit in the wave
     const half_t* qrow = p.qkv + static_cast<size_t>(row_begin + q_local) * p.width + h * D;
     // The queries stay as stored; the factor log2(e)/sqrt(d) is applied in fp32 inside the exponent's fused
     // multiply-add (folding it into the fp16 queries would round it, and every product, to 11 bits: an error in
@@ -265,8 +266,6 @@ flash_prefill_kernel(AttnDev p) {
                     pv[0] = __builtin_amdgcn_exp2f(fmaf(st[kf][r], sc, -m_new));
                     pv[1] = __builtin_amdgcn_exp2f(fmaf(st[kf][r + 1], sc, -m_new));
                     const half2_t ph = __builtin_convertvector(pv, half2_t);   // one packed conversion per pair
-                    // the denominator adds the probabilities as the product sees them: their rounding cancels where one key
-                    // dominates, and a pair costs one instruction
                     psum = __builtin_amdgcn_fdot2(ph, half2_t{static_cast<half_t>(1.0f), static_cast<half_t>(1.0f)}, psum, false);
                     pf[kf * 2 + (r >> 3)][r & 7] = ph[0];
                     pf[kf * 2 + (r >> 3)][(r & 7) + 1] = ph[1];

@@ -1,10 +1,14 @@
 """GPU parity of prefill attention whose keys are cut into ranges (run with -m gpu): few query tiles, ranges that end inside a
 query tile's causal triangle, ranges without a visible key for some queries, one range and the most there are.  References and
 tolerances are those of the other GPU tests."""
+import numpy as np
 import pytest
+import torch
 
 import synth_inputs as si
-from tests.test_gpu_layer import _cache_case, _check_layer
+from oracle import qtale_oracle as orc
+from tests.helpers import cfg_dict, check_parity, oracle_layer, to_f64
+from tests.test_gpu_layer import _cache_case, _check_layer, _run_layer
 
 pytestmark = pytest.mark.gpu
 
@@ -33,24 +37,42 @@ def test_prompts_without_a_cache(qt, d, mode, val):
     _check_layer(qt, shape, 1100, [1000, 0, 100], mode, val, seed=820 + d, std=0.08, starts=[0, 5, 11])
 
 
+def _on_a_full_cache(x, p, cfg, positions, k, v):
+    """The oracle's layer for rows that no cache takes in any more: each attends to the entries k, v [cap, n_kv * d] and not to itself."""
+    nh, nkv, d = cfg["n_heads"], cfg["n_kv_heads"], cfg["head_dim"]
+    q = orc.rmsnorm(x, p.g1, cfg["rms_eps"]) @ p.Wq.T
+    attn = np.zeros((len(x), nh * d))
+    for i, pos in enumerate(positions):
+        qi = orc.rope(q[i], pos, d, cfg["rope_base"])
+        for h in range(nh):
+            hk = h // (nh // nkv)
+            s = k[:, hk * d:(hk + 1) * d] @ qi[h * d:(h + 1) * d] / np.sqrt(d)
+            w = np.exp(s - s.max())
+            attn[i, h * d:(h + 1) * d] = (w / w.sum()) @ v[:, hk * d:(hk + 1) * d]
+    h1 = x + attn @ p.Wo.T
+    n2 = orc.rmsnorm(h1, p.g2, cfg["rms_eps"])
+    return h1 + (orc.silu(n2 @ p.Wg.T) * (n2 @ p.Wu.T)) @ p.Wd.T
+
+
+# capacities that end inside a tile of 64 keys and at its end, keys not cut (up to 512 of them) and cut; no row, some rows and all rows fit
 @pytest.mark.parametrize("d", [64, 128])
-def test_a_cache_that_fills_up(qt, d):
-    # rows that do not fit are dropped: every query of the last tiles sees the same keys
-    import numpy as np
-    import torch
-    from oracle import qtale_oracle as orc
-    from tests.helpers import cfg_dict, check_parity, oracle_layer, to_f64
-    from tests.test_gpu_layer import _run_layer
+@pytest.mark.parametrize("cap,old,T", [(300, 250, 200), (320, 250, 200), (65, 0, 300), (300, 300, 20), (641, 600, 200), (704, 600, 200), (700, 500, 200), (1537, 1500, 140)])
+def test_a_cache_that_fills_up(qt, d, cap, old, T):
+    # rows that do not fit are dropped and attend to the entries that are there; the second sequence is not concerned
     shape = si.LayerShape(256, 4, 2, d, 688, 4, 32, "fp16")
-    cap, old, T = 700, 500, 200
     tensors = si.layer_tensors(shape, 0, 830, unit_gains=False, std=0.08)
-    x = si.hidden_states(shape, T, 830)
-    offs, pos = si.ragged_sequences([T], [old])
-    kc, vc = si.kv_cache(shape, 1, cap, 0, 830)
-    kv = qt.KVCache.from_token_major(kc.cuda(), vc.cuda(), torch.tensor([old], dtype=torch.int32).cuda(), shape.n_kv_heads)
+    lens, olds = [T, 30], [old, 10]
+    x = si.hidden_states(shape, T + 30, 830)
+    offs, pos = si.ragged_sequences(lens, olds)
+    kc, vc = si.kv_cache(shape, 2, cap, 0, 830)
+    kv = qt.KVCache.from_token_major(kc.cuda(), vc.cuda(), torch.tensor(olds, dtype=torch.int32).cuda(), shape.n_kv_heads)
     got, idx, _ = _run_layer(qt, shape, tensors, x, offs, pos, "ratio", 1.0, kv=kv)
+    assert np.array_equal(idx, np.arange(T + 30)) and kv.kv_len.tolist() == [min(old + T, cap), 40]
+    fit = min(T, cap - old)
+    kept = np.r_[0:fit, T:T + 30]
     p, _ = oracle_layer(shape, 0, 830, tensors=tensors)
-    want, widx, _ = orc.layer_forward(to_f64(x), p, cfg_dict(shape), offs.numpy(), pos.numpy(), "ratio", 1.0,
-                                      orc.KVCache(to_f64(kc), to_f64(vc), [old]))
-    assert np.array_equal(idx, widx) and int(kv.kv_len[0]) == cap
-    check_parity(orc.parity_error(to_f64(got), want), "fp16", ("full cache", d), hidden=shape.hidden)
+    okv = orc.KVCache(to_f64(kc), to_f64(vc), olds)
+    want = np.empty((T + 30, shape.hidden))
+    want[kept], _, _ = orc.layer_forward(to_f64(x)[kept], p, cfg_dict(shape), np.array([0, fit, fit + 30]), pos.numpy()[kept], "ratio", 1.0, okv)
+    want[fit:T] = _on_a_full_cache(to_f64(x)[fit:T], p, cfg_dict(shape), pos.numpy()[fit:T], okv.k[0, :cap], okv.v[0, :cap])
+    check_parity(orc.parity_error(to_f64(got), want), "fp16", ("full cache", d, cap, old, T), hidden=shape.hidden)
