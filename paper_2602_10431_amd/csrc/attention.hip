@@ -265,8 +265,8 @@ flash_prefill_kernel(AttnDev p) {
                     float2_t pv;
                     pv[0] = __builtin_amdgcn_exp2f(fmaf(st[kf][r], sc, -m_new));
                     pv[1] = __builtin_amdgcn_exp2f(fmaf(st[kf][r + 1], sc, -m_new));
+                    psum += pv[0] + pv[1];                           // in 32 bits
                     const half2_t ph = __builtin_convertvector(pv, half2_t);   // one packed conversion per pair
-                    psum = __builtin_amdgcn_fdot2(ph, half2_t{static_cast<half_t>(1.0f), static_cast<half_t>(1.0f)}, psum, false);
                     pf[kf * 2 + (r >> 3)][r & 7] = ph[0];
                     pf[kf * 2 + (r >> 3)][(r & 7) + 1] = ph[1];
                 }

@@ -76,3 +76,25 @@ def test_a_cache_that_fills_up(qt, d, cap, old, T):
     want[kept], _, _ = orc.layer_forward(to_f64(x)[kept], p, cfg_dict(shape), np.array([0, fit, fit + 30]), pos.numpy()[kept], "ratio", 1.0, okv)
     want[fit:T] = _on_a_full_cache(to_f64(x)[fit:T], p, cfg_dict(shape), pos.numpy()[fit:T], okv.k[0, :cap], okv.v[0, :cap])
     check_parity(orc.parity_error(to_f64(got), want), "fp16", ("full cache", d, cap, old, T), hidden=shape.hidden)
+
+
+@pytest.mark.parametrize("nkv,T", [(4, 9), (4, 4), (2, 4), (1, 4), (1, 9)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_many_small_probabilities_beside_a_large_one(qt, d, nkv, T):
+    # one cached key whose score is 10.4 above that of 3000 others: each of these weighs 2^-15 of it (below the smallest normal
+    # fp16) and together a tenth, of numerator and denominator.  Prefill (9 rows) and decode forms (4 rows), 1, 2 and 4 query heads per kv head
+    shape = si.LayerShape(256, 4, nkv, d, 688, 4, 32, "fp16")
+    tensors = si.layer_tensors(shape, 0, 840, unit_gains=False, std=0.08)
+    rep, n = 4 // nkv, 3000
+    tensors["q"] = tensors["q"].view(nkv, rep, d, 256)[:, :1].expand(nkv, rep, d, 256).reshape(4 * d, 256).contiguous()   # equal in a group
+    x = si.hidden_states(shape, 1, 840).expand(T, 256).contiguous()          # the same query in every row
+    offs, pos = torch.tensor([0, T], dtype=torch.int32), torch.full((T,), 3001, dtype=torch.int32)
+    p, _ = oracle_layer(shape, 0, 840, tensors=tensors)
+    q = orc.rope((orc.rmsnorm(to_f64(x[:1]), p.g1, shape.rms_eps) @ p.Wq.T)[0], 3001, d, shape.rope_base).reshape(nkv, rep, d)[:, 0]
+    big = q * (10.4 * np.sqrt(d) / (q * q).sum(axis=1, keepdims=True))
+    kc, vc = torch.zeros(1, n + 1 + T, nkv * d, dtype=torch.float16), torch.ones(1, n + 1 + T, nkv * d, dtype=torch.float16)
+    kc[0, 700], vc[0, 700] = torch.from_numpy(big.reshape(-1)).half(), -1.0
+    kv = qt.KVCache.from_token_major(kc.cuda(), vc.cuda(), torch.tensor([n + 1], dtype=torch.int32).cuda(), nkv)
+    got, _, _ = _run_layer(qt, shape, tensors, x, offs, pos, "ratio", 1.0, kv=kv)
+    want, _, _ = orc.layer_forward(to_f64(x), p, cfg_dict(shape), offs.numpy(), pos.numpy(), "ratio", 1.0, orc.KVCache(to_f64(kc), to_f64(vc), [n + 1]))
+    check_parity(orc.parity_error(to_f64(got), want), "fp16", ("small probabilities", d, nkv, T), hidden=shape.hidden)
