@@ -409,7 +409,7 @@ __device__ __forceinline__ float dot8(const half8_t& a, const half8_t& b) {
 // FUSED = false: rope_append_kernel has rotated and appended already, the queries are read as they are and all keys from the
 // cache (attention_rotates says when).
 template <int D, bool SPLIT, bool FUSED>
-__global__ void __launch_bounds__(256, SPLIT ? 1 : 8)
+__global__ void __launch_bounds__(256, SPLIT ? 5 : 8)
 attn_decode_kernel(AttnDev p) {
     constexpr int LPK = D / 8;            // lanes per key (each lane owns 8 of the D columns)
     constexpr int KPW = 64 / LPK;         // keys per wave per step
@@ -418,7 +418,8 @@ attn_decode_kernel(AttnDev p) {
     const int i = blockIdx.y;
     if (i >= *p.count) return;
     const int hk = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = lane % LPK, slot = lane / LPK;
 
     // This row's query, key and value and their rotation depend on nothing but i: they are requested first and arrive
@@ -449,6 +450,7 @@ attn_decode_kernel(AttnDev p) {
 
     const int b = p.row_seq[i];
     const int row_begin = p.cu_exec[b];
+    const bool once = p.cu_exec[b + 1] - row_begin == 1;         // no other row reads this sequence's keys
     const size_t head_off = (static_cast<size_t>(b) * p.nkv + hk) * p.cap * D;   // cache [B][n_kv_heads][cap][D]
     const half_t* kbase = p.k_cache + head_off;
     const half_t* vbase = p.v_cache + head_off;
@@ -471,7 +473,7 @@ attn_decode_kernel(AttnDev p) {
     half8_t kn[UNR], vn[UNR];
     const int last = max(key_hi - 1, 0);                         // an empty cache: slot 0, loaded and not used
     const int lane_key = wave * KPW + slot;
-    auto fetch = [&](int kb) {
+    auto fetch = [&](int kb, auto nt) {
         const int first = min(kb, last);
         // (scalar registers; as ordinary pointers they are folded into a 64-bit sum per load and lane)
         uint64_t ks = reinterpret_cast<uint64_t>(kbase + static_cast<size_t>(first) * D);
@@ -479,17 +481,22 @@ attn_decode_kernel(AttnDev p) {
         asm("" : "+s"(ks), "+s"(vs));
         using Bytes = const __attribute__((address_space(1))) char*;
         using Piece = const __attribute__((address_space(1))) half8_t*;
+        auto load = [&](auto nt) {
 #pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const uint32_t off = static_cast<uint32_t>(min(lane_key + u * step, last - first) * D + sub * 8) * 2u;
-            kn[u] = stream_load(reinterpret_cast<Piece>(reinterpret_cast<Bytes>(ks) + off));
-            vn[u] = stream_load(reinterpret_cast<Piece>(reinterpret_cast<Bytes>(vs) + off));
-        }
+            for (int u = 0; u < UNR; ++u) {
+                const uint32_t off = static_cast<uint32_t>(min(lane_key + u * step, last - first) * D + sub * 8) * 2u;
+                const Piece k = reinterpret_cast<Piece>(reinterpret_cast<Bytes>(ks) + off), v = reinterpret_cast<Piece>(reinterpret_cast<Bytes>(vs) + off);
+                kn[u] = nt.value ? stream_load(k) : *k;
+                vn[u] = nt.value ? stream_load(v) : *v;
+            }
+        };
+        if (SPLIT && once) keep_side([&] { load(std::true_type{}); });
+        else load(nt);
     };
     // Few workgroups (SPLIT): latency counts and registers do not, the stream starts before anything else is computed.  Many
     // workgroups: eight per CU (64 registers) stream at 6.0 TB/s, so the first request waits until the registers are free.
     if (SPLIT) {
-        fetch(key_lo);
+        fetch(key_lo, std::false_type{});
         __builtin_amdgcn_sched_barrier(0);
     }
 
@@ -541,42 +548,48 @@ attn_decode_kernel(AttnDev p) {
         }
     }
 
-    for (int kb = key_lo; kb < key_hi; kb += UNR * step) {     // trip count is uniform over the workgroup
-        const int k0 = kb + wave * KPW + slot;
-        half8_t kv[UNR], vv[UNR];
-        bool ok[UNR];
-        if (!SPLIT) {
-            fetch(kb);
-            __builtin_amdgcn_sched_barrier(0);                  // all eight loads before the first wait
+    // Without split keys two loops rather than a branch at the loads (32 x 4 rows on 4000 keys 658 and 668 us, in 64 registers either
+    // way); with split keys two loops take 126 registers and a branch 94, of which five workgroups fit a CU.
+    auto stream = [&](auto nt) {
+        for (int kb = key_lo; kb < key_hi; kb += UNR * step) { // trip count is uniform over the workgroup
+            const int k0 = kb + wave * KPW + slot;
+            half8_t kv[UNR], vv[UNR];
+            bool ok[UNR];
+            if (!SPLIT) {
+                fetch(kb, nt);
+                __builtin_amdgcn_sched_barrier(0);                  // all eight loads before the first wait
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                ok[u] = k0 + u * step < key_hi;
+                kv[u] = kn[u];
+                vv[u] = vn[u];
+            }
+            if (SPLIT) fetch(kb + UNR * step, nt);                 // past the end: one redundant, unused fetch
+            float s[UNR];
+            float mx = m_run;
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const float acc = key_group_sum<LPK>(dot8(qh, kv[u])) * p.scale_log2;
+                s[u] = ok[u] ? acc : kNegBig;
+                mx = fmaxf(mx, s[u]);
+            }
+            const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
+            m_run = mx;
+            l_run *= alpha;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] *= alpha;
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const float pv = ok[u] ? __builtin_amdgcn_exp2f(s[u] - mx) : 0.0f;
+                l_run += pv;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = fmaf(pv, static_cast<float>(vv[u][e]), o[e]);
+            }
         }
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            ok[u] = k0 + u * step < key_hi;
-            kv[u] = kn[u];
-            vv[u] = vn[u];
-        }
-        if (SPLIT) fetch(kb + UNR * step);                     // past the end: one redundant, unused fetch
-        float s[UNR];
-        float mx = m_run;
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const float acc = key_group_sum<LPK>(dot8(qh, kv[u])) * p.scale_log2;
-            s[u] = ok[u] ? acc : kNegBig;
-            mx = fmaxf(mx, s[u]);
-        }
-        const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
-        m_run = mx;
-        l_run *= alpha;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] *= alpha;
-#pragma unroll
-        for (int u = 0; u < UNR; ++u) {
-            const float pv = ok[u] ? __builtin_amdgcn_exp2f(s[u] - mx) : 0.0f;
-            l_run += pv;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = fmaf(pv, static_cast<float>(vv[u][e]), o[e]);
-        }
-    }
+    };
+    if (!SPLIT && once) stream(std::true_type{});
+    else stream(std::false_type{});
 
     // merge the key slots of a wave (lanes that own the same columns), then the four waves through LDS
     __shared__ float sm[4][D + 2];

@@ -91,6 +91,7 @@ attn_decode_gqa_kernel(AttnDev p) {
     }
     const int b = p.row_seq[i];
     const int row_begin = p.cu_exec[b];
+    const bool once = p.cu_exec[b + 1] - row_begin == 1;         // no other row reads this sequence's keys
     const size_t head_off = (static_cast<size_t>(b) * p.nkv + hk) * p.cap * D;   // cache [B][n_kv_heads][cap][D]
     const half_t* kbase = p.k_cache + head_off;
     const half_t* vbase = p.v_cache + head_off;
@@ -118,24 +119,33 @@ attn_decode_gqa_kernel(AttnDev p) {
     auto fetch_k = [&](int kb) {
         const uint64_t a = base_of(kbase, kb);
         const int room = last - min(kb, last);
+        auto load = [&](auto nt) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const uint32_t off = static_cast<uint32_t>(min(wave * kGqaKeys + 16 * u + c, room) * (2 * D) + 16 * g);
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t off = static_cast<uint32_t>(min(wave * kGqaKeys + 16 * u + c, room) * (2 * D) + 16 * g);
 #pragma unroll
-            for (int s = 0; s < S; ++s) {
-                const auto* src = reinterpret_cast<const __attribute__((address_space(1))) half8_t*>(reinterpret_cast<Bytes>(a) + off + 64 * s);
-                kn[u][s] = D == 64 ? stream_load(src) : *src;
+                for (int s = 0; s < S; ++s) {
+                    const auto* src = reinterpret_cast<const __attribute__((address_space(1))) half8_t*>(reinterpret_cast<Bytes>(a) + off + 64 * s);
+                    kn[u][s] = nt.value ? stream_load(src) : *src;
+                }
             }
-        }
+        };
+        if (D == 64 && once) keep_side([&] { load(std::true_type{}); });
+        else load(std::false_type{});
     };
     auto fetch_v = [&](int kb) {
         const uint64_t a = base_of(vbase, kb);
         const int room = last - min(kb, last);
+        auto load = [&](auto nt) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint32_t off = static_cast<uint32_t>(min(wave * kGqaKeys + 4 * g + (e < 4 ? e : 12 + e), room) * (2 * D) + 2 * F * c);
-            vn[e] = stream_load(reinterpret_cast<const __attribute__((address_space(1))) VPiece*>(reinterpret_cast<Bytes>(a) + off));
-        }
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t off = static_cast<uint32_t>(min(wave * kGqaKeys + 4 * g + (e < 4 ? e : 12 + e), room) * (2 * D) + 2 * F * c);
+                const auto* src = reinterpret_cast<const __attribute__((address_space(1))) VPiece*>(reinterpret_cast<Bytes>(a) + off);
+                vn[e] = nt.value ? stream_load(src) : *src;
+            }
+        };
+        if (once) keep_side([&] { load(std::true_type{}); });
+        else load(std::false_type{});
     };
     const bool new_keys = FUSED && (!SPLIT || blockIdx.z == 0);   // this workgroup also takes the call's own keys
     if (new_keys && wave == 0 && own < n_new) {

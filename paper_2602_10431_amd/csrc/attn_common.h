@@ -34,11 +34,24 @@ struct AttnDev {
 __device__ __forceinline__ void agent_store(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float agent_load(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// A cached key or value is read once per call: loaded as non-temporal it does not turn over the L2 on its way.  (One query head
-// per kv head, 64 rows x 32 heads x 2048 keys, 27 GB of caches in rotation so that nothing stays in the memory-side cache: layer
-// 449.5 -> 413.6 us, 6.0 -> 6.6 TB/s in this kernel; 128 rows of the 13B shape 536 -> 493; 8 rows x 2000 keys 107 -> 100.)
+// A cached key or value of a sequence with one executed row is read once per call: loaded as non-temporal it does not turn over the L2
+// on its way.  (One query head per kv head, 64 rows x 32 heads x 2048 keys, 27 GB of caches in rotation so that nothing stays in the
+// memory-side cache: layer 449.5 -> 413.6 us, 6.0 -> 6.6 TB/s in this kernel; 128 rows of the 13B shape 536 -> 493; 8 rows x 2000 keys
+// 107 -> 100.)  The rows of a longer new part read the same keys again, which the L2 serves: ordinary loads there.  Layers, us, all
+// non-temporal / by the sequence's rows / all ordinary: 7B shape 16 x 4 rows on 2000 keys 294 / 239 / 237, 32 x 4 on 4000 1020 / 658 / 651,
+// 31 x 1 + 65 on 1000 264 / 233 / 243, one sequence of 64 beside idle ones on 4000 426 / 271 / 271; four query heads per kv head,
+// 32 x 4 on 4000 320 / 303 / 302, 31 x 1 on 100 + 65 on 8000 367 / 342 / 349.
 template <class T>
 __device__ __forceinline__ T stream_load(const __attribute__((address_space(1))) T* p) { return __builtin_nontemporal_load(p); }
+
+// One side of a branch whose other side makes the same loads as ordinary ones: without something of its own on either end the compiler
+// makes one of both, and ordinary.
+template <class F>
+__device__ __forceinline__ void keep_side(F&& f) {
+    __builtin_amdgcn_sched_barrier(0);
+    f();
+    __builtin_amdgcn_sched_barrier(0);
+}
 
 // The cached keys of a (row, kv head) that this workgroup streams.  Without a split all of them.
 struct KeyRange {

@@ -36,3 +36,14 @@ def test_new_parts_around_the_steps(qt, rep, d, n):
     lens = [n, 1, n, 1] + [0] * 40
     old = [0, 130, 127, 0] + [3] * 40
     _cache_case(qt, shape, lens, old, old, 192, 720 + n, 1.0)
+
+
+@pytest.mark.parametrize("rep", [1, 2, 4])
+@pytest.mark.parametrize("d", [64, 128])
+def test_sequences_of_one_and_of_several_rows_in_one_call(qt, rep, d):
+    # the cached keys of the former are read once per call, those of the latter again for each row: two ways to load them
+    shape = si.LayerShape(256, 2 * rep, 2, d, 128, 4, 32, "fp16")
+    lens, old = [1, 3, 1, 4, 0, 2, 1, 1], [130, 257, 640, 64, 9, 511, 0, 300]
+    _cache_case(qt, shape, lens, old, old, 645, 740 + rep, 1.0)                      # few rows: keys split
+    lens, old = [1, 3] * 35, (EDGES * 3)[:70]
+    _cache_case(qt, shape, lens, old, old, 645, 750 + rep, 1.0)                      # more than 128 rows: not split
