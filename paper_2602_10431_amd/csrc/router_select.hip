@@ -205,10 +205,11 @@ router_mlp_kernel(const uint16_t* __restrict__ x, int T, int H, const float* __r
         if (tid < kMlpTokens) {
 #pragma unroll
             for (int r = 0; r < kMlpUnits; ++r) {                // in unit order
-                const int unit = min(rg + r, R - 1);             // past R: the hidden value is 0
+                const int unit = min(rg + r, R - 1);
+                const bool live = rg + r < R;                    // past R 0 times 0: an infinite weight of the last unit stays out
                 const double u = act[r][tid];
-                le = fma(static_cast<double>(W2[unit]), u, le);
-                lb = fma(static_cast<double>(W2[R + unit]), u, lb);
+                le = fma(static_cast<double>(live ? W2[unit] : 0.0f), u, le);
+                lb = fma(static_cast<double>(live ? W2[R + unit] : 0.0f), u, lb);
             }
         }
         __syncthreads();                                         // act and part are rewritten by the next turn

@@ -226,6 +226,21 @@ def test_mlp_router_scores_are_bit_exact_on_both_sides_of_the_matrix_form(qt, T,
     test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype)
 
 
+@pytest.mark.parametrize("T", [512, 513])
+@pytest.mark.parametrize("R", [3, 5, 16, 17, 30])
+def test_mlp_router_with_an_infinite_second_layer_weight(qt, T, R):
+    # the last unit's weight for the execute logit is infinite: +inf where the unit is live (0 times inf elsewhere, NaN in the oracle too)
+    shape = si.LayerShape(64, 1, 1, 64, 64, 4, 32, "fp16")
+    x = si.hidden_states(shape, T, 90 + R)
+    W1, b1, W2, b2 = _mlp_router(64, R, 90 + R)
+    W2[0, R - 1] = float("inf")
+    z = qt.qtale_router_mlp_scores(x.cuda(), W1.cuda(), b1.cuda(), W2.cuda(), b2.cuda())
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        want = orc.router_scores_mlp(x.to(torch.float64).numpy(), W1.numpy(), b1.numpy(), W2.numpy(), b2.numpy())
+    assert np.isinf(want).any() and np.array_equal(z.cpu().numpy(), want, equal_nan=True)
+
+
 @pytest.mark.parametrize("K,G,bits", [(40, 32, 4), (72, 64, 3), (264, 128, 2), (320, 32, 3), (384, 128, 4), (456, 64, 2)])
 def test_large_tile_gemm_short_and_ragged_k(qt, K, G, bits):
     # 2600 rows x 2048 columns is past the 64-row-tile regime, so these run the 128 x 256 tiles: one to eight
