@@ -157,6 +157,7 @@ router_mlp_kernel(const uint16_t* __restrict__ x, int T, int H, const float* __r
     typedef double double4_t __attribute__((ext_vector_type(4)));
     __shared__ double part[kMlpWaves][kMlpUnits * kMlpTokens];
     __shared__ double act[kMlpUnits][kMlpTokens];
+    __shared__ double w2[2][kMlpUnits];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = lane & 15, g = lane >> 4;
     const int t0 = blockIdx.x * kMlpTokens;
@@ -200,21 +201,136 @@ router_mlp_kernel(const uint16_t* __restrict__ x, int T, int H, const float* __r
             for (int w = 0; w < kMlpWaves; ++w) sum += part[w][tid];
             const int unit = rg + tid / kMlpTokens;
             act[tid / kMlpTokens][tid % kMlpTokens] = unit < R ? fmax(sum + static_cast<double>(b1[unit]), 0.0) : 0.0;
+        } else if (tid < kMlpUnits * kMlpTokens + 2 * kMlpUnits) {
+            const int r = tid % kMlpUnits, o = (tid - kMlpUnits * kMlpTokens) / kMlpUnits;
+            w2[o][r] = rg + r < R ? static_cast<double>(W2[o * R + rg + r]) : 0.0;   // past R 0 times 0: an infinite weight of the last unit stays out
         }
         __syncthreads();
         if (tid < kMlpTokens) {
 #pragma unroll
             for (int r = 0; r < kMlpUnits; ++r) {                // in unit order
-                const int unit = min(rg + r, R - 1);
-                const bool live = rg + r < R;                    // past R 0 times 0: an infinite weight of the last unit stays out
                 const double u = act[r][tid];
-                le = fma(static_cast<double>(live ? W2[unit] : 0.0f), u, le);
-                lb = fma(static_cast<double>(live ? W2[R + unit] : 0.0f), u, lb);
+                le = fma(w2[0][r], u, le);
+                lb = fma(w2[1][r], u, lb);
             }
         }
         __syncthreads();                                         // act and part are rewritten by the next turn
     }
     if (tid < kMlpTokens && t0 + tid < T) z[t0 + tid] = static_cast<float>((le + static_cast<double>(b2[0])) - (lb + static_cast<double>(b2[1])));
+}
+
+// A few hidden units: the 16 rows of the matrix instruction would be mostly idle, the vector ALUs do the first layer.  A workgroup owns
+// 4 x kMlpTW tokens (kMlpTW = 1, 2 or 4 per wave, by the number of tokens: launch_router_mlp) and walks H in chunks of 512 columns:
+// the W1 chunk of 4 hidden units is staged in LDS once per workgroup (two buffers, the next chunk's global loads are issued before the
+// current one is consumed, one barrier per chunk), a lane holds 8 consecutive columns of its tokens, and every staged weight is
+// converted to fp64 once and used for all of them (at four tokens 16 accumulators of two registers each per lane, two workgroups per
+// CU; 8 units per pass would spill).  A token's sums do not depend on kMlpTW.  The walk repeats per group of 4 units (x then comes from
+// L2).
+constexpr int kMlpRC = 4;         // hidden units per pass
+constexpr int kMlpKC = 512;       // columns per staged chunk
+constexpr int kMlpWL = (kMlpRC * kMlpKC / 4) / 256;   // float4 loads per thread per chunk
+
+template <bool BF16, int kMlpTW>
+__global__ void __launch_bounds__(256, 2)
+router_mlp_narrow_kernel(const uint16_t* __restrict__ x, int T, int H, const float* __restrict__ W1,
+                  const float* __restrict__ b1, const float* __restrict__ W2, const float* __restrict__ b2, int R,
+                  float* __restrict__ z) {
+    __shared__ __attribute__((aligned(16))) float Ws[2][kMlpRC][kMlpKC];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int t0 = blockIdx.x * (4 * kMlpTW) + wave * kMlpTW;
+    const uint16_t* xrow[kMlpTW];
+#pragma unroll
+    for (int i = 0; i < kMlpTW; ++i) xrow[i] = x + static_cast<size_t>(min(t0 + i, T - 1)) * H;
+
+    double le[kMlpTW], lb[kMlpTW];
+#pragma unroll
+    for (int i = 0; i < kMlpTW; ++i) { le[i] = 0.0; lb[i] = 0.0; }
+
+    float4 wreg[kMlpWL];
+    u32x4_t xreg[kMlpTW];
+    auto fetch = [&](int rc, int kb) {                         // global -> registers for chunk (rc, kb)
+#pragma unroll
+        for (int it = 0; it < kMlpWL; ++it) {
+            const int c = it * 256 + tid;
+            const int row = c / (kMlpKC / 4), col = (c % (kMlpKC / 4)) * 4;
+            wreg[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (rc + row < R && kb + col < H)
+                wreg[it] = *reinterpret_cast<const float4*>(W1 + static_cast<size_t>(rc + row) * H + kb + col);
+        }
+        const int k = kb + lane * 8;
+#pragma unroll
+        for (int i = 0; i < kMlpTW; ++i) {
+            xreg[i] = u32x4_t{0u, 0u, 0u, 0u};
+            if (k < H) xreg[i] = *reinterpret_cast<const u32x4_t*>(xrow[i] + k);
+        }
+    };
+
+    const int n_kb = (H + kMlpKC - 1) / kMlpKC;
+    const int n_rc = (R + kMlpRC - 1) / kMlpRC;
+    const int n_chunks = n_rc * n_kb;                          // walked as one sequence: rc-major, kb-minor
+    fetch(0, 0);
+    int buf = 0;
+    double acc[kMlpTW][kMlpRC];
+    for (int ch = 0; ch < n_chunks; ++ch) {
+        const int rc = (ch / n_kb) * kMlpRC, kbi = ch % n_kb;
+        if (kbi == 0) {
+#pragma unroll
+            for (int i = 0; i < kMlpTW; ++i)
+#pragma unroll
+                for (int r = 0; r < kMlpRC; ++r) acc[i][r] = 0.0;
+        }
+        // park this chunk's weights, expand this chunk's activations
+#pragma unroll
+        for (int it = 0; it < kMlpWL; ++it) {
+            const int c = it * 256 + tid;
+            *reinterpret_cast<float4*>(&Ws[buf][c / (kMlpKC / 4)][(c % (kMlpKC / 4)) * 4]) = wreg[it];
+        }
+        double xd[kMlpTW][8];
+#pragma unroll
+        for (int i = 0; i < kMlpTW; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                xd[i][2 * j] = static_cast<double>(act_to_float<BF16>(static_cast<uint16_t>(xreg[i][j] & 0xffffu)));
+                xd[i][2 * j + 1] = static_cast<double>(act_to_float<BF16>(static_cast<uint16_t>(xreg[i][j] >> 16)));
+            }
+        __syncthreads();          // chunk staged; the other buffer (read in the previous iteration) is free again
+        if (ch + 1 < n_chunks) fetch(((ch + 1) / n_kb) * kMlpRC, ((ch + 1) % n_kb) * kMlpKC);
+#pragma unroll
+        for (int r = 0; r < kMlpRC; ++r) {
+            const float4 w0 = *reinterpret_cast<const float4*>(&Ws[buf][r][lane * 8]);
+            const float4 w1 = *reinterpret_cast<const float4*>(&Ws[buf][r][lane * 8 + 4]);
+            const double wd[8] = {static_cast<double>(w0.x), static_cast<double>(w0.y), static_cast<double>(w0.z),
+                                  static_cast<double>(w0.w), static_cast<double>(w1.x), static_cast<double>(w1.y),
+                                  static_cast<double>(w1.z), static_cast<double>(w1.w)};
+#pragma unroll
+            for (int i = 0; i < kMlpTW; ++i)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[i][r] = fma(xd[i][j], wd[j], acc[i][r]);
+        }
+        buf ^= 1;
+        if (kbi == n_kb - 1) {
+            // hidden units of this pass: full sums, bias, ReLU, then their share of the two logits (in unit order)
+#pragma unroll
+            for (int r = 0; r < kMlpRC; ++r) {
+                const bool live = rc + r < R;
+                const double bias = live ? static_cast<double>(b1[rc + r]) : 0.0;
+                const double we = live ? static_cast<double>(W2[rc + r]) : 0.0;
+                const double wb = live ? static_cast<double>(W2[R + rc + r]) : 0.0;
+#pragma unroll
+                for (int i = 0; i < kMlpTW; ++i) {
+                    const double u = fmax(wave_sum(acc[i][r]) + bias, 0.0);
+                    le[i] = fma(we, u, le[i]);
+                    lb[i] = fma(wb, u, lb[i]);
+                }
+            }
+        }
+    }
+    if (lane == 0) {
+        const double be = static_cast<double>(b2[0]), bb = static_cast<double>(b2[1]);
+#pragma unroll
+        for (int i = 0; i < kMlpTW; ++i)
+            if (t0 + i < T) z[t0 + i] = static_cast<float>((le[i] + be) - (lb[i] + bb));
+    }
 }
 
 // Few tokens (decode steps): one workgroup per token, the 256 threads split H (8 columns each per 2048-column
@@ -290,6 +406,29 @@ hipError_t launch_router_mlp(const void* x, int bf16, int T, int H, const float*
     if (T <= 512) {
         if (bf16) hipLaunchKernelGGL(router_mlp_small_kernel<true>, dim3(T), dim3(256), 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
         else hipLaunchKernelGGL(router_mlp_small_kernel<false>, dim3(T), dim3(256), 0, stream, xp, T, H, W1, b1, W2, b2, R, z);
+        return hipGetLastError();
+    }
+    // Up to four hidden units, and up to eight where the matrix form's workgroups leave the chip half empty (few tokens) or it pays a
+    // whole turn of 2048 columns for a part of one.  us, 4 / 8 units, vector / matrix: H = 1024, 520 tokens 4.3 / 7.8,
+    // 6.8 / 7.9; 4096 6.2 / 8.1, 9.8 / 8.1; 12000 12.3 / 21.2, 22.1 / 21.4; H = 3072, 1000 tokens 6.8 / 13.8, 11.8 / 14.4; 2000 7.7 / 13.8,
+    // 13.5 / 14.4; 4500 13.2 / 26.5, 23.7 / 27.3; 12000 21.5 / 40.3, 39.0 / 41.1; H = 4096, 1000 8.0 / 14.2, 14.1 / 15.0; 1400 9.2 / 14.6,
+    // 16.6 / 15.0; 4500 16.4 / 27.8, 29.3 / 28.5; H = 5120, 1000 9.3 / 19.1, 16.7 / 20.0; 3000 13.6 / 19.8, 25.0 / 20.5; 6000 19.5 /
+    // 38.2, 35.2 / 39.8.  Nine units take a third pass: H = 4096, 600 tokens 19.9 / 14.9.
+    if (R <= 4 || (R <= 8 && (T <= 1024 || (H % 2048 > 0 && (T <= 2048 || T > 4096))))) {
+        auto go = [&](auto bf, auto tw) {
+            constexpr int TW = decltype(tw)::value;
+            hipLaunchKernelGGL((router_mlp_narrow_kernel<decltype(bf)::value, TW>), dim3((T + 4 * TW - 1) / (4 * TW)), dim3(256), 0, stream, xp, T, H, W1,
+                               b1, W2, b2, R, z);
+        };
+        // kMlpTW tokens per wave: four reuse every converted weight four times, but 16 tokens per workgroup need 16 tokens per CU; with
+        // fewer tokens the workgroups get smaller until they number about two per CU
+        auto by_tokens = [&](auto bf) {
+            if (T > 4096) go(bf, std::integral_constant<int, 4>{});
+            else if (T > 2048) go(bf, std::integral_constant<int, 2>{});
+            else go(bf, std::integral_constant<int, 1>{});
+        };
+        if (bf16) by_tokens(std::true_type{});
+        else by_tokens(std::false_type{});
         return hipGetLastError();
     }
     const dim3 grid((T + kMlpTokens - 1) / kMlpTokens), block(kMlpWaves * 64);

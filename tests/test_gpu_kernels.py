@@ -214,7 +214,8 @@ def test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype):
 @pytest.mark.parametrize("T", [1023, 2048, 2049, 4095, 4096, 4097, 5003])
 @pytest.mark.parametrize("H,R,dtype", [(72, 5, "fp16"), (520, 4, "bf16")])
 def test_mlp_router_scores_are_bit_exact_in_every_token_form(qt, T, H, R, dtype):
-    # one, two (above 2048 tokens) and four (above 4096) tokens per wave, at the edges and with ragged last workgroups
+    # four units: one, two (above 2048 tokens) and four (above 4096) tokens per wave, at the edges and with ragged last workgroups;
+    # five: the matrix instruction from 2049 to 4096 tokens
     test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype)
 
 
@@ -226,7 +227,14 @@ def test_mlp_router_scores_are_bit_exact_on_both_sides_of_the_matrix_form(qt, T,
     test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype)
 
 
-@pytest.mark.parametrize("T", [512, 513])
+@pytest.mark.parametrize("T", [513, 1024, 1025, 2048, 2049, 4097])
+@pytest.mark.parametrize("H,R,dtype", [(2048, 8, "fp16"), (264, 8, "bf16"), (2056, 9, "bf16"), (520, 3, "fp16")])
+def test_mlp_router_scores_are_bit_exact_where_few_units_change_form(qt, T, H, R, dtype):
+    # up to four units on the vector ALUs, five to eight by tokens and columns, nine and more on the matrix instruction
+    test_mlp_router_scores_are_bit_exact(qt, T, H, R, dtype)
+
+
+@pytest.mark.parametrize("T", [512, 513, 1100])
 @pytest.mark.parametrize("R", [3, 5, 16, 17, 30])
 def test_mlp_router_with_an_infinite_second_layer_weight(qt, T, R):
     # the last unit's weight for the execute logit is infinite: +inf where the unit is live (0 times inf elsewhere, NaN in the oracle too)
