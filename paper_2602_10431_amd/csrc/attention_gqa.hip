@@ -18,11 +18,15 @@
 //     reference point of the exponentials is at most 12 log2 units below the largest score and follows lazily, so the rest is
 //     never far below fp16's range: what is lost is under 2^-25 against sums of 2^8 and more;
 //   * a step's keys are requested again as soon as the scores are formed, its values as soon as they are consumed: 16 KB per
-//     wave in flight with one register set, three waves per SIMD.
+//     wave in flight with one register set, three waves per SIMD (four with 64-wide heads).  A wave's last step requests nothing
+//     and a wave without cached keys makes no step: short caches are bound by the launch of many workgroups.
 // Kernel time, us, vector ALUs / matrix cores (plain loads) and the layer's time / with non-temporal loads: 128-wide heads, 4 per
 // kv head: 16 rows x 1000 keys 22.9 / 19.7, 64 x 2048 99 / 95, layer 194 / 183, 64 x 1024..3072 122 / 109, 128 x 500..1500 118 / 102;
 // 64-wide: 8 x 750..2250 15 / 11, 20 x 3000 30.6 / 26, 64 x 2048 54 / 50, layer 109 / 98.  What bounds it now is the stream, and
-// with few rows the chain row -> sequence -> length in front of it and the combination of the ranges behind it.
+// with few rows the chain row -> sequence -> length in front of it and the combination of the ranges behind it.  Short caches,
+// layers of hidden size 1024 with 32 heads, us, vector ALUs / every wave stepping and requesting past the end / now: 128-wide, 2 per
+// kv head 128 rows x 50 keys 69.8 / 73.0 / 67.8, 256 x 50 88.4 / 99.3 / 88.9, 256 x 200 151 / 147 / 139; 4 per kv head 256 x 50 81.9 /
+// 82.0 / 76.3; 64-wide, 2 per kv head 256 x 50 80.2 / 80.3 / 72.8, 256 x 200 101.6 / 102.6 / 96.2, 20 x 3000 95 / 87 / 87.
 #include <algorithm>
 #include <type_traits>
 
@@ -35,7 +39,7 @@ constexpr int kGqaStep = 4 * kGqaKeys;           // per workgroup
 static_assert(kGqaStep == kAttnGqaStep, "the granularity of the key ranges");
 
 template <int D, int REP, bool SPLIT, bool FUSED>
-__global__ void __launch_bounds__(256, 3)
+__global__ void __launch_bounds__(256, D == 64 ? 4 : 3)
 attn_decode_gqa_kernel(AttnDev p) {
     constexpr int S = D / 32;                    // k-steps of the scores
     constexpr int F = D / 16;                    // output fragments, and columns of V per lane
@@ -79,15 +83,20 @@ attn_decode_gqa_kernel(AttnDev p) {
 #pragma unroll
     for (int s = 0; s < S; ++s) q[s] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + (c & (REP - 1))) * D + 32 * s + 8 * g);
     float s_own = 0.0f;
+    const bool new_keys = FUSED && (!SPLIT || blockIdx.z == 0);   // this workgroup also takes the call's own keys
     if (FUSED) {
         float2 cs[S / 2][8];
         load_cs(i, cs);
+        if (new_keys && wave == 0) {
 #pragma unroll
-        for (int s = 0; s < S; ++s) k_own[s] = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + 32 * s + 8 * g);
-        v_own = *reinterpret_cast<const VPiece*>(row_i + (p.nh + p.nkv + hk) * D + F * c);
+            for (int s = 0; s < S; ++s) k_own[s] = *reinterpret_cast<const half8_t*>(row_i + (p.nh + hk) * D + 32 * s + 8 * g);
+            v_own = *reinterpret_cast<const VPiece*>(row_i + (p.nh + p.nkv + hk) * D + F * c);
+        }
         rotate(q, cs);
-        rotate(k_own, cs);
-        s_own = scores(k_own)[0];                                // every row of K is this key
+        if (new_keys && wave == 0) {
+            rotate(k_own, cs);
+            s_own = scores(k_own)[0];                            // every row of K is this key
+        }
     }
     const int b = p.row_seq[i];
     const int row_begin = p.cu_exec[b];
@@ -102,52 +111,43 @@ attn_decode_gqa_kernel(AttnDev p) {
     const KeyRange range = decode_key_range<SPLIT>(p, n_cached, kGqaStep);
     if (SPLIT && range.none) return;
 
-    // Keys past the end of the range are clamped to its last one and masked.  Addresses are a uniform base that walks with the
-    // step plus a 32-bit lane offset inside it.
+    // kb: first key of a wave's step, inside the range.  Keys past the range's end are clamped to its last one and masked.  Addresses are
+    // a uniform base that walks with the step plus a 32-bit lane offset inside it.
     half8_t kn[2][S];
     VPiece vn[8];
-    const int last = max(range.hi - 1, 0);                       // an empty cache: slot 0, loaded and not used
+    const int last = range.hi - 1;
     using Bytes = const __attribute__((address_space(1))) char*;
     auto base_of = [&](const half_t* base, int kb) {
-        uint64_t a = reinterpret_cast<uint64_t>(base + static_cast<size_t>(min(kb, last)) * D);
+        uint64_t a = reinterpret_cast<uint64_t>(base + static_cast<size_t>(kb) * D);
         asm("" : "+s"(a));
         return a;
     };
-    // (Values, and the keys of 64-wide heads, as non-temporal loads.  The keys of 128-wide heads arrive a quarter of a row per
+    // (Values, and the keys of 64-wide heads, as non-temporal loads where nt says so.  The keys of 128-wide heads arrive a quarter of a row per
     // instruction and gain nothing or lose: 20 rows x 1500 to 4500 keys, layer 132 us with plain key loads, 135 without;
     // 64-wide heads 64 x 2048 104 and 98.)
-    auto fetch_k = [&](int kb) {
+    auto fetch_k = [&](int kb, auto nt) {
         const uint64_t a = base_of(kbase, kb);
-        const int room = last - min(kb, last);
-        auto load = [&](auto nt) {
+        const int room = last - kb;
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const uint32_t off = static_cast<uint32_t>(min(wave * kGqaKeys + 16 * u + c, room) * (2 * D) + 16 * g);
+        for (int u = 0; u < 2; ++u) {
+            const uint32_t off = static_cast<uint32_t>(min(16 * u + c, room) * (2 * D) + 16 * g);
 #pragma unroll
-                for (int s = 0; s < S; ++s) {
-                    const auto* src = reinterpret_cast<const __attribute__((address_space(1))) half8_t*>(reinterpret_cast<Bytes>(a) + off + 64 * s);
-                    kn[u][s] = nt.value ? stream_load(src) : *src;
-                }
+            for (int s = 0; s < S; ++s) {
+                const auto* src = reinterpret_cast<const __attribute__((address_space(1))) half8_t*>(reinterpret_cast<Bytes>(a) + off + 64 * s);
+                kn[u][s] = D == 64 && nt.value ? stream_load(src) : *src;
             }
-        };
-        if (D == 64 && once) keep_side([&] { load(std::true_type{}); });
-        else load(std::false_type{});
+        }
     };
-    auto fetch_v = [&](int kb) {
+    auto fetch_v = [&](int kb, auto nt) {
         const uint64_t a = base_of(vbase, kb);
-        const int room = last - min(kb, last);
-        auto load = [&](auto nt) {
+        const int room = last - kb;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint32_t off = static_cast<uint32_t>(min(wave * kGqaKeys + 4 * g + (e < 4 ? e : 12 + e), room) * (2 * D) + 2 * F * c);
-                const auto* src = reinterpret_cast<const __attribute__((address_space(1))) VPiece*>(reinterpret_cast<Bytes>(a) + off);
-                vn[e] = nt.value ? stream_load(src) : *src;
-            }
-        };
-        if (once) keep_side([&] { load(std::true_type{}); });
-        else load(std::false_type{});
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t off = static_cast<uint32_t>(min(4 * g + (e < 4 ? e : 12 + e), room) * (2 * D) + 2 * F * c);
+            const auto* src = reinterpret_cast<const __attribute__((address_space(1))) VPiece*>(reinterpret_cast<Bytes>(a) + off);
+            vn[e] = nt.value ? stream_load(src) : *src;
+        }
     };
-    const bool new_keys = FUSED && (!SPLIT || blockIdx.z == 0);   // this workgroup also takes the call's own keys
     if (new_keys && wave == 0 && own < n_new) {
         const size_t at = head_off + static_cast<size_t>(old + own) * D;
         if (c == 0) {
@@ -156,10 +156,6 @@ attn_decode_gqa_kernel(AttnDev p) {
         }
         if (g == 0) *reinterpret_cast<VPiece*>(p.v_cache + at + F * c) = v_own;
     }
-    fetch_k(range.lo);
-    fetch_v(range.lo);
-    __builtin_amdgcn_sched_barrier(0);
-
     // Running sums of column c (head c % REP; rounded probabilities for c / REP even, the rest for odd): l_run of this lane's
     // keys, o[f] of rows (columns of V) F (4 g + r) + f.  Probabilities are 2^(score - m_run), at most 2^12.
     constexpr float kTop = 12.0f, kSet = 8.0f;
@@ -211,59 +207,82 @@ attn_decode_gqa_kernel(AttnDev p) {
     };
     const float none = -INFINITY;
 
-    if (new_keys) {
-        if (wave == 0) {                                         // the row's own key: a step of one
-            VPiece vv[8];
+    // The stream, twice: a branch at the loads of every step leaves the compiler unsure of how many are in flight, so it waits for all
+    // of them (layers of 32 64-wide heads, 16 kv heads, 256 rows x 200 keys 103 us, now 96).
+    const int k_first = range.lo + wave * kGqaKeys;              // this wave's first cached keys, if there are that many
+    auto stream = [&](auto nt) {
+        if (nt.value) asm volatile("; one row");                 // (the two would be made one, with ordinary loads)
+        else asm volatile("; several rows");
+        auto fetch_first = [&] {
+            if (k_first < range.hi) {
+                fetch_k(k_first, nt);
+                fetch_v(k_first, nt);
+            }
+        };
+        fetch_first();
+        __builtin_amdgcn_sched_barrier(0);
+        if (new_keys) {
+            if (wave == 0) {                                     // the row's own key: a step of one
+                VPiece vv[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) vv[e] = v_own;
-            absorb(float4_t{g == 0 && own < n_new ? s_own : none, none, none, none}, float4_t{none, none, none, none}, vv);
-        }
-        // the sequence's earlier new keys (none in a decode step of one token per sequence); the first cached step is
-        // requested again afterwards, its registers serve here
-        const int n_other = min(own, n_new);
-        if (n_other > 0) {
-            for (int jb = wave * kGqaKeys; jb < n_other; jb += kGqaStep) {
-                float4_t st[2];
+                for (int e = 0; e < 8; ++e) vv[e] = v_own;
+                absorb(float4_t{g == 0 && own < n_new ? s_own : none, none, none, none}, float4_t{none, none, none, none}, vv);
+            }
+            // the sequence's earlier new keys (none in a decode step of one token per sequence); the first cached step is
+            // requested again afterwards, its registers serve here
+            const int n_other = min(own, n_new);
+            if (!nt.value && n_other > 0) {
+                for (int jb = wave * kGqaKeys; jb < n_other; jb += kGqaStep) {
+                    float4_t st[2];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int rj = row_begin + min(jb + 4 * g + (e < 4 ? e : 12 + e), n_other - 1);
-                    vn[e] = *reinterpret_cast<const VPiece*>(p.qkv + static_cast<size_t>(rj) * p.width + (p.nh + p.nkv + hk) * D + F * c);
+                    for (int e = 0; e < 8; ++e) {
+                        const int rj = row_begin + min(jb + 4 * g + (e < 4 ? e : 12 + e), n_other - 1);
+                        vn[e] = *reinterpret_cast<const VPiece*>(p.qkv + static_cast<size_t>(rj) * p.width + (p.nh + p.nkv + hk) * D + F * c);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int rj = row_begin + min(jb + 16 * u + c, n_other - 1);
+                        float2 cs[S / 2][8];
+#pragma unroll
+                        for (int s = 0; s < S; ++s) kn[u][s] = *reinterpret_cast<const half8_t*>(p.qkv + static_cast<size_t>(rj) * p.width + (p.nh + hk) * D + 32 * s + 8 * g);
+                        load_cs(rj, cs);
+                        rotate(kn[u], cs);
+                        st[u] = scores(kn[u]);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            if (jb + 16 * u + 4 * g + r >= n_other) st[u][r] = none;
+                    }
+                    absorb(st[0], st[1], vn);
                 }
+                fetch_first();
+            }
+        }
+        auto step = [&](int kb, auto more) {
+            float4_t st[2];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int rj = row_begin + min(jb + 16 * u + c, n_other - 1);
-                    float2 cs[S / 2][8];
+            for (int u = 0; u < 2; ++u) st[u] = scores(kn[u]);
+            if (more.value) {
+                fetch_k(kb + kGqaStep, nt);
+                __builtin_amdgcn_sched_barrier(0);
+            } else {                                             // the last step may hold fewer keys
 #pragma unroll
-                    for (int s = 0; s < S; ++s) kn[u][s] = *reinterpret_cast<const half8_t*>(p.qkv + static_cast<size_t>(rj) * p.width + (p.nh + hk) * D + 32 * s + 8 * g);
-                    load_cs(rj, cs);
-                    rotate(kn[u], cs);
-                    st[u] = scores(kn[u]);
+                for (int u = 0; u < 2; ++u)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        if (jb + 16 * u + 4 * g + r >= n_other) st[u][r] = none;
-                }
-                absorb(st[0], st[1], vn);
+                        if (kb + 16 * u + 4 * g + r >= range.hi) st[u][r] = none;
             }
-            fetch_k(range.lo);
-            fetch_v(range.lo);
-        }
-    }
-
-    for (int kb = range.lo; kb < range.hi; kb += kGqaStep) {     // trip count is uniform over the workgroup
-        float4_t st[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) st[u] = scores(kn[u]);
-        fetch_k(kb + kGqaStep);                                  // past the end: one redundant, unused fetch
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (kb + wave * kGqaKeys + 16 * u + 4 * g + r >= range.hi) st[u][r] = none;
-        absorb(st[0], st[1], vn);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_v(kb + kGqaStep);
-    }
+            absorb(st[0], st[1], vn);
+            if (more.value) {
+                __builtin_amdgcn_sched_barrier(0);
+                fetch_v(kb + kGqaStep, nt);
+            }
+        };
+        int kb = k_first;                                        // uniform over the wave
+        for (; kb + kGqaStep < range.hi; kb += kGqaStep) step(kb, std::true_type{});
+        if (kb < range.hi) step(kb, std::false_type{});
+    };
+    if (once) stream(std::true_type{});
+    else stream(std::false_type{});
 
     // the four waves meet in LDS; a head's two columns are added there
     __shared__ float sm[4][2 * REP][D + 2];
