@@ -332,20 +332,31 @@ static bool wide_round(const GemmDev& d) {
     return d.KT >= 32 && d.M_max > kGemmWideRows && cols * ((d.M_max + 63) / 64) > cus && gemm_wide_blocks(d) <= cus;
 }
 
-// Above 256 rows, outputs that the 128 x 256 tiles would take and the 128-row kernel with two workgroups per CU takes faster: gate/up
-// in three chunks of which the last is not full, and outputs whose tiles are a few more than the CUs (they take one round, but
-// some CUs hold two tiles and most one) while the last chunk is half empty at least.  us, tiles / this kernel: gate/up 14336 x
-// 4096 at 257, 320, 352, 384 rows 100 / 82, 101 / 89, 102 / 97, 102 / 104, 13824 x 5120 125 / 100, 124 / 110, 125 / 118, 126 / 127,
-// 11008 x 4096 at 330, 352, 384 96 / 87, 97 / 87, 96 / 99, 5632 x 2048 33 / 30, 33 / 30, 33 / 33; at 400 rows (four chunks) 144 /
-// 147, 105 / 100; tiles 1.03 to 1.17 times the CUs: store 6144 x 4096 at 1300 rows 97 / 79 (1408, full, 98 / 99), 12288 x 4096 at
-// 700 99 / 89 (768 99 / 100), 15360 x 5120 at 513 and 560 122 / 109, 122 / 108 (640 123 / 122), gate/up 5632 x 2048 at 700 53 / 44.
+// Above 256 rows, outputs that the 128 x 256 tiles would take and the 128-row kernel with two workgroups per CU takes faster.  Its row
+// chunks are full but the last; the full ones have to run at once, on the XCD that holds most columns too (it deals columns to XCDs),
+// and the rest finds room beside and behind them.  us, tiles / this kernel (4 bit, groups of 128, unless stated):
+//   three chunks (257 to 352 rows, the last one to three fragments of four), gate/up: 14336 x 4096 at 300 and 352 rows 107 / 95, 109 / 101,
+//     11008 x 4096 at 330 and 352 99 / 92, 100 / 92, with K = 1024 33.6 / 32.3, K = 512 21.3 / 22.8, 13184 x 512 at 257 22.2 / 22.1;
+//     16384 columns (64 full chunks per XCD) at 300 113 / 99, K = 1024 36.8 / 34.1; 16768 (66) at 320 and 352 112 / 113, 113 / 123,
+//     18944 118 / 123, 119 / 131, 21760 129 / 142, 126 / 154 (K = 1024 40 / 47, 40 / 52).  Wider, the tiles need a second round too:
+//     21888 at 257, 320, 352 rows 143 / 134, 159 / 137, 184 / 152, 26624 155 / 144, 169 / 161, 203 / 170, 30720 165 / 172, 180 / 186,
+//     224 / 200.  The same within 3 % for 2 and 3 bit, groups of 32 and K = 2048 to 8192.
+//   more chunks, the last half full at most, tiles that are a few more than the CUs (they take one round, but some CUs hold two tiles
+//     and most one): store 12288 x 4096 at 700 rows 101 / 90, 6144 x 4096 at 1300 100 / 84, K = 1024 33 / 29, K = 512 22.0 / 20.4, 3 bit
+//     97 / 81, groups of 32 105 / 82; 15616 x 1024 at 560 (64 per XCD) 33.2 / 31.1; gate/up 9728 x 4096 at 448 104 / 91, 4544 x 4096 at 940
+//     (63) 99 / 88; but 65 per XCD and more are level or lose: store 12544 x 1024 at 690 (65) 32.9 / 33.4, 6272 x 1024 at 1300 (70) 32.4 /
+//     33.3, 4608 x 1024 at 1984 (75) 33.6 / 34.8, gate/up 6528 at 704 (65) K = 512 22.3 / 23.7, K = 4096 104 / 102.
 // (Only where the host knows the row count: workgroups without rows leave one of the two per CU alone, which is slower than four
 // slices.)
 static bool two_slices_win(const GemmDev& d, bool swiglu, int cus) {
     if (d.count && !d.rows_exact) return false;
-    if (swiglu && d.M_max > kGemmWideRows && d.M_max <= 352) return true;
-    const int tiles = ((d.M_max + 127) / 128) * ((d.vf_total + 7) / 8);
-    return tiles > cus && 5 * tiles <= 6 * cus && (d.M_max - 1) % 128 < 64;
+    const int chunks = gemm_wide_chunks(d), tiles = chunks * ((d.vf_total + 7) / 8);
+    const bool at_once = (gemm_wide_cols(d) + 7) / 8 * (chunks - 1) <= 2 * cus / 8;
+    if (swiglu && d.M_max <= 352) {
+        if (at_once) return d.M_max <= 320 || d.KT >= 16;
+        return tiles > 2 * cus && (d.M_max > 320 ? tiles <= 3 * cus : 2 * tiles <= 5 * cus);
+    }
+    return at_once && tiles > cus && 5 * tiles <= 6 * cus && (d.M_max - 1) % 128 < 64;
 }
 
 // Residual outputs above 64 rows on the 128-row kernel: the number of K parts, as many as one round of the chip takes and the

@@ -137,15 +137,19 @@ def test_linear_that_fills_one_round_of_128_row_workgroups(qt, M, N, bits, G, K)
 
 
 # two k-slices (two workgroups per CU): gate/up in two chunks with K of 64 k-tiles and more (odd numbers of rounds, every
-# remainder of the ring, a ragged last k-tile), in three chunks with a short K, and outputs whose large tiles are a few more
-# than the CUs; 1 to 4 live row fragments in the last chunk
+# remainder of the ring, a ragged last k-tile), in three chunks with a short K (of 16 k-tiles above 320 rows), with a width whose
+# full chunks run at once and one whose large tiles take a second round, and outputs whose large tiles are a few more than the CUs;
+# 1 to 4 live row fragments in the last chunk.  (200 k-columns at 352 rows and 353 rows are the large tiles'.)
 @pytest.mark.parametrize("M,I,K,G,bits", [(129, 8328, 4096, 128, 4), (160, 8328, 4104, 64, 3), (193, 8328, 4168, 32, 2), (256, 8328, 4352, 128, 4),
                                           (150, 8328, 4296, 32, 4), (257, 13192, 72, 64, 4), (320, 13192, 136, 128, 2), (352, 13192, 200, 32, 3),
-                                          (353, 13192, 136, 64, 4), (700, 5640, 264, 128, 4), (644, 5640, 72, 32, 4)])
+                                          (353, 13192, 136, 64, 4), (352, 13192, 1032, 32, 3), (321, 16376, 1000, 64, 4), (257, 21896, 72, 32, 2),
+                                          (352, 21896, 136, 128, 4), (385, 9352, 264, 128, 4), (420, 9352, 72, 32, 4), (448, 9352, 200, 64, 3)])
 def test_swiglu_on_two_slices(qt, M, I, K, G, bits):
     test_swiglu_of_a_hundred_rows(qt, M, I, K, G, bits)
 
 
-@pytest.mark.parametrize("M,N,K,G,bits", [(1300, 6152, 136, 128, 4), (1313, 6152, 72, 32, 3), (700, 12296, 328, 64, 4), (705, 12296, 136, 32, 2)])
+# (the second of each pair of widths is one column block too wide, the last row count has a last chunk of more than half)
+@pytest.mark.parametrize("M,N,K,G,bits", [(1300, 6136, 136, 128, 4), (1300, 6152, 136, 128, 4), (1313, 6136, 72, 32, 3), (1313, 6152, 72, 32, 3),
+                                          (700, 12280, 328, 64, 4), (700, 12296, 328, 64, 4), (704, 12280, 136, 32, 2), (705, 12296, 136, 32, 2)])
 def test_linear_on_two_slices(qt, M, N, K, G, bits):
     test_linear_of_a_hundred_rows(qt, M, N, K, G, bits)
