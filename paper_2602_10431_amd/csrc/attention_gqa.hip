@@ -13,10 +13,15 @@
 //     between lanes;
 //   * V^T needs eight keys of one column per lane.  Lane (c, g) loads columns F c .. F c + F - 1 (F = D / 16: whole rows, 4 per
 //     instruction) of those eight keys, and fragment f takes column F c + f of each lane: 4 F byte permutes per step, no LDS;
-//   * the probabilities keep their 32 bits: as an fp16 operand a probability is split into its rounded value and the rest,
-//     which go to two of the 16 columns (heads fill 2, 4 or 8), so both products come from the same instruction.  The
-//     reference point of the exponentials is at most 12 log2 units below the largest score and follows lazily, so the rest is
-//     never far below fp16's range: what is lost is under 2^-25 against sums of 2^8 and more;
+//   * as an fp16 operand a probability (at most 2^4) is split into its rounded value and 2048 times the rest, which go to two of
+//     the 16 columns (heads fill 2, 4 or 8), so both products come from the same instruction.  The rest is rounded too: what is
+//     lost is at most 2^-23 of the probability, or 2^-36.  The reference point of the exponentials follows the largest score
+//     lazily.  Error of the sums before they are rounded to fp16, against 64 bits (2-norm, 700 to 12000 normal keys and values), on
+//     the vector ALUs, where probabilities were 32-bit operands / here: 128-wide heads, 2, 4, 8 per kv head 1.83e-7 / 1.64e-7,
+//     1.82 / 1.71, 1.84 / 1.68, 64-wide 1.70 / 1.68, 1.78 / 1.75, 1.73 / 1.77; scores four times as large 4.2 to 4.5 / 3.6 to 4.0,
+//     3.8 to 4.0 / 3.5; values of one sign 0.25 / 0.3 (the matrix instruction's additions).  The outputs' own rounding is 2.4e-4.
+//     (Reference 8 to 12 log2 units below the largest score, the rest not scaled, one chain per score: 2.2 to 2.4, large scores up
+//     to 5.2.)
 //   * a step's keys are requested again as soon as the scores are formed, its values as soon as they are consumed: 16 KB per
 //     wave in flight with one register set, three waves per SIMD (four with 64-wide heads).  A wave's last step requests nothing
 //     and a wave without cached keys makes no step: short caches are bound by the launch of many workgroups.
@@ -74,11 +79,14 @@ attn_decode_gqa_kernel(AttnDev p) {
                 t[s + S / 2][e] = static_cast<half_t>(fmaf(hi, cs[s][e].x, lo * cs[s][e].y));
             }
     };
-    auto scores = [&](const half8_t* k) {
-        float4_t st = {0.f, 0.f, 0.f, 0.f};
+    auto scores = [&](const half8_t* k) {                        // 64 columns per chain: one of 128 rounds twice as large sums as often
+        float4_t sum[S / 2];
 #pragma unroll
-        for (int s = 0; s < S; ++s) st = __builtin_amdgcn_mfma_f32_16x16x32_f16(k[s], q[s], st, 0, 0, 0);
-        return st;
+        for (int s = 0; s < S; s += 2) {
+            sum[s / 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k[s], q[s], float4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            sum[s / 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(k[s + 1], q[s + 1], sum[s / 2], 0, 0, 0);
+        }
+        return S == 2 ? sum[0] : sum[0] + sum[S / 2 - 1];
     };
 #pragma unroll
     for (int s = 0; s < S; ++s) q[s] = *reinterpret_cast<const half8_t*>(row_i + (hk * REP + (c & (REP - 1))) * D + 32 * s + 8 * g);
@@ -157,10 +165,10 @@ attn_decode_gqa_kernel(AttnDev p) {
         if (g == 0) *reinterpret_cast<VPiece*>(p.v_cache + at + F * c) = v_own;
     }
     // Running sums of column c (head c % REP; rounded probabilities for c / REP even, the rest for odd): l_run of this lane's
-    // keys, o[f] of rows (columns of V) F (4 g + r) + f.  Probabilities are 2^(score - m_run), at most 2^12.
-    constexpr float kTop = 12.0f, kSet = 8.0f;
+    // keys, o[f] of rows (columns of V) F (4 g + r) + f.  Probabilities are 2^(score - m_run), at most 2^kTop.
+    constexpr float kTop = 4.0f, kScale = 2048.0f;
     const float sc = p.scale_log2;
-    const float rest = (c / REP) & 1 ? -1.0f : 0.0f;
+    const float rest = (c / REP) & 1 ? -1.0f : 0.0f, scale = (c / REP) & 1 ? kScale : 1.0f;
     float m_run = kNegBig, l_run = 0.0f;
     float4_t o[F];
 #pragma unroll
@@ -171,7 +179,7 @@ attn_decode_gqa_kernel(AttnDev p) {
         if (__any(mx > m_run + kTop)) {
             mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));              // the column's largest score: all its lanes move together
-            const float m_new = mx > m_run + kTop ? mx - kSet : m_run;
+            const float m_new = mx > m_run + kTop ? mx : m_run;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
             l_run *= alpha;
 #pragma unroll
@@ -188,8 +196,8 @@ attn_decode_gqa_kernel(AttnDev p) {
             pv[1] = __builtin_amdgcn_exp2f(fmaf(e < 4 ? st0[e + 1] : st1[e - 3], sc, -m_run));
             l_run += pv[0] + pv[1];
             const half2_t hi = __builtin_convertvector(pv, half2_t);
-            pv[0] = fmaf(rest, static_cast<float>(hi[0]), pv[0]);   // exact
-            pv[1] = fmaf(rest, static_cast<float>(hi[1]), pv[1]);
+            pv[0] = fmaf(rest, static_cast<float>(hi[0]), pv[0]) * scale;   // exact
+            pv[1] = fmaf(rest, static_cast<float>(hi[1]), pv[1]) * scale;
             const half2_t h = __builtin_convertvector(pv, half2_t);
             pb[e] = h[0];
             pb[e + 1] = h[1];
@@ -305,7 +313,7 @@ attn_decode_gqa_kernel(AttnDev p) {
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const float a = exp2f(sm[w][r][D] - mn);
-            num += (sm[w][r][e] + sm[w][r + REP][e]) * a;
+            num += fmaf(sm[w][r + REP][e], 1.0f / kScale, sm[w][r][e]) * a;
             den += sm[w][r][D + 1] * a;
         }
         if (SPLIT) {
