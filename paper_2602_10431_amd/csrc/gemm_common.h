@@ -21,7 +21,7 @@ struct GemmDev {
     const int32_t* idx;
     int bf16;
     int bits;                      // 4, 3 or 2: width of the weight codes
-    int in_layer;                  // called by a layer (few-row kernel)
+    int streams;                   // GemmArgs::streams (few-row kernel)
     int chunk_rows;                // wide kernel: rows per chunk
     int ksplit;                    // decode kernel: parts K is cut into across workgroups (1 = none)
     int epi_rt;                    // decode kernel: epilogue chosen at run time (GemmEpilogue)

@@ -348,20 +348,22 @@ gemm_few_kernel(FewDev a) {
     }
 }
 
-// Layer calls of at most eight rows, weights of at least 12 MB: non-temporal loads.  They are read once per call, and as ordinary loads the layers
-// of a step push each other out of the memory-side cache (256 MB) before any is used again.  Whole layer, one token unless stated,
-// us, ordinary / non-temporal, over 3, 6 and 20 layers' weights in rotation: 7B shape 53.7 / 51.2, 54.6 / 51.4, 54.6 / 53.5; 8B-GQA 52.2 /
-// 50.1, 52.7 / 50.3, 52.8 / 52.3, 4 tokens 58.6 / 56.6, 59.2 / 56.7, 59.3 / 58.9; 13B, 2 tokens 67.8 / 65.9, 67.9 / 65.6, 68.0 / 65.8.
-// What fits that cache together is better left there: smaller layers (hidden 2048, 3 layers 32.4 / 33.9, 24 layers 36.5 / 34.4; 2-bit
-// 7B 47.0 / 47.9, 51.2 / 48.1, 51.9 / 51.6) and linears called by themselves (4096 x 14336, 3 rows 8.2 / 9.8, 8.2 / 10.1, 10.6 / 10.2).
-// 5 to 8 rows: 7B, 8 rows 63.2 / 60.9, 65.5 / 61.1, 68.0 / 64.3; 8B-GQA, 8 rows 67.0 / 63.0, 67.6 / 63.3, 67.8 / 67.7; 13B, 6 rows 82.2 /
-// 77.8, 82.8 / 78.0, 82.0 / 78.8; four 8B-GQA layers of a stack 290.0 / 290.1.  16 rows: 8B-GQA 77.9 / 73.9, 79.1 / 74.3, 79.1 / 80.5, so there the
-// ordinary loads stay.
+// Layer calls of at most eight rows, 4-bit weights of at least 6 MB: non-temporal loads.  They are read once per call, and where the
+// layers that take turns do not fit the memory-side cache (256 MB) together, ordinary loads push each other's out of it before any is
+// used again.  Whole layers, us, ordinary / non-temporal, 1 and 8 tokens: 7B shape, 322 MB of weights in turn 54.4 / 53.0, 75.4 / 73.9,
+// 2 GB 54.7 / 53.0, 74.5 / 72.4; 8B-GQA 347 MB 53.1 / 52.0, 67.9 / 66.2, 2 GB 53.2 / 52.0, 67.9 / 67.3; 13B 2 GB 65.7 / 64.1, 95.8 / 93.8; hidden
+// 2560 1.5 GB 38.6 / 38.1, 55.1 / 53.2 (without the linears of 9 MB 39.1, 55.7); 2048, SwiGLU 8192 854 MB 37.3 / 36.1, 51.0 / 48.9; 5632 382 MB
+// 34.7 / 32.9, 44.3 / 41.1, 860 MB 34.9 / 34.9, 44.3 / 44.0; 1536 420 MB 32.2 / 31.4, 45.3 / 44.3.
+// What fits the cache together is better left there.  A stack knows that (fits_cache, qtale_api.hip): 7B 215 MB 50.8 / 52.3, 71.6 / 74.4,
+// 8B-GQA 231 MB 50.3 / 51.9, 64.0 / 65.4, 13B 168 MB 60.4 / 62.0, 91.0 / 100.  Of a call of a single layer it is taken that others follow;
+// models whose largest linear is below 6 MB fit whole (24 layers of hidden 1024 163 MB, from 1 MB on 38.1 / 39.3 with 8 tokens, of 1280 252 MB 41.0 /
+// 41.8).  Linears called by themselves keep ordinary loads (4096 x 14336, 3 rows 8.2 / 9.8), as do more rows (8B-GQA, 16 rows, 20
+// layers 79.1 / 80.5) and 2-bit weights (7B 47.0 / 47.9, 51.9 / 51.6).
 static bool few_streams(const GemmDev& d) {
-    if (!d.in_layer || d.bits != 4 || d.M_max > 8) return false;
+    if (!d.streams || d.bits != 4 || d.M_max > 8) return false;
     size_t bytes = 0;
     for (int i = 0; i < d.n_w; ++i) bytes += static_cast<size_t>(d.NF[i]) * d.KT * 64 * (4 * d.bits);
-    return bytes >= (12u << 20);
+    return bytes >= (6u << 20);
 }
 
 template <int BITS, int GPT, bool SWIGLU, int NF, int NP, int NK, int MR, int PRO, bool NT_LOADS = false>

@@ -484,7 +484,7 @@ hipError_t launch_gemm_w4a16(const GemmArgs& a, hipStream_t stream) {
     d.idx = a.idx;
     d.bf16 = a.bf16;
     d.bits = a.bits;
-    d.in_layer = a.in_layer;
+    d.streams = a.streams;
     // Few rows: the weight stream dominates and 128-row tiles cannot fill the chip.  Each range has a kernel of its own:
     // gemm_few.h, launch_small_rows, launch_mid_rows.
     if (a.n_parts) *a.n_parts = 0;

@@ -193,7 +193,21 @@ struct LayerLink {
     const qtale_layer_weights* next = nullptr;  // in: the next layer, or null
     float* next_z = nullptr;                    // in: where its scores go
     bool next_scored = false;                   // out: they were written
+    bool cached = false;                        // in: the stack's weights fit the memory-side cache together
 };
+
+// Whether the linears of all layers stay in the 256 MB memory-side cache from one call to the next (gemm_few.h: few_streams).
+bool fits_cache(const qtale_layer_cfg* c, const qtale_layer_weights* layers, int n_layers) {
+    size_t bytes = 0;
+    for (int l = 0; l < n_layers; ++l) {
+        const int bits = layers[l].bits ? layers[l].bits : c->bits;
+        for (const qtale_qlinear* w : {&layers[l].q, &layers[l].k, &layers[l].v, &layers[l].o, &layers[l].gate, &layers[l].up, &layers[l].down}) {
+            const PrepackDims pd = prepack_dims(w->N, w->K, c->group, bits);
+            bytes += pd.code_bytes + pd.sz_bytes;
+        }
+    }
+    return bytes <= (size_t{256} << 20);
+}
 
 int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_layer_weights* w, void* x, int T,
                        const int32_t* seq_offsets, int B, const int32_t* positions, const qtale_kv* kv,
@@ -207,6 +221,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     const int M_max = ratio_mode ? k : T;
     float* z = scores ? scores : ws.z;
     int32_t* count = ws.scalars;
+    const int streams = !(link && link->cached);
 
     SelectArgs s{};
     s.z = z; s.T = T; s.mode = ratio_mode ? 0 : 1; s.k = k;
@@ -238,7 +253,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     }
     const int qkv_w = (nh + 2 * nkv) * d;
     GemmArgs qg{};
-    qg.A = ws.nbuf; qg.count = count; qg.M_max = M_max; qg.rows_exact = ratio_mode; qg.in_layer = 1; qg.K = H; qg.group = c->group; qg.bits = lbits; qg.n_w = 3;
+    qg.A = ws.nbuf; qg.count = count; qg.M_max = M_max; qg.rows_exact = ratio_mode; qg.streams = streams; qg.K = H; qg.group = c->group; qg.bits = lbits; qg.n_w = 3;
     qg.w[0] = {w->q.prepacked, w->q.N, w->q.K};
     qg.w[1] = {w->k.prepacked, w->k.N, w->k.K};
     qg.w[2] = {w->v.prepacked, w->v.N, w->v.K};
@@ -330,7 +345,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     {
         Prof pr(ctx, stream, 6);
         GemmArgs g{};
-        g.A = ws.attn; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.in_layer = 1; g.K = nh * d; g.group = c->group; g.bits = lbits; g.n_w = 1;
+        g.A = ws.attn; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.streams = streams; g.K = nh * d; g.group = c->group; g.bits = lbits; g.n_w = 1;
         g.w[0] = {w->o.prepacked, w->o.N, w->o.K};
         g.epilogue = EPI_RESID_F32; g.out = ws.h; g.ldo = H; g.resid = x; g.idx = ws.idx; g.bf16 = bf16;
         g.part = o_part; g.part_floats = o_floats; g.n_parts = &o_parts;
@@ -347,7 +362,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     {
         Prof pr(ctx, stream, 8);
         GemmArgs g{};
-        g.A = ws.nbuf; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.in_layer = 1; g.K = H; g.group = c->group; g.bits = lbits; g.n_w = 2;
+        g.A = ws.nbuf; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.streams = streams; g.K = H; g.group = c->group; g.bits = lbits; g.n_w = 2;
         g.w[0] = {w->gate.prepacked, w->gate.N, w->gate.K};
         g.w[1] = {w->up.prepacked, w->up.N, w->up.K};
         g.epilogue = EPI_SWIGLU_F16; g.out = ws.act; g.ldo = I;
@@ -360,7 +375,7 @@ int layer_forward_impl(qtale_ctx* ctx, const qtale_layer_cfg* c, const qtale_lay
     {
         Prof pr(ctx, stream, 9);
         GemmArgs g{};
-        g.A = ws.act; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.in_layer = 1; g.K = I; g.group = c->group; g.bits = lbits; g.n_w = 1;
+        g.A = ws.act; g.count = count; g.M_max = M_max; g.rows_exact = ratio_mode; g.streams = streams; g.K = I; g.group = c->group; g.bits = lbits; g.n_w = 1;
         g.w[0] = {w->down.prepacked, w->down.N, w->down.K};
         g.epilogue = EPI_RESID_SCATTER; g.out = x; g.ldo = H; g.resid = ws.h; g.idx = ws.idx; g.bf16 = bf16;
         int d_parts = 0;
@@ -607,6 +622,7 @@ int qtale_stack_forward(qtale_ctx* ctx, const qtale_layer_cfg* cfg, const qtale_
     const Workspace ws = carve(cfg, T, B, workspace);
     const size_t row_bytes = static_cast<size_t>(cfg->hidden) * 2;
     bool scores_ready = false;
+    const bool cached = fits_cache(cfg, layers, n_layers);
     for (int l = 0; l < n_layers; ++l) {
         if (dbg_hidden) {
             HIP_TRY(hipMemcpyAsync(reinterpret_cast<char*>(dbg_hidden) + static_cast<size_t>(l) * T * row_bytes, x,
@@ -614,6 +630,7 @@ int qtale_stack_forward(qtale_ctx* ctx, const qtale_layer_cfg* cfg, const qtale_
         }
         LayerLink link;
         link.scores_ready = scores_ready;
+        link.cached = cached;
         if (l + 1 < n_layers) {
             link.next = &layers[l + 1];
             link.next_z = scores ? scores + static_cast<size_t>(l + 1) * T : ws.z;

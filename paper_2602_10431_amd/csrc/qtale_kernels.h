@@ -147,7 +147,7 @@ struct GemmArgs {
     int K;
     int group;
     int bits;                  // 4, 3 or 2
-    int in_layer;              // nonzero: one of a layer's linears, the others come before it is called again
+    int streams;               // nonzero: more weights than the memory-side cache holds are read before these are again
     int n_w;                   // number of weight matrices: 1, 2 (gate/up interleaved), 3 (q|k|v concatenated)
     GemmWeights w[3];
     int epilogue;

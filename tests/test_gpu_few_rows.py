@@ -205,3 +205,22 @@ def test_few_row_stack_is_the_same_on_every_run(qt):
         outs.append((x.cpu(), [kv.k.cpu() for kv in kvs]))
     for x, ks in outs[1:]:
         assert torch.equal(x, outs[0][0]) and all(torch.equal(a, b) for a, b in zip(ks, outs[0][1]))
+
+
+@pytest.mark.parametrize("T", [1, 4, 5, 8])
+@pytest.mark.parametrize("I,G", [(6152, 128), (6136, 32)])
+def test_streamed_weights_give_the_bits_of_cached_ones(qt, T, I, G):
+    # gate/up of 6 MB: non-temporal loads in a call of a single layer (just below it: ordinary ones), ordinary loads in a stack whose
+    # weights fit the memory-side cache
+    shape = si.LayerShape(1024, 16, 4, 64, I, 4, G, "fp16")
+    _check_layer(qt, shape, T, [T - T // 2, T // 2], "ratio", 1.0, seed=60 + T)
+    layer = qt.quantize_layer(si.layer_tensors(shape, 0, 60 + T, unit_gains=False), 4, G)
+    cfg, ctx = qt.cfg_from_shape(shape), qt.Context()
+    qt.qtale_set_exec_ratio(ctx, 1.0)
+    x0 = si.hidden_states(shape, T, 60 + T).cuda()
+    offs, pos = (t.cuda() for t in si.ragged_sequences([T - T // 2, T // 2]))
+    xl, xs = x0.clone(), x0.clone()
+    qt.qtale_layer_forward(ctx, cfg, layer, xl, offs, pos)
+    qt.qtale_stack_forward(ctx, qt.Stack(cfg, [layer]), xs, offs, pos)
+    torch.cuda.synchronize()
+    assert torch.equal(xl, xs)
