@@ -217,11 +217,7 @@ struct WBits<2> {
     static __device__ __forceinline__ Tile load(const void* frag_base, int kt, int lane) {
         return (reinterpret_cast<const u32x2_t*>(frag_base) + static_cast<size_t>(kt) * 64)[lane];
     }
-    template <bool NT = false>
-    static __device__ __forceinline__ Tile load_lane(const char* lane_ptr) {
-        const Tile* p = reinterpret_cast<const Tile*>(lane_ptr);
-        return NT ? __builtin_nontemporal_load(p) : *p;
-    }
+    static __device__ __forceinline__ Tile load_lane(const char* lane_ptr) { return *reinterpret_cast<const u32x2_t*>(lane_ptr); }
     static __device__ __forceinline__ SZ expand(uint32_t raw) { return expand_sz2(raw); }
     static __device__ __forceinline__ half8_t dequant(const Tile& t, int j, const SZ& s, uint32_t magic) {
         const half2_t p0 = dequant_pair2(t, 4 * j + 0, s, magic);
@@ -246,11 +242,10 @@ struct WBits<3> {
         t.x = p[0]; t.y = p[1]; t.z = p[2];
         return t;
     }
-    template <bool NT = false>
     static __device__ __forceinline__ Tile load_lane(const char* lane_ptr) {
         const uint32_t* p = reinterpret_cast<const uint32_t*>(lane_ptr);
         Tile t;
-        t.x = p[0]; t.y = p[1]; t.z = p[2];                      // (as non-temporal loads the three words would not become one)
+        t.x = p[0]; t.y = p[1]; t.z = p[2];
         return t;
     }
     static __device__ __forceinline__ SZ expand(uint32_t raw) { return expand_sz3(raw); }

@@ -133,7 +133,9 @@ gemm_few_kernel(FewDev a) {
         const int kt = min(2 * min(step, last) + th, p.KT - 1);
 #pragma unroll
         for (int fn = 0; fn < NF; ++fn) {
-            w[fn] = WB::template load_lane<NT_LOADS>(bptr[fn] + static_cast<size_t>(kt) * (64 * WB::kLaneBytes));
+            const char* wp = bptr[fn] + static_cast<size_t>(kt) * (64 * WB::kLaneBytes);
+            if constexpr (NT_LOADS) w[fn] = WB::template load_lane<true>(wp);
+            else w[fn] = WB::load_lane(wp);
 #pragma unroll
             for (int g = 0; g < GPT; ++g) sz[fn][g] = sptr[fn][static_cast<size_t>((kt * 64 + g * 32) >> p.gshift) * npad[fn]];
         }
