@@ -668,8 +668,11 @@ bool attention_rotates(int T, int B, int rep, int hidden, int head_dim) {
 }
 
 // Few rows: cut the cached keys.  With the ranges' length set on the device they are equally long over all rows and fill the chip
-// once (`target`: about what a CU holds; grouped queries take the same time with two to six per CU); sequences of different lengths cut into equally many
-// ranges left the longest ones running alone (20 rows x 8 kv heads x 1500 to 4500 keys: 66 -> 59 us).  Without it (calls of more
+// once; sequences of different lengths cut into equally many ranges left the longest ones running alone (20 rows x 8 kv heads x 1500
+// to 4500 keys: 66 -> 59 us).  `target`: workgroups that the ranges are to be, per CU about what its registers hold with one query
+// head; grouped queries by their number, layers of 32 heads, us, two / three / four per CU, 20 rows x 3000 keys and 28 x 2000: 2
+// heads per kv head 143 / 137 / 133, 124 / 127 / 130 (64-wide 95 / 90 / 87, 83 / 84 / 86), 4 92 / 94 / 91, 8 70.1 / 71.0 / 71.6,
+// 70.8 / 73.0 / 72.2 (64-wide 54.7 / 55.8 / 55.8, 55.0 / 56.9 / 56.1); one to eight rows within 2 %.  Without it (calls of more
 // than 256 tokens) every row is cut so that about four workgroups per CU stream.
 int attention_splits(int max_rows, int nh, int nkv, int cap, bool device_chunk, int* target) {
     const int wgs = max_rows * nkv, rep = nh / nkv;
