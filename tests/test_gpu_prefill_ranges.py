@@ -30,6 +30,21 @@ def test_chunks_on_a_cache(qt, nh, nkv, d, lens, old):
     _cache_case(qt, shape, lens, old, old, max(a + o for a, o in zip(lens, old)) + 1, 810 + sum(lens) + d, 0.6)
 
 
+# more than 64 sequences: the work list is sorted by 256 threads, which also measure the ranges and clear their counters; more than 256
+# sequences: a thread takes several.  (The ranges' sums lie in the workspace, most of it in the SwiGLU's buffer: its width has room
+# for two ranges and more.)
+@pytest.mark.parametrize("B,nh,nkv,most,I", [(70, 2, 1, 2000, 24576), (70, 3, 3, 1500, 32768), (260, 1, 1, 1050, 16384)])
+@pytest.mark.parametrize("d", [64, 128])
+def test_chunks_of_many_sequences(qt, B, nh, nkv, most, I, d):
+    shape = si.LayerShape(256, nh, nkv, d, I, 4, 32, "fp16")
+    lens = [0 if b % 13 == 5 else 1 + 3 * b % 11 for b in range(B)]
+    lens[B // 2], lens[B - 1] = 130, 1
+    old = [0 if b % 9 == 2 else (most * (b * 37 % B)) // B for b in range(B)]
+    assert sum(lens) > 4 * B                                     # prefill
+    _cache_case(qt, shape, lens, old, old, most + 140, 850 + B + d, 1.0)
+    _cache_case(qt, shape, lens, old, old, most + 140, 860 + B + d, 0.6)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("mode,val", [("ratio", 1.0), ("threshold", 0.5)])
 def test_prompts_without_a_cache(qt, d, mode, val):
