@@ -397,6 +397,9 @@ static hipError_t launch_wide_parts(GemmDev& d, const GemmArgs& a, hipStream_t s
 //   129 to 256 rows with two workgroups per CU (two k-slices), four slices or mid / two slices: 11008 (344 workgroups) 130, 160, 192, 224,
 //     256 rows 48 / 43, 48 / 43, 54 / 49, 62 / 55, 63 / 62; 14336 (448) 56 / 53, 53 / 52, 59 / 58, 68 / 63, 70 / 70; 13824 x 5120 (432)
 //     69 / 63, 65 / 62, 74 / 69, 85 / 77, 87 / 85; K = 2048 18 / 20
+//     up to 160 rows (96 and at most 64) and 160 columns of workgroups, 20 per XCD, both take the same time (4 bit 0.98 to 1.02, 2 bit 0.99 to
+//     1.0) or two slices lose: 3 bit, groups of 32, 5120 k-columns, 145 rows, 154, 160, 161 columns 55 / 59, 53 / 55, 62 / 55; so four there
+//     (4 bit, groups of 128, 160 and 161 columns 52.2 / 52.6, 58.0 / 52.5; 192 rows, 3 bit, groups of 32, 129 columns 73 / 62)
 //   129 to 192 rows: 11008 (344 workgroups) 59 / 59 / 65, K = 2048 34 / 35 / 35, K = 1024 21.5 / 25 / 22; 14336 (448) 76 / 63 / 68, K = 1024
 //     26 / 26 / 24; 18944 (592, three rounds) 91 / 91 / 77;   193 to 256 rows: 11008 77 / 74 / 68, 14336 91 / 80 / 76
 // Beyond that, store: 6144 columns at 96 / 160 rows, decode / wide / mid 18 / 27 / 24, 21 / 27 / 24; 12288: 24 / 28 / 26, 45 / 29 / 37.
@@ -415,7 +418,8 @@ static hipError_t launch_mid_rows(GemmDev& d, const GemmArgs& a, hipStream_t str
         if (blocks <= cus) {                                         // one round of wide workgroups
             return d.M_max > 192 && d.KT < 32 ? launch_gemm_mid(d, a.epilogue, stream) : launch_gemm_wide(d, a.epilogue, 1, 4, stream);
         }
-        if (chunks == 2 && blocks <= 2 * cus && d.KT >= 64 && exact) return launch_gemm_wide(d, a.epilogue, 1, 2, stream);
+        const bool short_second = d.M_max <= 160 && 4 * 16 * ((gemm_wide_cols(d) + 7) / 8) <= 5 * cus;
+        if (chunks == 2 && blocks <= 2 * cus && d.KT >= 64 && exact && !short_second) return launch_gemm_wide(d, a.epilogue, 1, 2, stream);
         if (chunks == 1) return d.M_max <= 96 && d.KT >= 64 ? launch_gemm_wide(d, a.epilogue, 1, 4, stream) : launch_gemm_mid(d, a.epilogue, stream);
         if (d.M_max > 192 || blocks > 2 * cus) return launch_gemm_mid(d, a.epilogue, stream);
         if (d.KT <= 32 && 2 * blocks <= 3 * cus) return launch_gemm_skinny(d, a.epilogue, stream);

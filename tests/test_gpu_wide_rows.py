@@ -148,6 +148,13 @@ def test_swiglu_on_two_slices(qt, M, I, K, G, bits):
     test_swiglu_of_a_hundred_rows(qt, M, I, K, G, bits)
 
 
+# up to 160 rows on both sides of 160 columns of workgroups, where two k-slices begin (161 rows: below it too)
+@pytest.mark.parametrize("M,I,K,G,bits", [(129, 10240, 4096, 128, 4), (129, 10248, 4096, 128, 4), (160, 10240, 4104, 32, 3), (160, 10248, 4104, 32, 3),
+                                          (150, 10312, 4296, 32, 4), (145, 10312, 4168, 64, 2), (161, 8328, 4104, 32, 3)])
+def test_swiglu_where_two_slices_begin(qt, M, I, K, G, bits):
+    test_swiglu_of_a_hundred_rows(qt, M, I, K, G, bits)
+
+
 # (the second of each pair of widths is one column block too wide, the last row count has a last chunk of more than half)
 @pytest.mark.parametrize("M,N,K,G,bits", [(1300, 6136, 136, 128, 4), (1300, 6152, 136, 128, 4), (1313, 6136, 72, 32, 3), (1313, 6152, 72, 32, 3),
                                           (700, 12280, 328, 64, 4), (700, 12296, 328, 64, 4), (704, 12280, 136, 32, 2), (705, 12296, 136, 32, 2)])
